@@ -2584,13 +2584,17 @@ struct qtn_costmodel {
 
 namespace {
 
+// Standardised features.
+void mlp_normalize(const qtn_costmodel *cm, const float *x, int64_t n, float *out) {
+  for (int64_t i = 0; i < n; i++)
+    for (int k = 0; k < kMlpIn; k++)
+      out[i * kMlpIn + k] = (x[i * kMlpIn + k] - cm->mean[k]) * cm->inv_std[k];
+}
+
 int mlp_upload_inputs(const qtn_costmodel *cm, const float *x, int64_t n, const MlpBuffers &b,
                       bool normalize, hipStream_t s, std::vector<float> &stage) {
   stage.assign(x, x + n * kMlpIn);
-  if (normalize)
-    for (int64_t i = 0; i < n; i++)
-      for (int k = 0; k < kMlpIn; k++)
-        stage[i * kMlpIn + k] = (stage[i * kMlpIn + k] - cm->mean[k]) * cm->inv_std[k];
+  if (normalize) mlp_normalize(cm, x, n, stage.data());
   QTN_HIP(hipMemcpyAsync(b.x, stage.data(), sizeof(float) * n * kMlpIn, hipMemcpyHostToDevice, s));
   QTN_HIP(hipMemcpyAsync(b.params, cm->params.data(), sizeof(float) * kMlpParams,
                          hipMemcpyHostToDevice, s));
@@ -2665,44 +2669,44 @@ int qtn_costmodel_train(qtn_costmodel *cm, const float *x, const double *ms, int
       }
       cm->norm_set = true;
     }
-    std::vector<float> t(n * kMlpOut), m(n * kMlpOut), stage;
+    hipStream_t s = (hipStream_t)hip_stream;
+    const MlpBuffers b = mlp_buffers(d_ws, n);
+    // parameters, moments, inputs, targets and mask go up in one copy
+    std::vector<float> stage(b.m + n * kMlpOut - b.params);
+    std::copy(cm->params.begin(), cm->params.end(), stage.data());
+    std::copy(cm->m1.begin(), cm->m1.end(), stage.data() + (b.m1 - b.params));
+    std::copy(cm->m2.begin(), cm->m2.end(), stage.data() + (b.m2 - b.params));
+    mlp_normalize(cm, x, n, stage.data() + (b.x - b.params));
+    float *t = stage.data() + (b.t - b.params), *m = stage.data() + (b.m - b.params);
     for (int64_t q = 0; q < n * kMlpOut; q++) {
       m[q] = ms[q] > 0 ? 1.0f : 0.0f;
       t[q] = ms[q] > 0 ? (float)std::log(ms[q]) : 0.0f;
     }
-    hipStream_t s = (hipStream_t)hip_stream;
-    const MlpBuffers b = mlp_buffers(d_ws, n);
-    if ((rc = mlp_upload_inputs(cm, x, n, b, true, s, stage))) return rc;
-    QTN_HIP(hipMemcpyAsync(b.t, t.data(), sizeof(float) * n * kMlpOut, hipMemcpyHostToDevice, s));
-    QTN_HIP(hipMemcpyAsync(b.m, m.data(), sizeof(float) * n * kMlpOut, hipMemcpyHostToDevice, s));
-    QTN_HIP(hipMemcpyAsync(b.m1, cm->m1.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice, s));
-    QTN_HIP(hipMemcpyAsync(b.m2, cm->m2.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice, s));
-    float *hist = nullptr;
-    QTN_HIP(hipHostMalloc((void **)&hist, sizeof(float) * epochs, hipHostMallocDefault));
+    std::vector<float> hist(epochs);
+    hipError_t he = hipMemcpyAsync(b.params, stage.data(), sizeof(float) * stage.size(),
+                                   hipMemcpyHostToDevice, s);
     int step = cm->step;
-    for (int e = 0; e < epochs; e++) {
-      hipError_t he = mlp_loss_grad(b, (int)n, s);
-      if (he == hipSuccess) he = hipMemcpyAsync(hist + e, b.loss, sizeof(float), hipMemcpyDeviceToHost, s);
-      if (he == hipSuccess) he = mlp_adam(b, ++step, lr, s);
-      if (he != hipSuccess) {
-        (void)hipHostFree(hist);
-        return set_err(QTN_EDEVICE, std::string("cost-model training: ") + hipGetErrorString(he));
-      }
+    for (int e = 0; e < epochs && he == hipSuccess; e++) {
+      const int slot = e % kMlpLosses;
+      he = mlp_train_step(b, (int)n, ++step, lr, b.loss + slot, s);
+      if (he == hipSuccess && (slot == kMlpLosses - 1 || e == epochs - 1))
+        he = hipMemcpyAsync(hist.data() + (e - slot), b.loss, sizeof(float) * (slot + 1),
+                            hipMemcpyDeviceToHost, s);
     }
-    std::vector<float> p(kMlpParams), a(kMlpParams), q2(kMlpParams);
-    hipError_t he = hipMemcpyAsync(p.data(), b.params, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipMemcpyAsync(a.data(), b.m1, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipMemcpyAsync(q2.data(), b.m2, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipStreamSynchronize(s);
-    if (he != hipSuccess) {
-      (void)hipHostFree(hist);
+    const size_t back = b.m2 + kMlpParams - b.params;
+    if (he == hipSuccess)
+      he = hipMemcpyAsync(stage.data(), b.params, sizeof(float) * back, hipMemcpyDeviceToHost, s);
+    // also after an error: nothing queued may outlive the host buffers
+    const hipError_t se = hipStreamSynchronize(s);
+    if (he == hipSuccess) he = se;
+    if (he != hipSuccess)
       return set_err(QTN_EDEVICE, std::string("cost-model training: ") + hipGetErrorString(he));
-    }
-    if (loss_history) std::copy(hist, hist + epochs, loss_history);
-    (void)hipHostFree(hist);
-    cm->params.swap(p);
-    cm->m1.swap(a);
-    cm->m2.swap(q2);
+    if (loss_history) std::copy(hist.begin(), hist.end(), loss_history);
+    std::copy(stage.data(), stage.data() + kMlpParams, cm->params.begin());
+    std::copy(stage.data() + (b.m1 - b.params), stage.data() + (b.m1 - b.params) + kMlpParams,
+              cm->m1.begin());
+    std::copy(stage.data() + (b.m2 - b.params), stage.data() + (b.m2 - b.params) + kMlpParams,
+              cm->m2.begin());
     cm->step = step;
     return QTN_OK;
   } catch (...) {

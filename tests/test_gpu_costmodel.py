@@ -43,6 +43,48 @@ def test_gradient_matches_oracle(qtn, orc, gpu):
     cm.close()
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 4097])
+def test_gradient_matches_oracle_at_chunk_edges(qtn, orc, gpu, n):
+    # 16 samples per chunk; one partial gradient below 30 samples, a block per
+    # chunk above, more chunks than blocks at 4,097.  Every sum has at most
+    # 2^13 terms of FP32 rounding 6e-8: relative errors stay under 1e-4.
+    p = _rand_params(11)
+    r = np.random.default_rng(n)
+    x = r.standard_normal((n, 16)).astype(np.float32)
+    t = r.standard_normal((n, 4)).astype(np.float32)
+    m = (r.random((n, 4)) > 0.2).astype(np.float32)
+    cm = qtn.CostModel(p)
+    loss, g = cm.grad(x, t, m)
+    y = cm.predict(x)
+    rl, rg = orc.mlp_loss_grad(p.astype(np.float64), x.astype(np.float64),
+                               t.astype(np.float64), m.astype(np.float64))
+    ry = orc.mlp_forward(p.astype(np.float64), x.astype(np.float64))
+    assert abs(loss - rl) <= 1e-4 * max(1.0, rl)
+    assert np.max(np.abs(g - rg)) <= 1e-4 * max(1.0, np.max(np.abs(rg)))
+    assert np.max(np.abs(y - ry)) <= 1e-4 * max(1.0, np.max(np.abs(ry)))
+    cm.close()
+
+
+def test_training_follows_oracle_steps(qtn, orc, gpu):
+    # 70 epochs (the loss slots wrap at 64) in two calls against FP64 steps
+    p = _rand_params(12)
+    r = np.random.default_rng(13)
+    x = r.standard_normal((40, 16)).astype(np.float32)
+    ms = np.exp(r.standard_normal((40, 4)))
+    ms[::7, 1] = -1.0
+    cm = qtn.CostModel(p)
+    hist = np.concatenate([cm.train(x, ms, 66, 1e-3), cm.train(x, ms, 4, 1e-3)])
+    mu, inv = cm.normalization()
+    xs = (x.astype(np.float64) - mu) * inv
+    t, m = np.log(np.where(ms > 0, ms, 1.0)), (ms > 0).astype(np.float64)
+    q, m1, m2 = p.astype(np.float64), np.zeros(len(p)), np.zeros(len(p))
+    for k in range(70):
+        rl, g = orc.mlp_loss_grad(q, xs, t, m)
+        assert abs(hist[k] - rl) <= 1e-3 * max(1.0, rl)
+        q, m1, m2 = orc.mlp_adam(q, m1, m2, g, k + 1, 1e-3)
+    cm.close()
+
+
 def test_adam_step_matches_oracle(qtn, orc, gpu):
     p = _rand_params(5)
     g = _rand_params(6, scale=1.0)
