@@ -94,7 +94,13 @@ struct Schedule {
   int scalar_prec = 0;  // storage of the scalar slots
   std::vector<DevGroup> groups;
   std::vector<DevOp> ops;
-  std::vector<int2> ranges;  // first n_cones: each cone's leading small groups
+  // segments: groups [x, y), program at word z of prog (-1: group by group);
+  // first n_cones: each cone's leading small groups
+  std::vector<int4> ranges;
+  std::vector<uint32_t> prog;  // segment programs (device.hpp)
+  size_t prog_more = 0;        // words kept free behind them
+  int lead_prec = -1;          // arithmetic of the leading segments if all are
+                               // programs of one precision, else -1
   std::vector<int> csb, ncb;
   std::vector<int> cns;       // slices per light cone (index slicing; 1: none)
   // hybrid executor: cones whose groups after the leading segment run by
@@ -105,12 +111,16 @@ struct Schedule {
   std::vector<int32_t> stab;  // serial-offset tables of streaming operands
   std::vector<uint8_t> uperm; // 32 bytes per group: union bit of each unit bit
   std::vector<int> group_cone, group_index;  // plan position of each group
+  // place of each group in the device's group array, which leaves out the
+  // groups that run as segment programs (-1)
+  std::vector<int> dev_group;
+  std::vector<size_t> stab_at;  // first stab entry of each group
   std::vector<int> singles;   // groups also given a one-group range (tuning)
   int singles_range0 = 0;     // range index of singles[0]
   std::vector<std::vector<Task>> cone_tasks;  // after the leading small groups
   int n_cones = 0, n_nets = 0, n_angles = 0;
   size_t off_res = 0, off_angles = 0, off_desc = 0, off_fills = 0, off_groups = 0,
-         off_ops = 0, off_stab = 0, off_uperm = 0, off_ranges = 0, off_csb = 0, off_ncb = 0, off_cns = 0, off_data = 0, total = 0;
+         off_ops = 0, off_stab = 0, off_uperm = 0, off_ranges = 0, off_prog = 0, off_csb = 0, off_ncb = 0, off_cns = 0, off_data = 0, total = 0;
   int64_t scalar_off = 0, scalar_sstride = 0;
   int n_sets = 1;  // angle sets evaluated per launch (one copy of the data each)
   std::vector<char> desc_blob;  // bytes [off_desc, off_data)
@@ -758,10 +768,234 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
   return QTN_OK;
 }
 
+// What a light cone's segment programs address, for angle set 0 and in bytes
+// from the data base, with the bytes between angle sets.
+struct ProgBases {
+  int64_t table, table_stride, arena, arena_stride, scalar, scalar_stride;
+  int table_elems;
+};
+
+// Compiles groups [g0, g1) of the schedule (one light cone's, in execution
+// order) into a segment program (prog); false where a group does not fit the
+// form (union wider than 16 bits, more than 64 operands, mixed arithmetic, a
+// gate table too long for LDS): such a segment runs group by group.
+//
+// Groups of a page are put on levels: after the group that makes an operand,
+// and, as the arena reuses memory along the execution order, after every
+// group that reads or writes an arena region the group overwrites.  An
+// intermediate made and read within the page takes LDS where it fits, for the
+// levels it lives on, and then has no part in the arena's hazards.
+bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
+                     std::vector<uint32_t> &prog) {
+  if (g1 <= g0) return false;
+  const int prec = s.groups[g0].prec;
+  const int64_t es = prec == 1 ? 8 : 16;
+  if (pb.table < 0 || pb.table_elems > kProgTable) return false;
+  const int64_t most = (int64_t)1 << 30;
+  for (int g = g0; g < g1; g++) {
+    const DevGroup &G = s.groups[g];
+    if (G.prec != prec || G.w > kProgMaxWidth || G.n_ops < 1 || G.n_ops > kProgMaxOps) return false;
+    const bool scalar = G.w == G.L;
+    if (scalar ? (G.out_off - pb.scalar) / es >= most : (G.out_off - pb.arena) / 256 >= most) return false;
+    for (int k = 0; k < G.n_ops; k++) {
+      const DevOp &o = s.ops[G.op_begin + k];
+      const bool gate = o.off >= pb.table && o.off < pb.table + pb.table_elems * es;
+      if (!gate && (o.off < pb.arena || (o.off - pb.arena) % 256 || (o.off - pb.arena) / 256 >= most))
+        return false;
+    }
+  }
+  auto pieces_of = [](const DevGroup &G) {
+    const int units = G.w > 8 ? 1 << (G.w - 8) : 1;
+    return std::min(units, kProgPieces);
+  };
+  size_t prev_at = 0;
+  bool first = true;
+  for (int b = g0; b < g1;) {
+    // groups [b, e) make the page
+    int e = b, words = kPageHeader + 8, n_ops = 0;
+    while (e < g1) {
+      const int more = 4 * s.groups[e].n_ops + 4 * pieces_of(s.groups[e]) + 1;
+      if (e > b && words + more > kPageWords) break;
+      words += more;
+      n_ops += s.groups[e].n_ops;
+      e++;
+    }
+    const int n = e - b;
+    // who makes an operand: the last group of the page to write its address
+    const int op0 = s.groups[b].op_begin;  // the page's operands are [op0, op0 + n_ops)
+    std::vector<int> maker(n_ops, -1), reader(n, -1);
+    for (int i = 0; i < n; i++) {
+      const DevGroup &G = s.groups[b + i];
+      for (int k = 0; k < G.n_ops; k++) {
+        const int64_t off = s.ops[G.op_begin + k].off;
+        if (off < pb.arena) continue;
+        for (int q = i - 1; q >= 0; q--)
+          if (s.groups[b + q].out_off == off && s.groups[b + q].w != s.groups[b + q].L) {
+            maker[G.op_begin - op0 + k] = q;
+            reader[q] = i;
+            break;
+          }
+      }
+    }
+    auto out_bytes = [&](int i) { return es << (s.groups[b + i].w - s.groups[b + i].L); };
+    std::vector<char> lds(n);
+    for (int i = 0; i < n; i++) lds[i] = reader[i] >= 0 && out_bytes(i) <= kProgPoolBytes;
+    std::vector<int> level(n), where(n, -1);
+    for (bool again = true; again;) {
+      again = false;
+      struct Use {
+        int64_t lo, hi;
+        int level;
+        bool write;
+      };
+      std::vector<Use> uses;  // arena regions touched by the groups so far
+      for (int i = 0; i < n; i++) {
+        const DevGroup &G = s.groups[b + i];
+        int lv = 0;
+        for (int k = 0; k < G.n_ops; k++)
+          if (maker[G.op_begin - op0 + k] >= 0) lv = std::max(lv, level[maker[G.op_begin - op0 + k]] + 1);
+        const bool writes = G.w != G.L && !lds[i];
+        const int64_t lo = G.out_off, hi = lo + out_bytes(i);
+        if (writes)
+          for (const Use &u : uses)
+            if (u.lo < hi && lo < u.hi) lv = std::max(lv, u.level + 1);
+        level[i] = lv;
+        for (int k = 0; k < G.n_ops; k++) {
+          const DevOp &o = s.ops[G.op_begin + k];
+          if (o.off < pb.arena || (maker[G.op_begin - op0 + k] >= 0 && lds[maker[G.op_begin - op0 + k]])) continue;
+          const int64_t sz = (o.dt == 1 ? 8ll : 16ll) << __builtin_popcount(o.mask);
+          uses.push_back({o.off, o.off + sz, lv, false});
+        }
+        if (writes) uses.push_back({lo, hi, lv, true});
+      }
+      // LDS: first fit among the intermediates alive on the same levels
+      struct Slot {
+        int at, end, from, to;
+      };
+      std::vector<Slot> pool;
+      for (int i = 0; i < n && !again; i++) {
+        if (!lds[i]) continue;
+        const int size = (int)((out_bytes(i) + 15) / 16 * 16), from = level[i], to = level[reader[i]];
+        int at = 0;
+        for (bool moved = true; moved;) {
+          moved = false;
+          for (const Slot &q : pool)
+            if (q.from <= to && from <= q.to && q.at < at + size && at < q.end) {
+              at = q.end;
+              moved = true;
+            }
+        }
+        if (at + size > kProgPoolBytes) {
+          lds[i] = 0;
+          again = true;
+        } else {
+          where[i] = at;
+          pool.push_back({at, at + size, from, to});
+        }
+      }
+    }
+    // emit
+    while (prog.size() % 4) prog.push_back(0);
+    const size_t at = prog.size();
+    if (!first) prog[prev_at + kPgNext] = (uint32_t)(at - prev_at);
+    first = false;
+    prev_at = at;
+    prog.resize(at + kPageHeader + 4 * n_ops, 0);
+    auto put64 = [&](int w, int64_t v) {
+      prog[at + w] = (uint32_t)v;
+      prog[at + w + 1] = (uint32_t)((uint64_t)v >> 32);
+    };
+    put64(kPgTableOff, pb.table);
+    put64(kPgTableStride, pb.table_stride);
+    put64(kPgArenaOff, pb.arena);
+    put64(kPgArenaStride, pb.arena_stride);
+    put64(kPgScalarOff, pb.scalar);
+    put64(kPgScalarStride, pb.scalar_stride);
+    prog[at + kPgPrec] = (uint32_t)prec;
+    prog[at + kPgTable] = (uint32_t)pb.table_elems;
+    std::vector<int> op_at(n);
+    size_t w = at + kPageHeader;
+    for (int i = 0, k0 = 0; i < n; i++) {
+      const DevGroup &G = s.groups[b + i];
+      op_at[i] = k0;
+      k0 += G.n_ops;
+      for (int k = 0; k < G.n_ops; k++) {
+        const DevOp &o = s.ops[G.op_begin + k];
+        uint32_t loc;
+        if (o.off < pb.table + pb.table_elems * es)
+          loc = kLocLds | (uint32_t)(kProgTableAt + (o.off - pb.table)) << 2;
+        else if (maker[G.op_begin - op0 + k] >= 0 && lds[maker[G.op_begin - op0 + k]])
+          loc = kLocLds | (uint32_t)(kProgPoolAt + where[maker[G.op_begin - op0 + k]]) << 2;
+        else
+          loc = (o.dt == prec ? kLocArena : kLocArenaX) | (uint32_t)((o.off - pb.arena) / 256) << 2;
+        // move masks of the compress (Hacker's Delight 7-4) of a 16-bit mask
+        uint32_t m = o.mask & 0xFFFFu, mk = ~m << 1, mv[4];
+        for (int q = 0; q < 4; q++) {
+          uint32_t mp = mk ^ (mk << 1);
+          mp ^= mp << 2;
+          mp ^= mp << 4;
+          mp ^= mp << 8;
+          mp ^= mp << 16;
+          mv[q] = mp & m & 0xFFFFu;
+          m = ((m ^ mv[q]) | (mv[q] >> (1 << q))) & 0xFFFFu;
+          mk &= ~mp;
+        }
+        prog[w++] = loc;
+        prog[w++] = mv[0] | mv[1] << 16;
+        prog[w++] = mv[2] | mv[3] << 16;
+        prog[w++] = o.mask;
+      }
+    }
+    const int n_levels = 1 + *std::max_element(level.begin(), level.end());
+    std::vector<int> by_level(n);
+    for (int i = 0; i < n; i++) by_level[i] = i;
+    // the costliest groups of a level first
+    auto cost = [&](int i) { return (double)s.groups[b + i].n_ops * std::ldexp(1.0, s.groups[b + i].w); };
+    std::stable_sort(by_level.begin(), by_level.end(), [&](int x, int y) {
+      return level[x] != level[y] ? level[x] < level[y] : cost(x) > cost(y);
+    });
+    prog[at + kPgLevels] = (uint32_t)n_levels;
+    prog[at + kPgItems] = (uint32_t)(prog.size() - at);
+    std::vector<uint32_t> begin(n_levels + 1, 0);
+    uint32_t item = 0;
+    for (int i : by_level) {
+      const DevGroup &G = s.groups[b + i];
+      const int units = G.w > 8 ? 1 << (G.w - 8) : 1, np = pieces_of(G), per = units / np;
+      uint32_t out;
+      if (G.w == G.L) out = kLocScalar | (uint32_t)((G.out_off - pb.scalar) / es) << 2;
+      else if (lds[i]) out = kLocLds | (uint32_t)(kProgPoolAt + where[i]) << 2;
+      else out = kLocArena | (uint32_t)((G.out_off - pb.arena) / 256) << 2;
+      for (int q = 0; q < np; q++, item++) {
+        prog.push_back((uint32_t)G.w | (uint32_t)G.L << 5 | (uint32_t)G.n_ops << 9 |
+                         (uint32_t)op_at[i] << 16);
+        prog.push_back(out);
+        prog.push_back((uint32_t)(q * per) | (uint32_t)per << 16);
+        prog.push_back(0);
+      }
+      begin[level[i] + 1] = item;
+    }
+    prog[at + kPgLevelAt] = (uint32_t)(prog.size() - at);
+    prog.insert(prog.end(), begin.begin(), begin.end());
+    while (prog.size() % 4) prog.push_back(0);
+    prog[at + kPgWords] = (uint32_t)(prog.size() - at);
+    b = e;
+  }
+  return true;
+}
+
+// Arithmetic of segment `range` when it runs as a program, else -1.
+int prog_prec(const Schedule &s, int range) {
+  const int4 r = s.ranges[range];
+  return r.z >= 0 ? s.groups[r.x].prec : -1;
+}
+
 // persistent: the schedule runs in a persistent executor (every group inside
-// a workgroup, so no group takes the cell mapping).
+// a workgroup, so no group takes the cell mapping).  size_only: s.total is
+// wanted alone; the programs of single groups are left out and an upper bound
+// of their words is counted.
 int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *force = nullptr,
-                   int singleton_width = 0, int n_sets = 1, bool persistent = false) {
+                   int singleton_width = 0, int n_sets = 1, bool persistent = false,
+                   bool size_only = false) {
   Schedule &s = *S;
   s = Schedule();
   s.serial = ++g_sched_serial;
@@ -796,6 +1030,13 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   s.scalar_sstride = al(n_scalars * es(s.scalar_prec));
   data += n_sets * s.scalar_sstride;
   int scalar_next = 0;
+  struct Job {
+    int g0, g1;
+    ProgBases pb;
+    int range;  // its segment, or -(i + 1) for the i-th single group
+    std::vector<uint32_t> prog;
+  };
+  std::vector<Job> jobs;  // segment programs to compile
   s.ncb.push_back(0);
   for (int i = 0; i < n; i++) {
     const qtn_network *net = nets[i];
@@ -811,13 +1052,19 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       // hybrid executor (executor 5): a cone with a bucket wider than the
       // network's hybrid width runs by per-group launches
       const bool heavy = persistent && net->executor == 5 && pl.max_width > net->hybrid_width;
+      // segments run as programs unless the network asks for one mapping
+      const bool programs = net->variant == 0 || net->variant == 4;
+      const int tab_prec = s.prec == kPrecC64 ? 1 : 0;
+      const ProgBases pb = {table[tab_prec], table_sstride[tab_prec], arena, arena_sstride,
+                            s.scalar_off, s.scalar_sstride, (int)gate_table_elems(net->p)};
       s.cone_heavy.push_back(heavy ? 1 : 0);
       std::vector<Task> tasks;
       int open_begin = -1;
       double seg_bytes = 0, seg_flops = 0;
       auto close_segment = [&](int end) {
         if (open_begin < 0) return;
-        s.ranges.push_back(make_int2(open_begin, end));
+        if (programs) jobs.push_back({open_begin, end, pb, (int)s.ranges.size(), {}});
+        s.ranges.push_back(make_int4(open_begin, end, -1, 0));
         tasks.push_back({QTN_K_BLOCK, (int)s.ranges.size() - 1, 0, 0, seg_bytes, seg_flops});
         open_begin = -1;
         seg_bytes = seg_flops = 0;
@@ -825,7 +1072,8 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       // index slicing: the groups run once per slice, in order, on the one
       // arena; slice k's scalars take slots k * n_scalars onwards
       for (int slice = 0; slice < pl.n_slices; slice++)
-      for (const Group &G : pl.groups) {
+      for (int gi : pl.exec_order) {
+        const Group &G = pl.groups[gi];
         if (G.ops.size() > 255) return set_err(QTN_ERANGE, "bucket with more than 255 tensors");
         if (G.out_tensor < 0 && G.prec != s.scalar_prec)
           return set_err(QTN_EINVAL, "scalar group precision differs from the scalar slots");
@@ -863,13 +1111,18 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
         env.persistent = persistent && !heavy;
         DevGroup dg;
         double gb = 0, gf = 0;
+        s.stab_at.push_back(s.stab.size());
         const int rc = describe_group(G, pl, env, s, &dg, &gb, &gf);
         if (rc) return rc;
         const int gid = (int)s.groups.size();
         s.groups.push_back(dg);
         s.group_cone.push_back(s.n_cones);
-        s.group_index.push_back((int)(&G - pl.groups.data()));
-        if (singleton_width > 0 && G.w <= singleton_width) s.singles.push_back(gid);
+        s.group_index.push_back(gi);
+        if (singleton_width > 0 && G.w <= singleton_width) {
+          s.singles.push_back(gid);
+          if (size_only) s.prog_more += kPageHeader + 12 + 4 * dg.n_ops + 4 * kProgPieces;
+          if (programs && !size_only) jobs.push_back({gid, gid + 1, pb, -(int)s.singles.size(), {}});
+        }
         if (is_small) {
           if (open_begin < 0) open_begin = gid;
           seg_bytes += gb;
@@ -887,8 +1140,22 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
     s.ncb.push_back(s.n_cones);
   }
   s.csb.push_back(scalar_next);
+  std::vector<int> single_prog(s.singles.size(), -1);
+  auto compile = [&](int q) {
+    if (!compile_segment(s, jobs[q].g0, jobs[q].g1, jobs[q].pb, jobs[q].prog)) jobs[q].prog.clear();
+  };
+  // about 20 us a segment: threads pay off from a few dozen
+  if (jobs.size() >= 64)
+    parallel_for((int)jobs.size(), compile);
+  else
+    for (int q = 0; q < (int)jobs.size(); q++) compile(q);
+  for (const Job &j : jobs) {
+    if (j.prog.empty()) continue;
+    (j.range >= 0 ? s.ranges[j.range].z : single_prog[-j.range - 1]) = (int)s.prog.size();
+    s.prog.insert(s.prog.end(), j.prog.begin(), j.prog.end());
+  }
   // the first n_cones ranges are the leading small segments (possibly empty)
-  std::vector<int2> lead(s.n_cones, make_int2(0, 0));
+  std::vector<int4> lead(s.n_cones, make_int4(0, 0, -1, 0));
   for (int c = 0; c < s.n_cones; c++) {
     auto &tk = s.cone_tasks[c];
     if (!tk.empty() && tk[0].kind == QTN_K_BLOCK) {
@@ -902,8 +1169,16 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
     for (auto &t : tk)
       if (t.kind == QTN_K_BLOCK) t.index += s.n_cones;
   s.ranges.insert(s.ranges.begin(), lead.begin(), lead.end());
+  for (int c = 0, none = 1; c < s.n_cones; c++) {
+    if (lead[c].y <= lead[c].x) continue;
+    const int pr = prog_prec(s, c);
+    if (none) s.lead_prec = pr;
+    else if (pr != s.lead_prec) s.lead_prec = -1;
+    none = 0;
+  }
   s.singles_range0 = (int)s.ranges.size();
-  for (int g : s.singles) s.ranges.push_back(make_int2(g, g + 1));
+  for (size_t i = 0; i < s.singles.size(); i++)
+    s.ranges.push_back(make_int4(s.singles[i], s.singles[i] + 1, single_prog[i], 0));
   s.n_nets = n;
   // persistent work items: the j-th task of every cone forms step j (leading
   // segment first); inside a step the costlier cones come first.  The
@@ -941,7 +1216,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       };
       if (lead[cn].y > lead[cn].x) {
         const int tk = new_task();
-        put(make_int4(lead[cn].x, lead[cn].y, 0, 0), tk);
+        put(make_int4(lead[cn].x, lead[cn].y, lead[cn].z, 0), tk);
         s.task_need[tk]++;
         j++;
       }
@@ -949,8 +1224,8 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       for (const Task &t : s.cone_tasks[cn]) {
         const int tk = new_task();
         if (t.kind == QTN_K_BLOCK) {
-          const int2 r = s.ranges[t.index];
-          put(make_int4(r.x, r.y, 0, 0), tk);
+          const int4 r = s.ranges[t.index];
+          put(make_int4(r.x, r.y, r.z, 0), tk);
           s.task_need[tk]++;
         } else {
           const uint32_t nu = t.n_units;
@@ -994,17 +1269,69 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       s.flops[t.kind] += t.flops;
     }
 
+  // device descriptors of the groups that kernels read one by one
+  std::vector<DevGroup> dev_groups;
+  std::vector<DevOp> dev_ops;
+  std::vector<int32_t> dev_stab;
+  std::vector<uint8_t> dev_uperm;
+  size_t n_groups = s.groups.size(), n_ops = s.ops.size(), n_stab = s.stab.size(),
+         n_uperm = s.uperm.size();
+  if (!size_only) {
+    const size_t ng = s.groups.size();
+    s.stab_at.push_back(s.stab.size());
+    s.dev_group.assign(ng, 0);
+    for (int r = 0; r < s.singles_range0; r++)
+      if (s.ranges[r].z >= 0) std::fill(&s.dev_group[s.ranges[r].x], &s.dev_group[0] + s.ranges[r].y, -1);
+    for (size_t g = 0; g < ng; g++) {
+      if (s.dev_group[g] < 0) continue;
+      s.dev_group[g] = (int)dev_groups.size();
+      DevGroup G = s.groups[g];
+      const int32_t shift = (int32_t)s.stab_at[g] - (int32_t)dev_stab.size();
+      const int32_t first = G.op_begin;
+      G.op_begin = (int32_t)dev_ops.size();
+      if (G.variant == kVarMfma) G.gtab -= shift;
+      for (int k = 0; k < G.n_ops; k++) {
+        DevOp o = s.ops[first + k];
+        if (o.stab >= 0) o.stab -= shift;
+        dev_ops.push_back(o);
+      }
+      dev_groups.push_back(G);
+      dev_stab.insert(dev_stab.end(), s.stab.begin() + s.stab_at[g], s.stab.begin() + s.stab_at[g + 1]);
+      dev_uperm.insert(dev_uperm.end(), s.uperm.begin() + 32 * g, s.uperm.begin() + 32 * (g + 1));
+    }
+  }
+  if (!size_only) {
+    n_groups = dev_groups.size();
+    n_ops = dev_ops.size();
+    n_stab = dev_stab.size();
+    n_uperm = dev_uperm.size();
+  }
+  auto on_device = [&](int4 r) {  // a segment or work item with device group numbers
+    const bool chunk = r.y < 0;
+    if (!chunk && (r.z >= 0 || r.y <= r.x)) return r;
+    const int n = r.y - r.x;
+    r.x = s.dev_group[r.x];
+    if (!chunk) r.y = r.x + n;
+    return r;
+  };
+  std::vector<int4> dev_ranges;
+  if (!size_only) {
+    for (const int4 &r : s.ranges) dev_ranges.push_back(on_device(r));
+    for (int4 &it : s.items) it = on_device(it);
+  }
+
   // workspace layout (bytes)
   s.off_res = 0;
   s.off_angles = align_up(8 * (size_t)(2 * s.n_cones + s.n_nets) * s.n_sets, 256);
   s.off_desc = align_up(s.off_angles + 8 * (size_t)s.n_angles * s.n_sets, 256);
   s.off_fills = s.off_desc;
   s.off_groups = align_up(s.off_fills + sizeof(FillDesc) * s.fills.size(), 256);
-  s.off_ops = align_up(s.off_groups + sizeof(DevGroup) * s.groups.size(), 256);
-  s.off_stab = align_up(s.off_ops + sizeof(DevOp) * s.ops.size(), 256);
-  s.off_uperm = align_up(s.off_stab + sizeof(int32_t) * s.stab.size(), 256);
-  s.off_ranges = align_up(s.off_uperm + s.uperm.size(), 256);
-  s.off_csb = align_up(s.off_ranges + sizeof(int2) * s.ranges.size(), 256);
+  s.off_ops = align_up(s.off_groups + sizeof(DevGroup) * n_groups, 256);
+  s.off_stab = align_up(s.off_ops + sizeof(DevOp) * n_ops, 256);
+  s.off_uperm = align_up(s.off_stab + sizeof(int32_t) * n_stab, 256);
+  s.off_ranges = align_up(s.off_uperm + n_uperm, 256);
+  s.off_prog = align_up(s.off_ranges + sizeof(int4) * s.ranges.size(), 256);
+  s.off_csb = align_up(s.off_prog + sizeof(uint32_t) * (s.prog.size() + s.prog_more), 256);
   s.off_ncb = align_up(s.off_csb + sizeof(int) * s.csb.size(), 256);
   s.off_cns = align_up(s.off_ncb + sizeof(int) * s.ncb.size(), 256);
   s.off_items = align_up(s.off_cns + sizeof(int) * s.cns.size(), 256);
@@ -1017,16 +1344,18 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   s.off_ctl = align_up(s.off_queue + sizeof(uint32_t) * s.items.size(), 256);
   s.off_data = align_up(s.off_ctl + sizeof(uint32_t) * s.n_ctl, 256);
   s.total = s.off_data + (size_t)data;
+  if (size_only) return QTN_OK;
   s.desc_blob.assign(s.off_data - s.off_desc, 0);
   auto put = [&](size_t off, const void *src, size_t bytes) {
     if (bytes) std::memcpy(s.desc_blob.data() + (off - s.off_desc), src, bytes);
   };
   put(s.off_fills, s.fills.data(), sizeof(FillDesc) * s.fills.size());
-  put(s.off_groups, s.groups.data(), sizeof(DevGroup) * s.groups.size());
-  put(s.off_ops, s.ops.data(), sizeof(DevOp) * s.ops.size());
-  put(s.off_stab, s.stab.data(), sizeof(int32_t) * s.stab.size());
-  put(s.off_uperm, s.uperm.data(), s.uperm.size());
-  put(s.off_ranges, s.ranges.data(), sizeof(int2) * s.ranges.size());
+  put(s.off_groups, dev_groups.data(), sizeof(DevGroup) * dev_groups.size());
+  put(s.off_ops, dev_ops.data(), sizeof(DevOp) * dev_ops.size());
+  put(s.off_stab, dev_stab.data(), sizeof(int32_t) * dev_stab.size());
+  put(s.off_uperm, dev_uperm.data(), dev_uperm.size());
+  put(s.off_ranges, dev_ranges.data(), sizeof(int4) * dev_ranges.size());
+  put(s.off_prog, s.prog.data(), sizeof(uint32_t) * s.prog.size());
   put(s.off_csb, s.csb.data(), sizeof(int) * s.csb.size());
   put(s.off_ncb, s.ncb.data(), sizeof(int) * s.ncb.size());
   put(s.off_cns, s.cns.data(), sizeof(int) * s.cns.size());
@@ -1160,7 +1489,8 @@ int enqueue(Exec &X, Timer &tm) {
   void *data = ws + s.off_data;
   auto *groups = (const DevGroup *)(ws + s.off_groups);
   auto *ops = (const DevOp *)(ws + s.off_ops);
-  auto *ranges = (const int2 *)(ws + s.off_ranges);
+  auto *ranges = (const int4 *)(ws + s.off_ranges);
+  auto *prog = (const uint32_t *)(ws + s.off_prog);
   auto *stab = (const int32_t *)(ws + s.off_stab);
   auto *uperm = (const uint8_t *)(ws + s.off_uperm);
   int rc;
@@ -1199,7 +1529,7 @@ int enqueue(Exec &X, Timer &tm) {
     if ((rc = tm.begin(QTN_K_PERSISTENT, rt.main, 0, (int)s.groups.size(), b_all, f_all, true)))
       return rc;
     if (X.dataflow)
-      QTN_HIP(launch_dataflow(data, groups, ops, stab, uperm, (const int4 *)(ws + s.off_items),
+      QTN_HIP(launch_dataflow(data, groups, ops, stab, uperm, prog, (const int4 *)(ws + s.off_items),
                               (int)s.items.size(), s.n_init, (const int *)(ws + s.off_item_task),
                               (const int *)(ws + s.off_task_next),
                               (const int *)(ws + s.off_task_first),
@@ -1207,7 +1537,7 @@ int enqueue(Exec &X, Timer &tm) {
                               (uint32_t *)(ws + s.off_ctl), s.n_ctl, nb, X.spin_limit, rt.main,
                               tm.t0(), tm.t1()));
     else
-      QTN_HIP(launch_persistent(s.prec, data, groups, ops, stab, uperm,
+      QTN_HIP(launch_persistent(s.prec, data, groups, ops, stab, uperm, prog,
                                 (const int4 *)(ws + s.off_items), (const int *)(ws + s.off_steps),
                                 s.n_steps, (uint32_t *)(ws + s.off_ctl), s.n_ctl, nb, X.spin_limit,
                                 rt.main, tm.t0(), tm.t1()));
@@ -1236,11 +1566,11 @@ int enqueue(Exec &X, Timer &tm) {
           const int ng = t.kind == QTN_K_BLOCK ? s.ranges[t.index].y - s.ranges[t.index].x : 1;
           if ((rc = tm.begin(t.kind, hs, g0, ng, t.bytes, t.flops, true))) return rc;
           if (t.kind == QTN_K_BLOCK)
-            QTN_HIP(launch_block_groups(s.prec, data, groups, ops, stab, uperm, ranges, t.index, 1,
-                                        NS, hs, tm.t0(), tm.t1()));
+            QTN_HIP(launch_block_groups(prog_prec(s, t.index), data, groups, ops, stab, uperm, prog,
+                                        ranges, t.index, 1, NS, hs, tm.t0(), tm.t1()));
           else
-            QTN_HIP(launch_wide_group(s.groups[t.index], data, groups, ops, stab, uperm, t.index,
-                                      NS, hs, tm.t0(), tm.t1()));
+            QTN_HIP(launch_wide_group(s.groups[t.index], data, groups, ops, stab, uperm,
+                                      s.dev_group[t.index], NS, hs, tm.t0(), tm.t1()));
           if ((rc = tm.end(hs, true))) return rc;
         }
       }
@@ -1256,8 +1586,8 @@ int enqueue(Exec &X, Timer &tm) {
     if ((rc = tm.begin(QTN_K_BLOCK, rt.main, 0, (int)s.groups.size(), NS * s.init_bytes,
                        NS * s.init_flops, true)))
       return rc;
-    QTN_HIP(launch_block_groups(s.prec, data, groups, ops, stab, uperm, ranges, 0, s.n_cones, NS,
-                                rt.main, tm.t0(), tm.t1()));
+    QTN_HIP(launch_block_groups(s.lead_prec, data, groups, ops, stab, uperm, prog, ranges, 0,
+                                s.n_cones, NS, rt.main, tm.t0(), tm.t1()));
     if ((rc = tm.end(rt.main, true))) return rc;
   }
   // timed runs serialize on one stream, so each event pair brackets one kernel
@@ -1286,7 +1616,8 @@ int enqueue(Exec &X, Timer &tm) {
         if ((rc = tm.begin(QTN_K_BLOCK, hs, s.ranges[c].x, s.ranges[c].y - s.ranges[c].x, 0, 0,
                            true)))
           return rc;
-        QTN_HIP(launch_block_groups(s.prec, data, groups, ops, stab, uperm, ranges, c, 1, NS, hs,
+        QTN_HIP(launch_block_groups(prog_prec(s, c), data, groups, ops, stab, uperm, prog, ranges, c,
+                                    1, NS, hs,
                                     tm.t0(), tm.t1()));
         if ((rc = tm.end(hs, true))) return rc;
       }
@@ -1295,11 +1626,11 @@ int enqueue(Exec &X, Timer &tm) {
         const int ng = t.kind == QTN_K_BLOCK ? s.ranges[t.index].y - s.ranges[t.index].x : 1;
         if ((rc = tm.begin(t.kind, hs, g0, ng, NS * t.bytes, NS * t.flops, true))) return rc;
         if (t.kind == QTN_K_BLOCK)
-          QTN_HIP(launch_block_groups(s.prec, data, groups, ops, stab, uperm, ranges, t.index, 1, NS,
-                                      hs, tm.t0(), tm.t1()));
+          QTN_HIP(launch_block_groups(prog_prec(s, t.index), data, groups, ops, stab, uperm, prog,
+                                      ranges, t.index, 1, NS, hs, tm.t0(), tm.t1()));
         else
-          QTN_HIP(launch_wide_group(s.groups[t.index], data, groups, ops, stab, uperm, t.index, NS,
-                                    hs, tm.t0(), tm.t1()));
+          QTN_HIP(launch_wide_group(s.groups[t.index], data, groups, ops, stab, uperm,
+                                    s.dev_group[t.index], NS, hs, tm.t0(), tm.t1()));
         if ((rc = tm.end(hs, true))) return rc;
       }
     }
@@ -1596,7 +1927,7 @@ int qtn_plan(qtn_network *net, const int32_t *const *orders, int32_t precision,
       size_t mx = ex->sched.total;
       for (const Force &f : tune_candidates()) {
         Schedule tmp;
-        if (build_schedule(one, 1, &tmp, &f, kTuneSingleWidth) == QTN_OK)
+        if (build_schedule(one, 1, &tmp, &f, kTuneSingleWidth, 1, false, true) == QTN_OK)
           mx = std::max(mx, tmp.total);
       }
       net->tune_workspace = mx;
@@ -1924,7 +2255,7 @@ static int tune_workspace_bytes(qtn_network *net, int n_sets, size_t *bytes) {
   size_t mx = 0;
   for (const Force &f : tune_candidates()) {
     Schedule tmp;
-    const int rc = build_schedule(one, 1, &tmp, &f, kTuneSingleWidth, n_sets);
+    const int rc = build_schedule(one, 1, &tmp, &f, kTuneSingleWidth, n_sets, false, true);
     if (rc) return rc;
     mx = std::max(mx, tmp.total);
   }
@@ -2004,9 +2335,11 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
             return rc;
           }
           hipError_t he = launch_block_groups(
-              s.prec, ws + s.off_data, (const DevGroup *)(ws + s.off_groups),
+              prog_prec(s, s.singles_range0 + (int)i), ws + s.off_data,
+              (const DevGroup *)(ws + s.off_groups),
               (const DevOp *)(ws + s.off_ops), (const int32_t *)(ws + s.off_stab),
-              (const uint8_t *)(ws + s.off_uperm), (const int2 *)(ws + s.off_ranges),
+              (const uint8_t *)(ws + s.off_uperm), (const uint32_t *)(ws + s.off_prog),
+              (const int4 *)(ws + s.off_ranges),
               s.singles_range0 + (int)i, 1, n_sets, ex.rt.main, tb.t0(), tb.t1());
           if (he == hipSuccess) rc = tb.end(ex.rt.main, true);
           if (he != hipSuccess || rc) {

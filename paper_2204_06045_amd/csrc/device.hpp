@@ -93,6 +93,55 @@ constexpr int kCellMaxLdsWords = 16384;  // 64 KiB per workgroup
 // offsets, then 2^L offsets of the summed indices.
 constexpr int kMmTM = 64, kMmTN = 64, kMmKC = 16, kMmMaxOps = 64;
 
+// Segment programs: a run of small groups of one light cone, compiled by the
+// planner for one workgroup (kernels.hip, run_program).  A program is a list
+// of pages, each at most kPageWords 32-bit words:
+//   header (kPageHeader words), operand records (4 words each), work items
+//   (4 words each), first item of every level (n_levels + 1 words).
+// A page's levels run between workgroup barriers; the items of one level are
+// independent and dealt to the waves.  Intermediates made and read inside a
+// page live in LDS where they fit, beside a copy of the gate table.  Sizes: a
+// page of 8 KiB holds about 60 groups, a whole light cone of a depth-3 cubic
+// graph; the total keeps five workgroups on a compute unit.
+constexpr int kPageWords = 2048;      // 8 KiB
+constexpr int kPageHeader = 24;
+constexpr int kProgTable = 272;       // gate-table elements held in LDS (p <= 8)
+constexpr int kProgPoolBytes = 17920; // LDS for intermediates
+constexpr int kProgMaxWidth = 16;     // union bits of a group (16-bit index compress)
+constexpr int kProgMaxOps = 64;       // operands of a group (one per lane)
+constexpr int kProgPieces = 16;       // most items a group is cut into
+// LDS: page, gate table (complex128 elements), intermediates
+constexpr int kProgTableAt = kPageWords * 4;
+constexpr int kProgPoolAt = kProgTableAt + kProgTable * 16;
+constexpr int kProgLdsBytes = kProgPoolAt + kProgPoolBytes;
+// header words
+enum PageWord : int {
+  kPgWords = 0,    // words of this page
+  kPgNext = 1,     // words from this page's start to the next page (0: last)
+  kPgLevels = 2,
+  kPgItems = 3,    // word offset of the items
+  kPgLevelAt = 4,  // word offset of the level table
+  kPgPrec = 5,     // arithmetic: 0 complex128, 1 complex64
+  kPgTable = 6,    // gate-table elements
+  kPgTableOff = 8, kPgTableStride = 10,    // 64-bit byte offsets from the data base
+  kPgArenaOff = 12, kPgArenaStride = 14,   // and bytes between angle sets
+  kPgScalarOff = 16, kPgScalarStride = 18,
+};
+// operand record: location, then the index compress of its mask
+//   word 0: kind | where << 2
+//   words 1, 2: the four move masks of the compress (16 bits each)
+//   word 3: mask
+enum ProgLoc : uint32_t {
+  kLocLds = 0,     // where: LDS byte offset
+  kLocArena = 1,   // where: arena offset / 256, stored in the page's precision
+  kLocArenaX = 2,  // the same, stored in the other precision
+  kLocScalar = 3,  // outputs only; where: scalar slot
+};
+// item: w | L << 5 | n_ops << 9 | first operand record << 16; output
+// location (kind | where << 2); first unit | units << 16; unused.  A unit is
+// 2^8 points of the union index: bits 0..5 on lanes, bits 6 and 7 in
+// registers.
+
 // Generic mapping: 2 register bits and 6 lane bits per wave unit.
 constexpr int kGenRegBits = 2;
 // Streaming mapping: at most this many operands per group (LDS lane tables).

@@ -920,6 +920,252 @@ __device__ void mm_tile(const GI &G, const DevOp *__restrict__ gops, const int32
   }
 }
 
+// -------------------------------------------------------- segment programs
+
+// v + (v of the lane whose index differs in bit t), for a v that is already
+// equal in all lanes differing only in bits below t: the mirrors then stand
+// in for the exchanges over 4 and 8.
+template <int T> __device__ __forceinline__ uint32_t other_lane(uint32_t v) {
+  if (T == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+  if (T == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+  if (T == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);
+}
+template <int T> __device__ __forceinline__ float sum_lane(float v) {
+  const uint32_t a = __float_as_uint(v);
+  if (T < 4) return v + __uint_as_float(other_lane<T>(a));
+  if (T == 4) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int T> __device__ __forceinline__ double sum_lane(double v) {
+  const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+  if (T < 4) return v + __hiloint2double((int)other_lane<T>(hi), (int)other_lane<T>(lo));
+  if (T == 4) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+template <int T, class C> __device__ __forceinline__ C csum_lane(C v) {
+  v.x = sum_lane<T>(v.x);
+  v.y = sum_lane<T>(v.y);
+  return v;
+}
+// Sum over the lowest n (<= 6) lane bits.
+template <class C> __device__ __forceinline__ C lane_sum(C v, int n) {
+  if (n > 0) v = csum_lane<0>(v);
+  if (n > 1) v = csum_lane<1>(v);
+  if (n > 2) v = csum_lane<2>(v);
+  if (n > 3) v = csum_lane<3>(v);
+  if (n > 4) v = csum_lane<4>(v);
+  if (n > 5) v = csum_lane<5>(v);
+  return v;
+}
+
+// A page's bases for one angle set (wave-uniform).
+struct ProgBase {
+  char *arena, *scalar;
+  char *lds;  // the workgroup's LDS
+};
+
+// The values of one operand (record words r0..r3, wave-uniform) at the
+// points I0 + 64 c, c < NC.
+template <class T, int NC>
+__device__ __forceinline__ void prog_load(const ProgBase &B, uint32_t r0, uint32_t r1, uint32_t r2,
+                                          uint32_t r3, uint32_t I0, T *v) {
+  // compress of the mask's bits, four moves
+  uint32_t x = I0 & r3, t;
+  t = x & (r1 & 0xFFFFu);
+  x = (x ^ t) | (t >> 1);
+  t = x & (r1 >> 16);
+  x = (x ^ t) | (t >> 2);
+  t = x & (r2 & 0xFFFFu);
+  x = (x ^ t) | (t >> 4);
+  t = x & (r2 >> 16);
+  x = (x ^ t) | (t >> 8);
+  // element steps of bits 6 and 7
+  const uint32_t lane_part = (uint32_t)__builtin_popcount(r3 & 63u), b6 = (r3 >> 6) & 1u;
+  const uint32_t s6 = b6 << lane_part, s7 = ((r3 >> 7) & 1u) << (lane_part + b6);
+  const uint32_t where = r0 >> 2;
+  auto spread = [&](auto load) {
+    v[0] = load(0u);
+    if (NC >= 2) v[1] = s6 ? load(s6) : v[0];
+    if (NC >= 4) {
+      if (s7) {
+        v[2] = load(s7);
+        v[3] = s6 ? load(s6 + s7) : v[2];
+      } else {
+        v[2] = v[0];
+        v[3] = v[1];
+      }
+    }
+  };
+  if ((r0 & 3u) == kLocLds) {
+    const char *p = B.lds + where + x * (uint32_t)sizeof(T);
+    spread([&](uint32_t d) { return *(const T *)(p + d * (uint32_t)sizeof(T)); });
+  } else {
+    const char *p = B.arena + (uint64_t)where * 256u;
+    if ((r0 & 3u) == kLocArena) {
+      spread([&](uint32_t d) { return gload<T>(p, (x + d) * (uint32_t)sizeof(T)); });
+    } else if (sizeof(T) == 16) {
+      spread([&](uint32_t d) {
+        const float2 f = gload<float2>(p, (x + d) * 8u);
+        return make_c<T>(f.x, f.y);
+      });
+    } else {
+      spread([&](uint32_t d) {
+        const double2 f = gload<double2>(p, (x + d) * 16u);
+        return make_c<T>(f.x, f.y);
+      });
+    }
+  }
+}
+
+// Units [u0, u0 + nu) of one group: every point multiplies all operands (a
+// level-l operand does not depend on the l bits summed before it, so the sum
+// is the same), then the summed bits are added over registers and lanes.
+template <class T, int NC>
+__device__ __forceinline__ void prog_units(const ProgBase &B, const uint4 *ops, uint32_t head,
+                                           uint32_t out, uint32_t u0, uint32_t nu, uint32_t set_lane) {
+  const int w = head & 31, L = (head >> 5) & 15, n_ops = (head >> 9) & 127;
+  const uint32_t lane = set_lane;
+  const uint4 rec = ops[min((int)lane, n_ops - 1)];
+  for (uint32_t u = u0; u < u0 + nu; u++) {
+    const uint32_t I0 = lane | (u << 8);
+    T acc[NC], v[NC];
+    // two operands at a time: the second one's loads are under way while the
+    // first is multiplied in
+    for (int k = 0; k < n_ops; k += 2) {
+      T v2[NC];
+      const int k2 = min(k + 1, n_ops - 1);
+      prog_load<T, NC>(B, __builtin_amdgcn_readlane(rec.x, k), __builtin_amdgcn_readlane(rec.y, k),
+                       __builtin_amdgcn_readlane(rec.z, k), __builtin_amdgcn_readlane(rec.w, k), I0,
+                       v);
+      if (k + 1 < n_ops)
+        prog_load<T, NC>(B, __builtin_amdgcn_readlane(rec.x, k2),
+                         __builtin_amdgcn_readlane(rec.y, k2), __builtin_amdgcn_readlane(rec.z, k2),
+                         __builtin_amdgcn_readlane(rec.w, k2), I0, v2);
+#pragma unroll
+      for (int c = 0; c < NC; c++) acc[c] = k == 0 ? v[c] : cmul(acc[c], v[c]);
+      if (k + 1 < n_ops) {
+#pragma unroll
+        for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], v2[c]);
+      }
+    }
+    int nc = NC;  // cells left: bit 6, then bit 7 summed
+    if (NC >= 2 && L >= 7) {
+#pragma unroll
+      for (int c = 0; c < NC / 2; c++) acc[c] = cadd(acc[2 * c], acc[2 * c + 1]);
+      nc = NC / 2;
+      if (NC >= 4 && L >= 8) {
+        acc[0] = cadd(acc[0], acc[NC >= 4 ? 1 : 0]);
+        nc = 1;
+      }
+    }
+    const int nl = min(L, 6);
+#pragma unroll
+    for (int c = 0; c < NC; c++)
+      if (c < nc) acc[c] = lane_sum(acc[c], nl);
+    if ((lane & ((1u << nl) - 1u)) == 0u && (w >= 6 || lane < (1u << w))) {
+      char *p = (out & 3u) == kLocLds
+                    ? B.lds + (out >> 2)
+                    : (out & 3u) == kLocScalar ? B.scalar + (uint64_t)(out >> 2) * sizeof(T)
+                                               : B.arena + (uint64_t)(out >> 2) * 256u;
+      // cell c left stands for union bits (c << (6 or 7)); with one left, none
+      const int cs = L >= 7 ? 7 : 6;
+#pragma unroll
+      for (int c = 0; c < NC; c++)
+        if (c < nc) *(T *)(p + (uint64_t)((I0 | ((uint32_t)c << cs)) >> L) * sizeof(T)) = acc[c];
+    }
+  }
+}
+
+// One program for angle set `set`, with the whole workgroup (any number of
+// waves).  Small groups are bound by latency: a few hundred points each, in a
+// chain per light cone.  Read from memory one by one, a group costs a chain of
+// dependent descriptor and operand loads (up to 4 us).  So a page of
+// descriptors comes in one copy, intermediates and gates stay in LDS, an
+// operand's record is read once per group (lane k holds operand k's) and
+// broadcast through scalar registers, and independent groups of a level run
+// on different waves.  Measured against the group-by-group form (complex128):
+// the launch of a depth-1 network of 10 vertices 29.9 -> 8.3 us; one of a
+// depth-3 network of 20 vertices 25.3 -> 14.6 us with more groups in each
+// (26 -> 20 launches an evaluation).
+template <class T>
+__device__ __forceinline__ void run_program_t(const uint32_t *__restrict__ prog, char *__restrict__ data, char *lds,
+                              uint32_t set) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t *pg = (uint32_t *)lds;
+  auto u64 = [&](int i) { return ((uint64_t)prog[i + 1] << 32) | prog[i]; };
+  {
+    // the gate table, once for all pages
+    const T *src = (const T *)(data + u64(kPgTableOff) + (uint64_t)set * u64(kPgTableStride));
+    T *dst = (T *)(lds + kProgTableAt);
+    const int n = (int)prog[kPgTable];
+    for (int e = threadIdx.x; e < n; e += blockDim.x) dst[e] = src[e];
+  }
+  for (;;) {
+    const uint32_t words = prog[kPgWords], next = prog[kPgNext];
+    const int n_levels = (int)prog[kPgLevels];
+    ProgBase B;
+    B.arena = data + u64(kPgArenaOff) + (uint64_t)set * u64(kPgArenaStride);
+    B.scalar = data + u64(kPgScalarOff) + (uint64_t)set * u64(kPgScalarStride);
+    B.lds = lds;
+    for (uint32_t e = threadIdx.x; e < words / 4; e += blockDim.x)
+      ((uint4 *)pg)[e] = ((const uint4 *)prog)[e];
+    __syncthreads();
+    const uint4 *ops = (const uint4 *)(pg + kPageHeader);
+    const uint4 *items = (const uint4 *)(pg + pg[kPgItems]);
+    const uint32_t *level = pg + pg[kPgLevelAt];
+    for (int l = 0; l < n_levels; l++) {
+      const int i1 = __builtin_amdgcn_readfirstlane(level[l + 1]);
+      for (int i = __builtin_amdgcn_readfirstlane(level[l]) + wave; i < i1; i += nw) {
+        const uint4 it = items[i];
+        const uint32_t head = __builtin_amdgcn_readfirstlane(it.x);
+        const uint32_t out = __builtin_amdgcn_readfirstlane(it.y);
+        const uint32_t un = __builtin_amdgcn_readfirstlane(it.z);
+        const uint4 *gops = ops + (head >> 16);
+        const uint32_t w = head & 31u;
+        if (w <= 6)
+          prog_units<T, 1>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
+        else if (w == 7)
+          prog_units<T, 2>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
+        else
+          prog_units<T, 4>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
+      }
+      __syncthreads();
+    }
+    if (next == 0u) return;
+    prog += next;
+  }
+}
+__device__ __forceinline__ void run_program(const uint32_t *__restrict__ prog,
+                                            char *__restrict__ data, char *lds, uint32_t set) {
+  if (prog[kPgPrec] == 0)
+    run_program_t<double2>(prog, data, lds, set);
+  else
+    run_program_t<float2>(prog, data, lds, set);
+}
+
+// LDS of the workgroup and persistent kernels: a program's, or the lane
+// tables of the streaming mapping and the matrix tiles.
+constexpr int kBlockLds =
+    kProgLdsBytes > kStreamMaxOps * 64 * 4 ? kProgLdsBytes : kStreamMaxOps * 64 * 4;
+// LDS is handed out in pieces of 1,280 bytes, which the runtime's occupancy
+// query does not count: a persistent grid sized by it would not be resident
+// as a whole (its grid barrier then runs into its bound).
+constexpr int kLdsPiece = 1280;
+static_assert(5 * ((kBlockLds + 64 + kLdsPiece - 1) / kLdsPiece * kLdsPiece) <= 160 * 1024,
+              "five workgroups per compute unit");
+
 // One group's wave units [u0, u1) of angle set `set` over the block's waves,
 // in the group's own precision.
 __device__ __forceinline__ void run_group(const GI &G, int g, const DevOp *__restrict__ ops,
@@ -972,16 +1218,34 @@ __global__ __launch_bounds__(kBlock, 5) void k_block_groups(char *__restrict__ d
                                                          const DevOp *__restrict__ ops,
                                                          const int32_t *__restrict__ stab,
                                                          const uint8_t *__restrict__ uperm,
-                                                         const int2 *__restrict__ ranges,
+                                                         const uint32_t *__restrict__ prog,
+                                                         const int4 *__restrict__ ranges,
                                                          int range_base, int n_ranges) {
-  __shared__ __align__(16) uint32_t s_lane[kStreamMaxOps * 64];
+  __shared__ __align__(16) uint32_t s_lane[kBlockLds / 4];
   // block b runs range b % n_ranges for angle set b / n_ranges
   const uint32_t set = blockIdx.x / (uint32_t)n_ranges;
-  const int2 rg = ranges[range_base + (int)(blockIdx.x % (uint32_t)n_ranges)];
+  const int4 rg = ranges[range_base + (int)(blockIdx.x % (uint32_t)n_ranges)];
+  if (rg.z >= 0) {
+    run_program(prog + rg.z, data, (char *)s_lane, set);
+    return;
+  }
   for (int g = rg.x; g < rg.y; g++) {
     const GI G = load_group(groups + g);
     run_group(G, g, ops, stab, uperm, data, s_lane, 0u, G.n_units, set);
   }
+}
+
+// Segments that are all programs of one precision: without the other
+// mappings' code the kernel needs few registers and nothing spills.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_programs(char *__restrict__ data,
+                                                     const uint32_t *__restrict__ prog,
+                                                     const int4 *__restrict__ ranges,
+                                                     int range_base, int n_ranges) {
+  __shared__ __align__(16) char lds[kProgLdsBytes];
+  const uint32_t set = blockIdx.x / (uint32_t)n_ranges;
+  const int4 rg = ranges[range_base + (int)(blockIdx.x % (uint32_t)n_ranges)];
+  if (rg.z >= 0) run_program_t<T>(prog + rg.z, data, lds, set);
 }
 
 // Units of a wide launch.  Blocks are dealt round-robin to the 8 XCDs; each
@@ -1097,14 +1361,20 @@ __global__ __launch_bounds__(kBlock, (mm_waves<T, NCB>())) void k_wide_mfma(char
 
 // ----------------------------------------------------- persistent executor
 
-// Runs one work item with the whole block: a segment of small groups
-// [it.x, it.y) in order, or units [it.z, it.w) of wide group it.x (it.y < 0).
+// Runs one work item with the whole block: a segment of small groups (its
+// program at it.z, or groups [it.x, it.y) in order when it.z < 0), or units
+// [it.z, it.w) of wide group it.x (it.y < 0).
 __device__ __forceinline__ void run_item(int4 it, char *__restrict__ data,
                                          const DevGroup *__restrict__ groups,
                                          const DevOp *__restrict__ ops,
                                          const int32_t *__restrict__ stab,
-                                         const uint8_t *__restrict__ uperm, uint32_t *s_lane) {
+                                         const uint8_t *__restrict__ uperm,
+                                         const uint32_t *__restrict__ prog, uint32_t *s_lane) {
   const bool chunk = it.y < 0;
+  if (!chunk && it.z >= 0) {
+    run_program(prog + it.z, data, (char *)s_lane, 0u);
+    return;
+  }
   const int g_end = chunk ? it.x + 1 : it.y;
   for (int g = it.x; g < g_end; g++) {
     const GI G = load_group(groups + g);
@@ -1163,11 +1433,12 @@ __global__ __launch_bounds__(kBlock, 5) void k_persistent(char *__restrict__ dat
                                                        const DevOp *__restrict__ ops,
                                                        const int32_t *__restrict__ stab,
                                                        const uint8_t *__restrict__ uperm,
+                                                       const uint32_t *__restrict__ prog,
                                                        const int4 *__restrict__ items,
                                                        const int *__restrict__ step_begin,
                                                        int n_steps, uint32_t *ctl,
                                                        uint32_t spin_limit) {
-  __shared__ __align__(16) uint32_t s_lane[kStreamMaxOps * 64];
+  __shared__ __align__(16) uint32_t s_lane[kBlockLds / 4];
   __shared__ int s_item;
   uint32_t *step_ctr = ctl + 4;
   for (int st = 0; st < n_steps; st++) {
@@ -1180,7 +1451,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_persistent(char *__restrict__ dat
       const int i = s_item;
       __syncthreads();
       if (i >= e) break;
-      run_item(items[i], data, groups, ops, stab, uperm, s_lane);
+      run_item(items[i], data, groups, ops, stab, uperm, prog, s_lane);
     }
     if (st + 1 < n_steps && !grid_barrier(ctl, spin_limit)) return;
   }
@@ -1211,6 +1482,7 @@ __global__ __launch_bounds__(kBlock) void k_dataflow(char *__restrict__ data,
                                                      const DevOp *__restrict__ ops,
                                                      const int32_t *__restrict__ stab,
                                                      const uint8_t *__restrict__ uperm,
+                                                     const uint32_t *__restrict__ prog,
                                                      const int4 *__restrict__ items, int n_items,
                                                      const int *__restrict__ item_task,
                                                      const int *__restrict__ task_next,
@@ -1218,7 +1490,7 @@ __global__ __launch_bounds__(kBlock) void k_dataflow(char *__restrict__ data,
                                                      const int *__restrict__ task_need,
                                                      uint32_t *queue, uint32_t *ctl,
                                                      uint32_t spin_limit) {
-  __shared__ __align__(16) uint32_t s_lane[kStreamMaxOps * 64];
+  __shared__ __align__(16) uint32_t s_lane[kBlockLds / 4];
   __shared__ int s_item, s_ok;
   uint32_t *claim = ctl, *fill = ctl + 1, *err = ctl + 2, *done = ctl + 4;
   const int lane = threadIdx.x & 63;
@@ -1282,7 +1554,7 @@ __global__ __launch_bounds__(kBlock) void k_dataflow(char *__restrict__ data,
     const int i = s_item, ok = s_ok;
     __syncthreads();
     if (i >= n_items || i < 0 || !ok) break;
-    run_item(items[i], data, groups, ops, stab, uperm, s_lane);  // ends with a barrier
+    run_item(items[i], data, groups, ops, stab, uperm, prog, s_lane);  // ends with a barrier
     prev = i;
   }
 }
@@ -1465,13 +1737,19 @@ hipError_t launch_fill(int prec, void *data, const double *angles, const FillDes
 }
 
 hipError_t launch_block_groups(int prec, void *data, const DevGroup *groups, const DevOp *ops,
-                               const int32_t *stab, const uint8_t *uperm, const int2 *ranges,
-                               int range_base, int n_blocks, int n_sets, hipStream_t s,
+                               const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                               const int4 *ranges, int range_base, int n_blocks, int n_sets, hipStream_t s,
                                hipEvent_t t0, hipEvent_t t1) {
-  (void)prec;
   if (n_blocks <= 0 || n_sets <= 0) return no_launch(t0, t1, s);
-  QTN_LAUNCH(t0, t1, k_block_groups, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
-             groups, ops, stab, uperm, ranges, range_base, n_blocks);
+  if (prec == kPrecC128)
+    QTN_LAUNCH(t0, t1, k_programs<double2>, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
+               prog, ranges, range_base, n_blocks);
+  else if (prec == kPrecC64)
+    QTN_LAUNCH(t0, t1, k_programs<float2>, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
+               prog, ranges, range_base, n_blocks);
+  else
+    QTN_LAUNCH(t0, t1, k_block_groups, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
+             groups, ops, stab, uperm, prog, ranges, range_base, n_blocks);
   return hipGetLastError();
 }
 
@@ -1559,8 +1837,8 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
 }
 
 hipError_t launch_persistent(int prec, void *data, const DevGroup *groups, const DevOp *ops,
-                             const int32_t *stab, const uint8_t *uperm, const int4 *items,
-                             const int *step_begin, int n_steps, uint32_t *ctl, int n_ctl,
+                             const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                             const int4 *items, const int *step_begin, int n_steps, uint32_t *ctl, int n_ctl,
                              int n_blocks, uint32_t spin_limit, hipStream_t s, hipEvent_t t0,
                              hipEvent_t t1) {
   (void)prec;
@@ -1569,13 +1847,13 @@ hipError_t launch_persistent(int prec, void *data, const DevGroup *groups, const
   if (e != hipSuccess) return e;
   if (n_steps <= 0) return no_launch(t0, t1, s);
   QTN_LAUNCH(t0, t1, k_persistent, dim3(n_blocks), dim3(kBlock), s, (char *)data, groups, ops,
-             stab, uperm, items, step_begin, n_steps, ctl, spin_limit);
+             stab, uperm, prog, items, step_begin, n_steps, ctl, spin_limit);
   return hipGetLastError();
 }
 
 hipError_t launch_dataflow(void *data, const DevGroup *groups, const DevOp *ops,
-                           const int32_t *stab, const uint8_t *uperm, const int4 *items,
-                           int n_items, int n_init, const int *item_task, const int *task_next,
+                           const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                           const int4 *items, int n_items, int n_init, const int *item_task, const int *task_next,
                            const int *task_first, const int *task_need, uint32_t *queue,
                            uint32_t *ctl, int n_ctl, int n_blocks, uint32_t spin_limit,
                            hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
@@ -1586,7 +1864,7 @@ hipError_t launch_dataflow(void *data, const DevGroup *groups, const DevOp *ops,
   if (e != hipSuccess) return e;
   if (n_items <= 0) return no_launch(t0, t1, s);
   QTN_LAUNCH(t0, t1, k_dataflow, dim3(n_blocks), dim3(kBlock), s, (char *)data, groups, ops, stab,
-             uperm, items, n_items, item_task, task_next, task_first, task_need, queue, ctl,
+             uperm, prog, items, n_items, item_task, task_next, task_first, task_need, queue, ctl,
              spin_limit);
   return hipGetLastError();
 }

@@ -29,14 +29,16 @@ hipError_t launch_fill(int prec, void *data, const double *angles,
                        const FillDesc *fills, int n_nets, int n_angles, int n_sets,
                        hipStream_t s);
 
-// Groups [ranges[b].x, ranges[b].y) run in order inside one block, for
+// Groups [ranges[b].x, ranges[b].y) run inside one block, by the segment
+// program at word ranges[b].z of prog or, when that is negative, in order, for
 // b in [range_base, range_base + n_blocks), once per angle set (n_blocks *
-// n_sets blocks).  uperm holds 32 bytes per group: the union bit of each
+// n_sets blocks).  prec: the arithmetic when every range (an empty one apart)
+// is a program of that precision, else -1.  uperm holds 32 bytes per group: the union bit of each
 // wave-unit bit.
 hipError_t launch_block_groups(int prec, void *data, const DevGroup *groups,
                                const DevOp *ops, const int32_t *stab,
-                               const uint8_t *uperm, const int2 *ranges,
-                               int range_base, int n_blocks, int n_sets, hipStream_t s,
+                               const uint8_t *uperm, const uint32_t *prog,
+                               const int4 *ranges, int range_base, int n_blocks, int n_sets, hipStream_t s,
                                hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 
 // One group over the whole grid, with the kernel of its mapping variant and
@@ -48,13 +50,15 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
 
 // Clears the control words, then runs every light cone's task list in
 // lockstep inside one persistent launch of n_blocks resident blocks.
-// items: (group_begin, group_end, 0, 0) for a segment of small groups or
+// items: (group_begin, group_end, program word or -1, 0) for a segment of
+// small groups or
 // (group, -1, unit_begin, unit_end) for a chunk of a wide group; step s owns
 // items [step_begin[s], step_begin[s+1]).  ctl needs 4 + n_steps words;
 // ctl[2] != 0 after the launch means a barrier wait exceeded spin_limit.
 hipError_t launch_persistent(int prec, void *data, const DevGroup *groups,
                              const DevOp *ops, const int32_t *stab,
-                             const uint8_t *uperm, const int4 *items, const int *step_begin, int n_steps,
+                             const uint8_t *uperm, const uint32_t *prog, const int4 *items,
+                             const int *step_begin, int n_steps,
                              uint32_t *ctl, int n_ctl, int n_blocks,
                              uint32_t spin_limit, hipStream_t s, hipEvent_t t0 = nullptr,
                              hipEvent_t t1 = nullptr);
@@ -67,8 +71,8 @@ hipError_t launch_persistent(int prec, void *data, const DevGroup *groups,
 // holds n_items words; ctl needs 4 + n_tasks words (ctl[2] != 0 after the
 // launch means a wait exceeded spin_limit).
 hipError_t launch_dataflow(void *data, const DevGroup *groups, const DevOp *ops,
-                           const int32_t *stab, const uint8_t *uperm, const int4 *items,
-                           int n_items, int n_init, const int *item_task, const int *task_next,
+                           const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                           const int4 *items, int n_items, int n_init, const int *item_task, const int *task_next,
                            const int *task_first, const int *task_need, uint32_t *queue,
                            uint32_t *ctl, int n_ctl, int n_blocks, uint32_t spin_limit,
                            hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);

@@ -683,10 +683,57 @@ std::string plan_cone(const LightCone &lc, const std::vector<int> &order,
     }
   }
 
-  // memory plan (bytes, 256-aligned): outputs are placed before the group's
-  // inputs are released
+  // execution order.  A run of small groups is one workgroup's work between
+  // two launches, so few, long runs are wanted: what needs no wide group leads
+  // (one launch for every light cone), and the rest waits until a wide group
+  // needs some of it; then all that can run does.  The wide groups keep their order, and with it the arena
+  // of the large intermediates: a small group's operands are small.
+  {
+    const int ng = (int)P.groups.size();
+    std::vector<char> after_wide(ng, 0), done(ng, 0);
+    for (int g = 0; g < ng; g++) {
+      for (const Operand &o : P.groups[g].ops) {
+        const Tensor &t = P.tensors[o.tensor];
+        if (t.gate < 0 && (!P.groups[t.producer].small || after_wide[t.producer])) after_wide[g] = 1;
+      }
+    }
+    for (int g = 0; g < ng; g++)
+      if (P.groups[g].small && !after_wide[g]) {
+        P.exec_order.push_back(g);
+        done[g] = 1;
+      }
+    // small groups not done yet whose producers are
+    auto run_ready = [&]() {
+      for (int q = 0; q < ng; q++) {
+        if (done[q] || !P.groups[q].small) continue;
+        bool ready = true;
+        for (const Operand &o : P.groups[q].ops) {
+          const Tensor &t = P.tensors[o.tensor];
+          ready &= t.gate >= 0 || done[t.producer];
+        }
+        if (!ready) continue;
+        P.exec_order.push_back(q);
+        done[q] = 1;
+      }
+    };
+    for (int g = 0; g < ng; g++) {
+      if (P.groups[g].small) continue;
+      bool ready = true;
+      for (const Operand &o : P.groups[g].ops) {
+        const Tensor &t = P.tensors[o.tensor];
+        ready &= t.gate >= 0 || done[t.producer];
+      }
+      if (!ready) run_ready();
+      P.exec_order.push_back(g);
+      done[g] = 1;
+    }
+    run_ready();
+  }
+
+  // memory plan (bytes, 256-aligned) along the execution order: outputs are
+  // placed before the group's inputs are released
   Arena A;
-  for (size_t g = 0; g < P.groups.size(); g++) {
+  for (int g : P.exec_order) {
     Group &G = P.groups[g];
     if (G.out_tensor >= 0) {
       int64_t sz = ((int64_t)1 << (G.w - G.L)) * (int64_t)es(G.prec);

@@ -143,7 +143,11 @@ struct ConePlan {
   int max_width = 0;
   int n_buckets = 0;
   std::vector<Tensor> tensors;
-  std::vector<Group> groups;       // in execution order
+  std::vector<Group> groups;       // by last elimination position
+  // execution order (indices of groups): the small groups that need no wide
+  // group first, then the wide groups in elimination order, with all small
+  // groups that can run just before a wide group that needs one of them
+  std::vector<int> exec_order;
   int n_scalars = 0;
   int64_t arena_bytes = 0;         // peak live bytes of intermediates
   double bytes = 0, flops = 0, paper_flops = 0;  // per evaluation

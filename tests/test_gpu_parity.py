@@ -59,6 +59,26 @@ def test_petersen_p1_optimum(qtn, gpu):
     assert abs(en / 15 - (0.5 + 1 / (3 * math.sqrt(3)))) < 1e-12
 
 
+@pytest.mark.parametrize("n,d,p,cfg", [
+    (10, 3, 1, {}),                                  # unions of 1..4 bits
+    (16, 3, 3, dict(small_width=16)),                # up to 16 bits, several items a group
+    (14, 4, 2, dict(small_width=16, max_levels=1)),  # one summed bit, many pages
+    (14, 3, 3, dict(small_width=16, slice_width=4)), # slices on one arena
+    (12, 3, 8, dict(slice_width=16)),                # the longest gate table held in LDS
+    (10, 3, 9, dict()),                              # a longer one: group by group
+    (12, 3, 3, dict(small_width=7)),                 # 7 bits: two register cells
+])
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_segment_programs(qtn, orc, gpu, n, d, p, cfg, prec):
+    inst = qs.instance(n, d, p, 3)
+    g, b = inst["angles"][0]
+    ref, ref_en = orc.energy(n, inst["edges"], g, b, threads=8)
+    for more in (dict(), dict(executor=2)):
+        print(f"{n} {d} {p} {prec} {cfg} {more}", flush=True)
+        zz, zi, en = _run(qtn, n, inst["edges"], g, b, prec, **cfg, **more)
+        _check(zz, zi, en, ref, ref_en, prec, str((cfg, more)))
+
+
 @pytest.mark.parametrize("n,p", [(12, 2), (16, 3), (16, 4), (20, 3)])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_small_graphs_all_configs(qtn, orc, gpu, n, p, prec):
