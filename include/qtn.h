@@ -79,7 +79,9 @@ typedef struct qtn_config {
     int32_t order_trials; /* >1: plan with the cheapest (sum of 2^width) of
                             the greedy min-fill order and order_trials-1
                             min-fill orders with random tie-breaks [0]     */
-    int32_t executor;    /* 0 default (single networks: per-group launches
+    int32_t executor;    /* 0 default (single networks: step launches, the
+                            next task of every light cone in each, or, for
+                            groups that fill the chip, per-group launches
                             over n_streams; batches: persistent lockstep),
                             1 per-group launches, 2 one persistent lockstep
                             launch, 3 per-group launches with each cone's
@@ -240,7 +242,8 @@ typedef struct qtn_timing {
 /* Like qtn_contract, but eager, with every launch serialized on one stream
  * and bracketed by its own HIP event pair, so that each pair times one kernel
  * alone; fills *timing.  Slower than qtn_contract by the event overhead and
- * the lost overlap; the kernels and the schedule are the same. */
+ * the lost overlap.  Every group that qtn_contract runs in a launch with
+ * others (a step launch) gets its own; mappings and results are the same. */
 int qtn_contract_timed(qtn_network *net, void *d_workspace, size_t bytes,
                        void *hip_stream, double *zz_out, double *energy_out,
                        qtn_timing *timing);
@@ -297,7 +300,9 @@ typedef struct qtn_launch_rec {
     int32_t w, L;      /* union width and summed indices (first group)    */
     int32_t n_ops;     /* operands of the first group                     */
     int32_t variant;   /* kernel mapping of the first group: 0 generic,
-                          1 streaming, 2 matrix form, 3 cells              */
+                          1 streaming, 2 matrix form, 3 cells (workgroup
+                          launches: the one it has outside its segment's
+                          program)                                         */
     int32_t n_units;   /* wave units of the first group                   */
     int32_t prec;      /* arithmetic of the first group: QTN_C128/QTN_C64 */
     int32_t cvt;       /* 1: some operand of it is stored in the other
@@ -452,7 +457,8 @@ int qtn_costmodel_adam_step(qtn_costmodel *cm, const float *grad, float lr,
  * for complex64 groups that have one; QTN_VAR_STREAM runs as the cell mapping
  * where it fits, else the lane-sum streaming mapping) and rebuilds the
  * schedule; groups the rule places inside a workgroup stay there (counted as
- * QTN_VAR_BLOCK).
+ * QTN_VAR_BLOCK).  In step launches short groups keep the cell mapping, and
+ * the predicted times choose each launch's workgroup size.
  * counts_out [4] or NULL: groups per QTN_VAR_*.  Workspace: the
  * cost-model bytes for as many samples as the network has groups. */
 int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm,

@@ -86,6 +86,7 @@ struct Task {
   uint32_t n_units;
   int variant;     // wide groups: mapping variant
   double bytes, flops;
+  double ms = -1;  // the cost model's time (-1: none)
 };
 
 // Device layout and launch list of one or more planned networks.
@@ -123,6 +124,17 @@ struct Schedule {
          off_ops = 0, off_stab = 0, off_uperm = 0, off_ranges = 0, off_prog = 0, off_csb = 0, off_ncb = 0, off_cns = 0, off_data = 0, total = 0;
   int64_t scalar_off = 0, scalar_sstride = 0;
   int n_sets = 1;  // angle sets evaluated per launch (one copy of the data each)
+  // step launches: the j-th task of every light cone (after the leading
+  // segment) in one launch; tasks of other mappings follow one by one
+  struct Step {
+    int first = 0, n = 0, blocks = 0;  // tasks [first, first + n) of step_tasks
+    int threads = 0;                   // of a workgroup
+    size_t lds = 0;
+    std::vector<Task> single;
+  };
+  std::vector<Step> steps;
+  std::vector<int4> step_tasks;
+  size_t off_step_tasks = 0;
   std::vector<char> desc_blob;  // bytes [off_desc, off_data)
   uint64_t serial = 0;          // distinct for every schedule built
   int item_order = 0;           // lockstep steps: 0 costliest cone's items first, 1 reversed
@@ -149,12 +161,14 @@ struct Runtime {
   double *pinned = nullptr;
   size_t pinned_n = 0;
   void *ws = nullptr;  // workspace the captured graph was recorded for
-  // pinned copy of the schedule's descriptor bytes, uploaded into the
-  // workspace before every evaluation (the workspace contents are the
-  // caller's between calls, and other schedules may share its address)
-  char *pinned_desc = nullptr;
-  size_t pinned_desc_cap = 0, pinned_desc_n = 0;
-  uint64_t desc_serial = 0;  // schedule whose blob the pinned copy holds
+  // the schedule's descriptors in device memory of the library's own, uploaded
+  // once per schedule (the workspace's contents are the caller's between
+  // calls); null where that allocation failed: then they go up into the
+  // workspace before every evaluation
+  char *dev_desc = nullptr;
+  size_t dev_desc_cap = 0;
+  uint64_t dev_serial = 0;    // schedule whose descriptors dev_desc holds
+  char *desc_base = nullptr;  // offsets off_desc..off_data count from here
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
   int persist_blocks = 0;
@@ -174,11 +188,11 @@ struct Runtime {
     if (main) (void)hipStreamDestroy(main);
     if (pinned) (void)hipHostFree(pinned);
     if (pinned_err) (void)hipHostFree(pinned_err);
-    if (pinned_desc) (void)hipHostFree(pinned_desc);
+    if (dev_desc) (void)hipFree(dev_desc);
     pinned_err = nullptr;
-    pinned_desc = nullptr;
-    pinned_desc_cap = pinned_desc_n = 0;
-    desc_serial = 0;
+    dev_desc = desc_base = nullptr;
+    dev_desc_cap = 0;
+    dev_serial = 0;
     persist_blocks = 0;
     ev_in = ev_fork = nullptr;
     main = nullptr;
@@ -194,8 +208,7 @@ struct Runtime {
     exec = nullptr;
     graph = nullptr;
     ws = nullptr;
-    desc_serial = 0;
-    pinned_desc_n = 0;
+    dev_serial = 0;
   }
   // Takes over o's streams, events and pinned buffers (o is left empty), for
   // a new schedule of the same network: streams are not torn down and
@@ -213,8 +226,8 @@ struct Runtime {
     pinned_n = o.pinned_n;
     persist_blocks = o.persist_blocks;
     pinned_err = o.pinned_err;
-    pinned_desc = o.pinned_desc;
-    pinned_desc_cap = o.pinned_desc_cap;
+    dev_desc = o.dev_desc;
+    dev_desc_cap = o.dev_desc_cap;
     exec = o.exec;
     graph = o.graph;
     o.exec = nullptr;
@@ -224,9 +237,9 @@ struct Runtime {
     o.pinned = nullptr;
     o.pinned_n = 0;
     o.pinned_err = nullptr;
-    o.pinned_desc = nullptr;
-    o.pinned_desc_cap = o.pinned_desc_n = 0;
-    o.desc_serial = 0;
+    o.dev_desc = o.desc_base = nullptr;
+    o.dev_desc_cap = 0;
+    o.dev_serial = 0;
     o.persist_blocks = 0;
     o.ws = nullptr;
     o.device = -1;
@@ -245,6 +258,7 @@ struct Exec {
   bool dataflow = false;  // persistent: per-task dependencies instead of lockstep
   bool hybrid = false;    // persistent lockstep for light cones, launches for heavy ones
   bool lead_per_cone = false;
+  bool steps = false;     // executor 0: step launches where the schedule has them
   uint32_t spin_limit = 1u << 22;
   int grid_quarters = 4;  // persistent grid: this many quarters of the resident blocks
 };
@@ -414,8 +428,7 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
   const int low = std::max(G.L, 6);
   auto cell_fits = [&](int cbits) {
     const int r = cbits - std::max(0, G.L - 6);
-    return !is_small && !persistent && off32 && (int)G.ops.size() <= 64 &&
-           cell_lds_words((int)G.ops.size(), cbits) <= kCellMaxLdsWords &&
+    return !is_small && !persistent && off32 && (int)G.ops.size() <= kCellMaxOps &&
            G.L - 6 <= kCellMaxSerial && r >= 0 && G.w - low >= r;
   };
   int cb = 0;
@@ -640,15 +653,16 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
       // over the unit bits; past kCellURuns of them, ascending order
       // (at most one run per two unit bits)
       int worst = 0;
-      for (const Operand &o : G.ops) {
+      for (size_t t = 0; t <= G.ops.size(); t++) {
+        const uint32_t mask = t < G.ops.size() ? G.ops[t].mask : ~((1u << G.L) - 1u);
         int runs = 0, prev = -2;
         for (size_t j = 0; j < sc.size(); j++) {
           const int q = sc[j].second;
-          if (!((o.mask >> q) & 1u)) {
+          if (!((mask >> q) & 1u)) {
             prev = -2;
             continue;
           }
-          const int rank = __builtin_popcount(o.mask & ((1u << q) - 1u));
+          const int rank = __builtin_popcount(mask & ((1u << q) - 1u));
           if (rank != prev + 1) runs++;
           prev = rank;
         }
@@ -667,6 +681,49 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
     for (size_t j = 0; j < sc.size(); j++) up[first + j] = (uint8_t)sc[j].second;
     dg.n_ubits = (uint8_t)sc.size();
     s.uperm.insert(s.uperm.end(), up, up + 32);
+  }
+  // A cell group's table of a tensor holding the union bits of mask: its
+  // unit-bit runs, the steps of the cell bits (kept bits, then serial bits:
+  // serial cell bit rb + t is union bit 6 + sl - 1 - t, bit 6 the highest
+  // cell bit, summed first) and the mask of those it holds.
+  auto cell_table = [&](uint32_t mask) -> int {
+    const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32, *up = rp + rb;
+    uint16_t ur[kCellURuns];
+    std::memset(ur, 0, sizeof ur);
+    auto place = [&](int q) { return __builtin_popcount(mask & ((1u << q) - 1u)); };
+    int nur = 0;
+    for (int j = 0; j < dg.n_ubits;) {
+      const int q = up[j];
+      if (!((mask >> q) & 1u)) {
+        j++;
+        continue;
+      }
+      const int dst = place(q);
+      int len = 1;
+      while (j + len < dg.n_ubits && ((mask >> up[j + len]) & 1u) && place(up[j + len]) == dst + len)
+        len++;
+      if (nur == kCellURuns) return set_err(QTN_ERANGE, "cell mapping: unit runs");
+      ur[nur++] = (uint16_t)(j | (len << 5) | (dst << 11));
+      j += len;
+    }
+    dg.n_unit = (uint8_t)std::max<int>(dg.n_unit, nur);
+    for (int w = 0; w < kCellURuns / 2; w++)
+      s.stab.push_back((int32_t)((uint32_t)ur[2 * w] | ((uint32_t)ur[2 * w + 1] << 16)));
+    uint32_t cm = 0;
+    for (int j = 0; j < cb; j++) {
+      const int q = j < rb ? rp[j] : 6 + dg.sl - 1 - (j - rb);
+      const bool held = (mask >> q) & 1u;
+      s.stab.push_back(held ? (int32_t)(1u << place(q)) : 0);
+      cm |= (held ? 1u : 0u) << j;
+    }
+    s.stab.push_back((int32_t)cm);
+    return QTN_OK;
+  };
+  if (cell) {
+    // the output holds every kept bit
+    dg.gtab = (int32_t)s.stab.size();
+    const int rc = cell_table(~((1u << G.L) - 1u));
+    if (rc) return rc;
   }
   for (int k : order) {
     const Operand &o = G.ops[k];
@@ -700,46 +757,9 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
         s.stab.push_back((int32_t)pext32(st << (1 + dg.rls), o.mask));
     }
     if (cell) {
-      // cell offsets (cell c: kept bits c % 2^rb, serial bits c / 2^rb),
-      // then the runs giving the unit part of the index from the unit
-      // number
       d.stab = (int32_t)s.stab.size();
-      const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32;
-      uint32_t cm = 0;
-      // serial cell bit rb + t is union bit 6 + sl - 1 - t (bit 6 the
-      // highest cell bit, summed first)
-      for (int j = 0; j < rb; j++) cm |= ((o.mask >> rp[j]) & 1u) << j;
-      for (int t = 0; t < dg.sl; t++)
-        cm |= ((o.mask >> (6 + dg.sl - 1 - t)) & 1u) << (rb + t);
-      for (uint32_t c = 0; c < (1u << cb); c++) {
-        uint32_t I = 0;
-        for (int j = 0; j < rb; j++) I |= ((c >> j) & 1u) << rp[j];
-        for (int t = 0; t < dg.sl; t++) I |= ((c >> (rb + t)) & 1u) << (6 + dg.sl - 1 - t);
-        s.stab.push_back((int32_t)pext32(I, o.mask));
-      }
-      const uint8_t *up = rp + rb;
-      uint16_t ur[kCellURuns];
-      std::memset(ur, 0, sizeof ur);
-      int nur = 0;
-      for (int j = 0; j < dg.n_ubits;) {
-        const int q = up[j];
-        if (!((o.mask >> q) & 1u)) {
-          j++;
-          continue;
-        }
-        const int dst = __builtin_popcount(o.mask & ((1u << q) - 1u));
-        int len = 1;
-        while (j + len < dg.n_ubits && ((o.mask >> up[j + len]) & 1u) &&
-               __builtin_popcount(o.mask & ((1u << up[j + len]) - 1u)) == dst + len)
-          len++;
-        if (nur == kCellURuns) return set_err(QTN_ERANGE, "cell mapping: unit runs");
-        ur[nur++] = (uint16_t)(j | (len << 5) | (dst << 11));
-        j += len;
-      }
-      dg.n_unit = (uint8_t)std::max<int>(dg.n_unit, nur);
-      for (int w = 0; w < kCellURuns / 2; w++)
-        s.stab.push_back((int32_t)((uint32_t)ur[2 * w] | ((uint32_t)ur[2 * w + 1] << 16)));
-      s.stab.push_back((int32_t)cm);
+      const int rc = cell_table(o.mask);
+      if (rc) return rc;
     }
     if (mfma) {
       // the operand's element offsets of the tile's rows (side A) or
@@ -804,9 +824,11 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
         return false;
     }
   }
-  auto pieces_of = [](const DevGroup &G) {
-    const int units = G.w > 8 ? 1 << (G.w - 8) : 1;
-    return std::min(units, kProgPieces);
+  auto prog_units = [](const DevGroup &G) {
+    return 1 << std::max(0, G.w - 6 - prog_reg_bits(G.w, G.L));
+  };
+  auto pieces_of = [&](const DevGroup &G) {
+    return std::min(prog_units(G), kProgPieces);
   };
   size_t prev_at = 0;
   bool first = true;
@@ -960,7 +982,7 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
     uint32_t item = 0;
     for (int i : by_level) {
       const DevGroup &G = s.groups[b + i];
-      const int units = G.w > 8 ? 1 << (G.w - 8) : 1, np = pieces_of(G), per = units / np;
+      const int np = pieces_of(G), per = prog_units(G) / np;
       uint32_t out;
       if (G.w == G.L) out = kLocScalar | (uint32_t)((G.out_off - pb.scalar) / es) << 2;
       else if (lds[i]) out = kLocLds | (uint32_t)(kProgPoolAt + where[i]) << 2;
@@ -970,7 +992,7 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
                          (uint32_t)op_at[i] << 16);
         prog.push_back(out);
         prog.push_back((uint32_t)(q * per) | (uint32_t)per << 16);
-        prog.push_back(0);
+        prog.push_back((uint32_t)prog_reg_bits(G.w, G.L));
       }
       begin[level[i] + 1] = item;
     }
@@ -987,6 +1009,86 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
 int prog_prec(const Schedule &s, int range) {
   const int4 r = s.ranges[range];
   return r.z >= 0 ? s.groups[r.x].prec : -1;
+}
+
+// Step launches of the light cones' task chains, where the rule takes them.
+constexpr double kAloneMs = 3.5e-3;      // a launch of one tiny group
+constexpr double kStepUnits = 4;         // units a wave takes once those are busy: 40 vertices,
+                                         // mixed, 9.6 ms with 1, 8.7 with 4, 8.8 with 16
+constexpr double kStepMaxUnits = 16384;  // most units a task
+void plan_steps(Schedule &s) {
+  double units = 0;
+  int64_t n_tasks = 0, n_other = 0;
+  size_t n_steps = 0;
+  for (const auto &tk : s.cone_tasks) {
+    n_steps = std::max(n_steps, tk.size());
+    for (const Task &t : tk) {
+      n_tasks++;
+      if (t.kind == QTN_K_BLOCK) {
+        if (s.ranges[t.index].z < 0) n_other++;
+      } else {
+        units += (double)s.groups[t.index].n_units * s.n_sets;
+        if (!step_group(s.groups[t.index])) n_other++;
+      }
+    }
+  }
+  // Above the line the groups fill the chip by themselves, and the four
+  // streams overlap the ends of launches of unlike light cones, which a step
+  // makes wait for each other.  Step launches against four streams, by units
+  // a task: 17 (20 vertices, depth 3) 286 us against 355; 469 (27 sets of a
+  // 22-vertex one) 333 against 430; 3,900 (40 vertices, mixed precision) 8.7
+  // ms against 10.3; 21,500 (17 sets of a depth-4 one) 8.7 ms against 8.5;
+  // 87,000 (32 sets of the 30-vertex one) 108 ms against 100.  A schedule
+  // that is mostly other mappings keeps its streams.
+  if (n_tasks == 0 || n_other * 8 > n_tasks || units > kStepMaxUnits * (double)n_tasks) return;
+  s.steps.resize(n_steps);
+  std::vector<std::vector<const Task *>> in_step(n_steps);
+  for (const auto &tk : s.cone_tasks)
+    for (size_t j = 0; j < tk.size(); j++) in_step[j].push_back(&tk[j]);
+  for (size_t j = 0; j < n_steps; j++) {
+    Schedule::Step &st = s.steps[j];
+    st.first = (int)s.step_tasks.size();
+    std::vector<std::pair<int, int>> wide;  // (-workgroups, group)
+    // a workgroup sets up its tables before its first unit: once the step
+    // fills the chip, several units share a set-up
+    double step_units = 0;
+    for (const Task *t : in_step[j])
+      if (t->kind == QTN_K_WIDE) step_units += (double)s.groups[t->index].n_units * s.n_sets;
+    const double per_wave = std::min(kStepUnits, step_units / kStepWaves);
+    // A segment is one workgroup's chain and wants many waves; groups that
+    // fill the chip want small workgroups, which start and end singly.  40
+    // vertices, mixed: 7.9 ms with 256 threads, 8.2 with 512, 8.6 with 1,024;
+    // 20 vertices, depth 3: 206, 169 and 165 us.  The cost model's times say
+    // where a segment outlasts the groups all the same (quartic graphs of
+    // 171 to 284 vertices at depth 3: 420-600, 341-471 and 337-446 us).
+    double seg_ms = 0, wide_ms = 0;
+    for (const Task *t : in_step[j])
+      (t->kind == QTN_K_BLOCK ? seg_ms : wide_ms) = std::max(t->kind == QTN_K_BLOCK ? seg_ms : wide_ms, t->ms);
+    st.threads = seg_ms > wide_ms ? 1024 : (step_units >= 2 * kStepWaves ? 256 : 512);
+    for (const Task *tp : in_step[j]) {
+      const Task &t = *tp;
+      if (t.kind == QTN_K_BLOCK && s.ranges[t.index].z >= 0) {
+        // segments first: each is one workgroup's chain
+        s.step_tasks.push_back(make_int4(-1, st.blocks, s.n_sets, s.ranges[t.index].z));
+        st.blocks += s.n_sets;
+        st.lds = std::max(st.lds, (size_t)kProgLdsBytes);
+      } else if (t.kind == QTN_K_WIDE && step_group(s.groups[t.index])) {
+        wide.push_back({-step_blocks(s.groups[t.index], s.n_sets, per_wave, st.threads), t.index});
+        st.lds = std::max(st.lds, step_lds(s.groups[t.index]));
+      } else {
+        st.single.push_back(t);
+      }
+    }
+    std::stable_sort(wide.begin(), wide.end());
+    for (auto &w : wide) {
+      const int nb = -w.first;
+      // a grid of whole rounds over the XCDs starts on one
+      if (nb >= 64) st.blocks = (st.blocks + 7) & ~7;
+      s.step_tasks.push_back(make_int4(w.second, st.blocks, nb, 0));
+      st.blocks += nb;
+    }
+    st.n = (int)s.step_tasks.size() - st.first;
+  }
 }
 
 // persistent: the schedule runs in a persistent executor (every group inside
@@ -1060,14 +1162,15 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       s.cone_heavy.push_back(heavy ? 1 : 0);
       std::vector<Task> tasks;
       int open_begin = -1;
-      double seg_bytes = 0, seg_flops = 0;
+      double seg_bytes = 0, seg_flops = 0, seg_ms = 0;
       auto close_segment = [&](int end) {
         if (open_begin < 0) return;
         if (programs) jobs.push_back({open_begin, end, pb, (int)s.ranges.size(), {}});
         s.ranges.push_back(make_int4(open_begin, end, -1, 0));
-        tasks.push_back({QTN_K_BLOCK, (int)s.ranges.size() - 1, 0, 0, seg_bytes, seg_flops});
+        tasks.push_back({QTN_K_BLOCK, (int)s.ranges.size() - 1, 0, 0, seg_bytes, seg_flops,
+                         seg_ms < 0 ? -1 : seg_ms + kAloneMs});
         open_begin = -1;
-        seg_bytes = seg_flops = 0;
+        seg_bytes = seg_flops = seg_ms = 0;
       };
       // index slicing: the groups run once per slice, in order, on the one
       // arena; slice k's scalars take slots k * n_scalars onwards
@@ -1127,9 +1230,10 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
           if (open_begin < 0) open_begin = gid;
           seg_bytes += gb;
           seg_flops += gf;
+          seg_ms = G.pred_ms < 0 || seg_ms < 0 ? -1 : seg_ms + std::max(0.0, G.pred_ms - kAloneMs);
         } else {
           close_segment(gid);
-          tasks.push_back({QTN_K_WIDE, gid, dg.n_units, dg.variant, gb, gf});
+          tasks.push_back({QTN_K_WIDE, gid, dg.n_units, dg.variant, gb, gf, G.pred_ms});
         }
       }
       close_segment((int)s.groups.size());
@@ -1257,6 +1361,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
     for (int i = (int)s.item_task.size() - 1; i >= 0; i--) s.task_first[s.item_task[i]] = i;
     s.n_init = s.n_steps > 0 ? s.step_begin[1] : 0;
   }
+  if (!force && !persistent && nets[0]->executor == 0) plan_steps(s);
   s.bytes[QTN_K_BLOCK] = s.init_bytes;
   s.flops[QTN_K_BLOCK] = s.init_flops;
   // a wide launch walks the units of every set in one flat 31-bit index
@@ -1289,7 +1394,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       const int32_t shift = (int32_t)s.stab_at[g] - (int32_t)dev_stab.size();
       const int32_t first = G.op_begin;
       G.op_begin = (int32_t)dev_ops.size();
-      if (G.variant == kVarMfma) G.gtab -= shift;
+      if (G.variant == kVarMfma || G.variant == kVarCell) G.gtab -= shift;
       for (int k = 0; k < G.n_ops; k++) {
         DevOp o = s.ops[first + k];
         if (o.stab >= 0) o.stab -= shift;
@@ -1318,6 +1423,8 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   if (!size_only) {
     for (const int4 &r : s.ranges) dev_ranges.push_back(on_device(r));
     for (int4 &it : s.items) it = on_device(it);
+    for (int4 &t : s.step_tasks)
+      if (t.x >= 0) t.x = s.dev_group[t.x];
   }
 
   // workspace layout (bytes)
@@ -1334,7 +1441,8 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   s.off_csb = align_up(s.off_prog + sizeof(uint32_t) * (s.prog.size() + s.prog_more), 256);
   s.off_ncb = align_up(s.off_csb + sizeof(int) * s.csb.size(), 256);
   s.off_cns = align_up(s.off_ncb + sizeof(int) * s.ncb.size(), 256);
-  s.off_items = align_up(s.off_cns + sizeof(int) * s.cns.size(), 256);
+  s.off_step_tasks = align_up(s.off_cns + sizeof(int) * s.cns.size(), 256);
+  s.off_items = align_up(s.off_step_tasks + sizeof(int4) * s.step_tasks.size(), 256);
   s.off_steps = align_up(s.off_items + sizeof(int4) * s.items.size(), 256);
   s.off_item_task = align_up(s.off_steps + sizeof(int) * s.step_begin.size(), 256);
   s.off_task_next = align_up(s.off_item_task + sizeof(int) * s.item_task.size(), 256);
@@ -1359,6 +1467,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   put(s.off_csb, s.csb.data(), sizeof(int) * s.csb.size());
   put(s.off_ncb, s.ncb.data(), sizeof(int) * s.ncb.size());
   put(s.off_cns, s.cns.data(), sizeof(int) * s.cns.size());
+  put(s.off_step_tasks, s.step_tasks.data(), sizeof(int4) * s.step_tasks.size());
   put(s.off_items, s.items.data(), sizeof(int4) * s.items.size());
   put(s.off_steps, s.step_begin.data(), sizeof(int) * s.step_begin.size());
   put(s.off_item_task, s.item_task.data(), sizeof(int) * s.item_task.size());
@@ -1366,6 +1475,13 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   put(s.off_task_first, s.task_first.data(), sizeof(int) * s.task_first.size());
   put(s.off_task_need, s.task_need.data(), sizeof(int) * s.task_need.size());
   return QTN_OK;
+}
+
+void drop_graph(Runtime &rt) {
+  if (rt.exec) (void)hipGraphExecDestroy(rt.exec);
+  if (rt.graph) (void)hipGraphDestroy(rt.graph);
+  rt.exec = nullptr;
+  rt.graph = nullptr;
 }
 
 int ensure_runtime(Runtime &rt, int n_streams, int n_res) {
@@ -1401,8 +1517,10 @@ int ensure_runtime(Runtime &rt, int n_streams, int n_res) {
     rt.ev_join.push_back(e);
   }
   if (rt.pinned_n < (size_t)n_res) {
+    drop_graph(rt);  // it holds the old buffer's address
     if (rt.pinned) QTN_HIP(hipHostFree(rt.pinned));
     rt.pinned = nullptr;
+    rt.pinned_n = 0;
     QTN_HIP(hipHostMalloc((void **)&rt.pinned, sizeof(double) * n_res, hipHostMallocDefault));
     rt.pinned_n = n_res;
   }
@@ -1474,29 +1592,23 @@ void set_item_order(Schedule &s, int order) {
   s.serial = ++g_sched_serial;
 }
 
-void drop_graph(Runtime &rt) {
-  if (rt.exec) (void)hipGraphExecDestroy(rt.exec);
-  if (rt.graph) (void)hipGraphDestroy(rt.graph);
-  rt.exec = nullptr;
-  rt.graph = nullptr;
-}
-
 // Every launch of one evaluation, on rt.main and the side streams.
 int enqueue(Exec &X, Timer &tm) {
   Schedule &s = X.sched;
   Runtime &rt = X.rt;
   char *ws = (char *)rt.ws;
+  char *desc = rt.desc_base;
   void *data = ws + s.off_data;
-  auto *groups = (const DevGroup *)(ws + s.off_groups);
-  auto *ops = (const DevOp *)(ws + s.off_ops);
-  auto *ranges = (const int4 *)(ws + s.off_ranges);
-  auto *prog = (const uint32_t *)(ws + s.off_prog);
-  auto *stab = (const int32_t *)(ws + s.off_stab);
-  auto *uperm = (const uint8_t *)(ws + s.off_uperm);
+  auto *groups = (const DevGroup *)(desc + s.off_groups);
+  auto *ops = (const DevOp *)(desc + s.off_ops);
+  auto *ranges = (const int4 *)(desc + s.off_ranges);
+  auto *prog = (const uint32_t *)(desc + s.off_prog);
+  auto *stab = (const int32_t *)(desc + s.off_stab);
+  auto *uperm = (const uint8_t *)(desc + s.off_uperm);
   int rc;
   if ((rc = tm.begin(QTN_K_FILL, rt.main))) return rc;
-  QTN_HIP(launch_fill(s.prec, data, (const double *)(ws + s.off_angles),
-                      (const FillDesc *)(ws + s.off_fills), s.n_nets, s.n_angles, s.n_sets,
+  QTN_HIP(launch_fill(s.prec, data, rt.pinned + (2 * s.n_cones + s.n_nets) * s.n_sets,
+                      (const FillDesc *)(desc + s.off_fills), s.n_nets, s.n_angles, s.n_sets,
                       rt.main));
   if ((rc = tm.end(rt.main))) return rc;
   const int NS = s.n_sets;  // launch records carry the bytes of every set
@@ -1529,17 +1641,17 @@ int enqueue(Exec &X, Timer &tm) {
     if ((rc = tm.begin(QTN_K_PERSISTENT, rt.main, 0, (int)s.groups.size(), b_all, f_all, true)))
       return rc;
     if (X.dataflow)
-      QTN_HIP(launch_dataflow(data, groups, ops, stab, uperm, prog, (const int4 *)(ws + s.off_items),
-                              (int)s.items.size(), s.n_init, (const int *)(ws + s.off_item_task),
-                              (const int *)(ws + s.off_task_next),
-                              (const int *)(ws + s.off_task_first),
-                              (const int *)(ws + s.off_task_need), (uint32_t *)(ws + s.off_queue),
-                              (uint32_t *)(ws + s.off_ctl), s.n_ctl, nb, X.spin_limit, rt.main,
+      QTN_HIP(launch_dataflow(data, groups, ops, stab, uperm, prog, (const int4 *)(desc + s.off_items),
+                              (int)s.items.size(), s.n_init, (const int *)(desc + s.off_item_task),
+                              (const int *)(desc + s.off_task_next),
+                              (const int *)(desc + s.off_task_first),
+                              (const int *)(desc + s.off_task_need), (uint32_t *)(desc + s.off_queue),
+                              (uint32_t *)(desc + s.off_ctl), s.n_ctl, nb, X.spin_limit, rt.main,
                               tm.t0(), tm.t1()));
     else
       QTN_HIP(launch_persistent(s.prec, data, groups, ops, stab, uperm, prog,
-                                (const int4 *)(ws + s.off_items), (const int *)(ws + s.off_steps),
-                                s.n_steps, (uint32_t *)(ws + s.off_ctl), s.n_ctl, nb, X.spin_limit,
+                                (const int4 *)(desc + s.off_items), (const int *)(desc + s.off_steps),
+                                s.n_steps, (uint32_t *)(desc + s.off_ctl), s.n_ctl, nb, X.spin_limit,
                                 rt.main, tm.t0(), tm.t1()));
     if ((rc = tm.end(rt.main, true))) return rc;
     if (X.hybrid && any_heavy) {
@@ -1594,7 +1706,22 @@ int enqueue(Exec &X, Timer &tm) {
   const int K = tm.on ? 1 : (int)rt.side.size();
   bool any = X.lead_per_cone;
   for (auto &tk : s.cone_tasks) any |= !tk.empty();
-  if (any) {
+  if (X.steps && !s.steps.empty() && !tm.on) {
+    // the cones' chains in step launches
+    auto *tasks = (const int4 *)(desc + s.off_step_tasks);
+    for (const Schedule::Step &st : s.steps) {
+      QTN_HIP(launch_step(s.prec, data, groups, ops, stab, uperm, prog, tasks + st.first, st.n,
+                          st.blocks, st.threads, st.lds, NS, rt.main));
+      for (const Task &t : st.single) {
+        if (t.kind == QTN_K_BLOCK)
+          QTN_HIP(launch_block_groups(prog_prec(s, t.index), data, groups, ops, stab, uperm, prog,
+                                      ranges, t.index, 1, NS, rt.main));
+        else
+          QTN_HIP(launch_wide_group(s.groups[t.index], data, groups, ops, stab, uperm,
+                                    s.dev_group[t.index], NS, rt.main));
+      }
+    }
+  } else if (any) {
     QTN_HIP(hipEventRecord(rt.ev_fork, rt.main));
     for (int i = 0; i < K; i++) QTN_HIP(hipStreamWaitEvent(rt.side[i], rt.ev_fork, 0));
     // heaviest light cones first, dealt round-robin over the side streams
@@ -1642,17 +1769,19 @@ int enqueue(Exec &X, Timer &tm) {
   }
   if ((rc = tm.begin(QTN_K_REDUCE, rt.main))) return rc;
   QTN_HIP(launch_reduce(s.scalar_prec == 1 ? kPrecC64 : kPrecC128, data, s.scalar_off,
-                        s.scalar_sstride, (const int *)(ws + s.off_csb),
-                        (const int *)(ws + s.off_ncb), (const int *)(ws + s.off_cns), s.n_cones,
+                        s.scalar_sstride, (const int *)(desc + s.off_csb),
+                        (const int *)(desc + s.off_ncb), (const int *)(desc + s.off_cns), s.n_cones,
                         s.n_nets, NS,
-                        (double *)(ws + s.off_res), rt.main));
+                        (double *)(ws + s.off_res), rt.pinned,
+                        X.persistent ? (const uint32_t *)(desc + s.off_ctl) : nullptr,
+                        rt.pinned_err, rt.main));
   if ((rc = tm.end(rt.main))) return rc;
   return QTN_OK;
 }
 
-// Upload descriptors and angles, run, read back.  The descriptors go up
-// before every evaluation: between calls the workspace belongs to the caller,
-// who may reuse it for other schedules or other data.
+// One evaluation: the angles are read from, and the results written to,
+// page-locked host memory by the first and the last kernel, so that a call
+// copies nothing once the schedule's descriptors are on the device.
 // set_angles: n_sets * n_angles doubles (per set, per network gamma[p] then
 // beta[p]); NULL: the networks' own angles (one set).
 int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, size_t bytes,
@@ -1667,39 +1796,45 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
   if ((uintptr_t)ws % 256) return set_err(QTN_EINVAL, "workspace must be 256-byte aligned");
   if (!set_angles && s.n_sets != 1) return set_err(QTN_EINVAL, "angle sets missing");
   const int n_res = (2 * s.n_cones + s.n_nets) * s.n_sets;
-  int rc = ensure_runtime(rt, n_streams, std::max(n_res, s.n_angles * s.n_sets));
+  int rc = ensure_runtime(rt, n_streams, n_res + s.n_angles * s.n_sets);
   if (rc) return rc;
-  if (rt.desc_serial != s.serial || rt.pinned_desc_n != s.desc_blob.size()) {
-    if (rt.pinned_desc_cap < s.desc_blob.size()) {
-      if (rt.pinned_desc) QTN_HIP(hipHostFree(rt.pinned_desc));
-      rt.pinned_desc = nullptr;
-      rt.pinned_desc_cap = 0;
-      QTN_HIP(hipHostMalloc((void **)&rt.pinned_desc, s.desc_blob.size(), hipHostMallocDefault));
-      rt.pinned_desc_cap = s.desc_blob.size();
+  const size_t n_desc = s.desc_blob.size();
+  if (rt.dev_desc_cap < n_desc) {
+    drop_graph(rt);
+    if (rt.dev_desc) QTN_HIP(hipFree(rt.dev_desc));
+    rt.dev_desc = nullptr;
+    rt.dev_desc_cap = 0;
+    rt.dev_serial = 0;
+    if (hipMalloc((void **)&rt.dev_desc, n_desc) == hipSuccess) {
+      rt.dev_desc_cap = n_desc;
+    } else {
+      rt.dev_desc = nullptr;
+      (void)hipGetLastError();
     }
-    std::memcpy(rt.pinned_desc, s.desc_blob.data(), s.desc_blob.size());
-    rt.pinned_desc_n = s.desc_blob.size();
-    rt.desc_serial = s.serial;
   }
+  // the captured graph holds the old addresses
+  char *base = rt.dev_desc ? rt.dev_desc - s.off_desc : (char *)ws;
+  if (rt.ws != ws || rt.desc_base != base) drop_graph(rt);
+  rt.ws = ws;
+  rt.desc_base = base;
   QTN_HIP(hipEventRecord(rt.ev_in, (hipStream_t)stream));
   QTN_HIP(hipStreamWaitEvent(rt.main, rt.ev_in, 0));
-  // the captured graph holds the old workspace's addresses
-  if (rt.ws != ws) drop_graph(rt);
-  rt.ws = ws;
-  QTN_HIP(hipMemcpyAsync((char *)ws + s.off_desc, rt.pinned_desc, rt.pinned_desc_n,
-                         hipMemcpyHostToDevice, rt.main));
+  if (!rt.dev_desc || rt.dev_serial != s.serial) {
+    QTN_HIP(hipMemcpyAsync(base + s.off_desc, s.desc_blob.data(), n_desc, hipMemcpyHostToDevice,
+                           rt.main));
+    rt.dev_serial = s.serial;
+  }
+  double *angles = rt.pinned + n_res;
   if (set_angles) {
-    std::memcpy(rt.pinned, set_angles, sizeof(double) * s.n_angles * s.n_sets);
+    std::memcpy(angles, set_angles, sizeof(double) * s.n_angles * s.n_sets);
   } else {
     size_t a = 0;
     for (auto *net : nets) {
-      for (int l = 0; l < net->p; l++) rt.pinned[a + l] = net->gamma[l];
-      for (int l = 0; l < net->p; l++) rt.pinned[a + net->p + l] = net->beta[l];
+      for (int l = 0; l < net->p; l++) angles[a + l] = net->gamma[l];
+      for (int l = 0; l < net->p; l++) angles[a + net->p + l] = net->beta[l];
       a += 2 * net->p;
     }
   }
-  QTN_HIP(hipMemcpyAsync((char *)ws + s.off_angles, rt.pinned,
-                         sizeof(double) * s.n_angles * s.n_sets, hipMemcpyHostToDevice, rt.main));
   if (eager || tm.on) {
     if ((rc = enqueue(X, tm))) return rc;
   } else {
@@ -1719,13 +1854,8 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
     }
     QTN_HIP(hipGraphLaunch(rt.exec, rt.main));
   }
-  QTN_HIP(hipMemcpyAsync(rt.pinned, (char *)ws + s.off_res, sizeof(double) * n_res,
-                         hipMemcpyDeviceToHost, rt.main));
-  if (X.persistent)
-    QTN_HIP(hipMemcpyAsync(rt.pinned_err, (char *)ws + s.off_ctl, 4 * sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, rt.main));
   QTN_HIP(hipStreamSynchronize(rt.main));
-  if (X.persistent && rt.pinned_err[2] != 0)
+  if (X.persistent && rt.pinned_err[0] != 0)
     return set_err(QTN_EDEVICE, X.dataflow
                                     ? "persistent executor: a dependency wait exceeded its bound"
                                     : "persistent executor: a grid barrier wait exceeded its bound");
@@ -1923,6 +2053,7 @@ int qtn_plan(qtn_network *net, const int32_t *const *orders, int32_t precision,
     ex->hybrid = net->executor == 5;
     ex->dataflow = net->executor == 4;
     ex->lead_per_cone = net->executor == 3;
+    ex->steps = net->executor == 0;
     {
       size_t mx = ex->sched.total;
       for (const Force &f : tune_candidates()) {
@@ -2045,6 +2176,7 @@ static Exec *angle_exec(qtn_network *net, int n_sets, int *rc) {
   if (*rc) return nullptr;
   // per-group launches (the persistent executors run one set)
   ex->lead_per_cone = net->executor == 3;
+  ex->steps = net->executor == 0;
   ex->spin_limit = net->spin_limit;
   if (net->angle_exec) ex->rt.take(net->angle_exec->rt);
   net->angle_exec = std::move(ex);
@@ -2322,7 +2454,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
         // the same groups again, each alone in one workgroup
         Timer tb;
         tb.on = true;
-        char *ws = (char *)d_workspace;
+        char *ws = (char *)d_workspace, *desc = ex.rt.desc_base;
         const Schedule &s = ex.sched;
         for (size_t i = 0; i < s.singles.size(); i++) {
           // the cell mapping, the complex128 matrix form and matrix-form
@@ -2336,10 +2468,10 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           }
           hipError_t he = launch_block_groups(
               prog_prec(s, s.singles_range0 + (int)i), ws + s.off_data,
-              (const DevGroup *)(ws + s.off_groups),
-              (const DevOp *)(ws + s.off_ops), (const int32_t *)(ws + s.off_stab),
-              (const uint8_t *)(ws + s.off_uperm), (const uint32_t *)(ws + s.off_prog),
-              (const int4 *)(ws + s.off_ranges),
+              (const DevGroup *)(desc + s.off_groups),
+              (const DevOp *)(desc + s.off_ops), (const int32_t *)(desc + s.off_stab),
+              (const uint8_t *)(desc + s.off_uperm), (const uint32_t *)(desc + s.off_prog),
+              (const int4 *)(desc + s.off_ranges),
               s.singles_range0 + (int)i, 1, n_sets, ex.rt.main, tb.t0(), tb.t1());
           if (he == hipSuccess) rc = tb.end(ex.rt.main, true);
           if (he != hipSuccess || rc) {
@@ -2413,6 +2545,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
       if (best >= 0) {
         G.pick_variant = (int8_t)cands[best].variant;
         G.pick_rls = (int8_t)cands[best].rls;
+        G.pred_ms = -1;
         if (!G.small) {
           rep.tuned_ms += t[best];
           rep.picks[best]++;
@@ -2447,6 +2580,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
     tuned->hybrid = net->exec->hybrid;
     tuned->dataflow = net->exec->dataflow;
     tuned->lead_per_cone = net->exec->lead_per_cone;
+    tuned->steps = net->exec->steps;
     tuned->spin_limit = net->exec->spin_limit;
     tuned->rt.take(ex.rt);
     drop_batches_with(net);
@@ -2519,6 +2653,7 @@ int qtn_set_tune_picks(qtn_network *net, const qtn_tune_pick *picks, int64_t n) 
       G.pick_place = picks[i].place;
       G.pick_variant = picks[i].variant;
       G.pick_rls = picks[i].rls;
+      G.pred_ms = -1;
     }
     qtn_network *one[1] = {net};
     auto ex = std::make_unique<Exec>();
@@ -2529,6 +2664,7 @@ int qtn_set_tune_picks(qtn_network *net, const qtn_tune_pick *picks, int64_t n) 
     ex->hybrid = net->exec->hybrid;
     ex->dataflow = net->exec->dataflow;
     ex->lead_per_cone = net->exec->lead_per_cone;
+    ex->steps = net->exec->steps;
     ex->spin_limit = net->exec->spin_limit;
     drop_batches_with(net);
     net->exec = std::move(ex);
@@ -3121,6 +3257,10 @@ int qtn_costmodel_adam_step(qtn_costmodel *cm, const float *grad, float lr, void
   }
 }
 
+// A group leaves the step launches' mapping when it takes more than this many
+// milliseconds.
+constexpr double kLeaveStepMs = 0.05;
+
 int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm, void *d_ws, size_t bytes,
                         void *hip_stream, int32_t *counts_out) {
   try {
@@ -3142,6 +3282,7 @@ int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm, void *d_ws, s
     int rc = qtn_costmodel_predict(cm, feats.data(), n, d_ws, bytes, hip_stream, y.data());
     if (rc) return rc;
     int32_t counts[4] = {0, 0, 0, 0};
+    const bool steps = net->exec->steps && !net->exec->sched.steps.empty();
     for (int64_t i = 0; i < n; i++) {
       Group &G = *gs[i];
       const float *p = &y[i * kMlpOut];
@@ -3154,12 +3295,17 @@ int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm, void *d_ws, s
       if (G.small) {
         G.pick_variant = -1;
         G.pick_rls = -1;
+        G.pred_ms = std::exp(p[QTN_VAR_BLOCK]);
         counts[QTN_VAR_BLOCK]++;
         continue;
       }
       int best = p[QTN_VAR_STREAM] <= p[QTN_VAR_GENERIC] ? QTN_VAR_STREAM : QTN_VAR_GENERIC;
       if (G.prec == 1 && p[QTN_VAR_MFMA] < p[best] && gemm_shape(G, *gp[i], nullptr))
         best = QTN_VAR_MFMA;
+      // step launches run the cell mapping: the times are those of launches
+      // of their own, and only a long group is worth one
+      if (steps && p[QTN_VAR_STREAM] < std::log(kLeaveStepMs)) best = QTN_VAR_STREAM;
+      G.pred_ms = std::exp(p[best]);
       counts[best]++;
       // the streaming family: the cell mapping where it fits, else the
       // lane-sum streaming mapping (the planner falls back by itself)
@@ -3174,6 +3320,7 @@ int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm, void *d_ws, s
     ex->hybrid = net->exec->hybrid;
     ex->dataflow = net->exec->dataflow;
     ex->lead_per_cone = net->exec->lead_per_cone;
+    ex->steps = net->exec->steps;
     ex->spin_limit = net->exec->spin_limit;
     drop_batches_with(net);
     net->exec = std::move(ex);

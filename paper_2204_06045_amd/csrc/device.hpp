@@ -70,18 +70,20 @@ enum Variant : uint8_t { kVarGeneric = 0, kVarStream = 1, kVarMfma = 2, kVarCell
 // uperm).  Ops [0, n_step) hold bit 6 (all ops when sl = 0), the next
 // n_serial hold bit 7 but not 6 (sl = 2), the rest no serial bit; the first
 // n_step0 ops of the last of these levels hold no unit bit (sl = 0: hold lane
-// bits only); n_unit = the most unit-bit runs of any operand.  Each op's stab entry starts its table: 2^CB cell offsets
-// (elements), kCellURuns / 2 words of unit-bit runs (src | len << 5 | dst <<
-// 11, two per word, src counting unit bits; unused runs 0) giving the unit
-// part of its index, then the mask of the cell bits its index holds.
+// bits only); n_unit = the most unit-bit runs of any operand or of the
+// output.  Each op's stab entry starts its table: kCellURuns / 2 words of
+// unit-bit runs (src | len << 5 | dst << 11, two per word, src counting unit
+// bits; unused runs 0) giving the unit part of its index, then CB element
+// steps of the cell bits (0: not held), then the mask of the cell bits held.
+// The output's, at gtab, is of the same form (dst and steps in the output).
 constexpr int kCellMinCB = 2, kCellMaxCB = 4, kCellRuleCB = 3;
 constexpr int kCellURuns = 16;
 constexpr int kCellMaxSerial = 2;
-// LDS words of a cell group's tables: per operand 2^CB lane tables of 64
-// words and its unit-bit runs.
-constexpr int cell_lds_words(int n_ops, int cb) { return n_ops * ((64 << cb) + kCellURuns / 2); }
-constexpr int cell_table_words(int cb) { return (1 << cb) + kCellURuns / 2 + 1; }
-constexpr int kCellMaxLdsWords = 16384;  // 64 KiB per workgroup
+constexpr int kCellMaxOps = 63;  // one lane per operand and one for the output
+constexpr int cell_table_words(int cb) { return kCellURuns / 2 + cb + 1; }
+// LDS words of a cell group's tables: the operands' lane offsets, and the
+// unit-bit runs of the operands and the output.
+constexpr int cell_lds_words(int n_ops) { return n_ops * 64 + (n_ops + 1) * (kCellURuns / 2); }
 
 // Matrix form (kVarMfma): ops are [side A..., side B...] with n_unit = |side
 // A|, n_step = |side B|.  A work unit is one kMmTM x 16 rls (m x n) output
@@ -138,9 +140,14 @@ enum ProgLoc : uint32_t {
   kLocScalar = 3,  // outputs only; where: scalar slot
 };
 // item: w | L << 5 | n_ops << 9 | first operand record << 16; output
-// location (kind | where << 2); first unit | units << 16; unused.  A unit is
-// 2^8 points of the union index: bits 0..5 on lanes, bits 6 and 7 in
-// registers.
+// location (kind | where << 2); first unit | units << 16; register bits.  A
+// unit is 2^(6 + register bits) points of the union index: bits 0..5 on lanes,
+// the next 0 to 2 in registers.
+constexpr int prog_reg_bits(int w, int L) {
+  // a register bit lets one load serve two points; a union of 8 bits or
+  // less has more waves than units, so it takes only the bits it has to sum
+  return w > 8 ? 2 : (L > 6 ? L - 6 : 0);
+}
 
 // Generic mapping: 2 register bits and 6 lane bits per wave unit.
 constexpr int kGenRegBits = 2;

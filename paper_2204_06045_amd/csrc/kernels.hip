@@ -30,6 +30,7 @@
 // batched complex matrix product of the sides' factors; it runs as three real
 // products on the matrix cores (3M), FP32 for complex64 and FP64 for
 // complex128 groups.
+#include <cmath>
 #include <cstddef>
 #include <map>
 #include <mutex>
@@ -44,6 +45,7 @@ namespace qtn {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kProgThreads = 1024;     // widest workgroup of a launch of programs
 constexpr int kStepOps = 4;  // step-class operands unrolled in the serial loop
 constexpr int kGenBatch = 3; // generic mapping: leaf operands loaded together
 
@@ -503,104 +505,180 @@ __device__ __forceinline__ void stream_unit(const GI &G, const DevOp *__restrict
 
 // -------------------------------------------------------------------- cells
 
-// Per-lane operand constants of the cell mapping: lane k holds operand k's
-// (k < n_ops <= 64).
-struct CellLane {
-  uint64_t base;    // address of the operand in angle set 0
-  uint64_t sstride; // bytes between angle sets
-  uint32_t es, dt;  // element bytes in the group's arithmetic, storage type
-  uint32_t cm;      // cell bits the operand's index holds
+// Per-lane constants of the cell mapping: lane k < n_ops holds operand k's,
+// lane n_ops the output's.
+template <int CB> struct CellLane {
+  uint64_t base;     // address in angle set 0
+  uint64_t sstride;  // bytes between angle sets
+  uint32_t es, dt;   // element bytes, storage type (read with CVT only)
+  uint32_t cm;       // cell bits the operand's index holds
+  uint32_t step[CB]; // operands: bytes from a cell bit's 0 to its 1; output: elements
 };
 
-// Block-wide setup.  LDS: the byte offsets of every operand, cell and lane
-// ([k][c][lane]: lane part plus cell part of the operand's index), then the
-// unit-bit runs of every operand ([k][kCellURuns / 2]).  Registers: the
-// lane's own operand constants.
-template <class T, bool CVT, int NC>
+// Block-wide setup.  LDS: every operand's byte offset of every lane
+// ([k][lane]), then the unit-bit runs of the operands and the output
+// ([k][kCellURuns / 2]).  Registers: the lane's own constants.
+template <class T, bool CVT, int CB>
 __device__ __forceinline__ void cell_setup(const GI &G, const DevOp *__restrict__ gops,
                                            const int32_t *__restrict__ ctab, char *data,
-                                           uint32_t *s_tab, CellLane &cl) {
-  for (int e = threadIdx.x; e < G.n_ops * NC * 64; e += blockDim.x) {
-    const int k = e / (NC * 64), c = (e / 64) % NC, lane = e & 63;
-    const DevOp &o = gops[k];
-    s_tab[e] = (pext_runs((uint32_t)lane, o) + (uint32_t)ctab[o.stab + c]) * esize<T, CVT>(op_dt(o));
+                                           uint32_t *s_tab, CellLane<CB> &cl) {
+  const int n_ops = G.n_ops, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int k = wave; k < n_ops; k += blockDim.x >> 6) {
+    // operand k is the same for the whole wave
+    const DevOp &o = gops[__builtin_amdgcn_readfirstlane(k)];
+    s_tab[k * 64 + lane] = pext_runs((uint32_t)lane, o) * esize<T, CVT>(op_dt(o));
   }
-  uint32_t *s_ur = s_tab + G.n_ops * NC * 64;
-  for (int e = threadIdx.x; e < G.n_ops * (kCellURuns / 2); e += blockDim.x) {
+  uint32_t *s_ur = s_tab + n_ops * 64;
+  for (int e = threadIdx.x; e < (n_ops + 1) * (kCellURuns / 2); e += blockDim.x) {
     const int k = e / (kCellURuns / 2), i = e % (kCellURuns / 2);
-    s_ur[e] = (uint32_t)ctab[gops[k].stab + NC + i];
+    s_ur[e] = (uint32_t)ctab[(k < n_ops ? gops[k].stab : G.gtab) + i];
   }
-  const int k = min((int)(threadIdx.x & 63), G.n_ops - 1);
-  const DevOp &o = gops[k];
-  cl.dt = (uint32_t)o.dt;
-  cl.es = esize<T, CVT>(cl.dt);
-  cl.base = (uint64_t)(data + o.off);
-  cl.sstride = (uint64_t)o.sstride;
-  cl.cm = (uint32_t)ctab[o.stab + NC + kCellURuns / 2];
+  const bool out = lane >= n_ops;
+  const DevOp &o = gops[out ? 0 : lane];
+  cl.dt = CVT && !out ? (uint32_t)o.dt : 0u;
+  cl.es = out ? (uint32_t)sizeof(T) : esize<T, CVT>(cl.dt);
+  cl.base = (uint64_t)(data + (out ? G.out_off : o.off));
+  cl.sstride = (uint64_t)(out ? G.out_sstride : o.sstride);
+  const int32_t *t = ctab + (out ? G.gtab : o.stab) + kCellURuns / 2;
+#pragma unroll
+  for (int j = 0; j < CB; j++) cl.step[j] = (uint32_t)t[j] * (out ? 1u : cl.es);
+  cl.cm = (uint32_t)t[CB];
 }
 
-// One reduce-scatter step over lane bit t: of the 2 * HALF accumulators the
-// lane keeps the half selected by its bit t, adding the partner lane's copy.
-template <class T, int HALF>
-__device__ __forceinline__ void reduce_scatter_step(T *acc, int lane, int t) {
-  const bool hi = ((lane >> t) & 1) != 0;
+// v of the lane whose index differs in bit t (any values in the others).
+template <int T> __device__ __forceinline__ uint32_t xor_word(uint32_t v) {
+  if (T == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+  if (T == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+  if (T == 2) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (4 << 10) | 0x1F);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // rotate by 8 of 16
+}
+template <int T> __device__ __forceinline__ double2 xor_lane(double2 v) {
+  return make_double2(__hiloint2double((int)xor_word<T>((uint32_t)__double2hiint(v.x)),
+                                       (int)xor_word<T>((uint32_t)__double2loint(v.x))),
+                      __hiloint2double((int)xor_word<T>((uint32_t)__double2hiint(v.y)),
+                                       (int)xor_word<T>((uint32_t)__double2loint(v.y))));
+}
+template <int T> __device__ __forceinline__ float2 xor_lane(float2 v) {
+  return make_float2(__uint_as_float(xor_word<T>(__float_as_uint(v.x))),
+                     __uint_as_float(xor_word<T>(__float_as_uint(v.y))));
+}
+// v + v of the lane whose index differs in bit T (any values in the others).
+template <int T> __device__ __forceinline__ float xor_sum(float v) {
+  const uint32_t a = __float_as_uint(v);
+  if (T < 4) return v + __uint_as_float(xor_word<T>(a));
+  if (T == 4) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int T> __device__ __forceinline__ double xor_sum(double v) {
+  const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+  if (T < 4) return v + __hiloint2double((int)xor_word<T>(hi), (int)xor_word<T>(lo));
+  if (T == 4) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+// One reduce-scatter step over lane bit T: of the 2 * HALF accumulators the
+// lane keeps the half selected by its bit T, adding the partner lane's copy.
+template <class T, int HALF, int BIT>
+__device__ __forceinline__ void reduce_scatter_step(T *acc, int lane) {
+  const bool hi = ((lane >> BIT) & 1) != 0;
 #pragma unroll
   for (int i = 0; i < HALF; i++) {
     const T keep = hi ? acc[i + HALF] : acc[i];
     const T send = hi ? acc[i] : acc[i + HALF];
-    acc[i] = cadd(keep, shfl_xor2(send, 1 << t));
+    acc[i] = cadd(keep, xor_lane<BIT>(send));
   }
+}
+template <class T, int N, int BIT>
+__device__ __forceinline__ void butterfly_step(T *acc, int nacc) {
+#pragma unroll
+  for (int i = 0; i < N; i++)
+    if (i < nacc) {
+      acc[i].x = xor_sum<BIT>(acc[i].x);
+      acc[i].y = xor_sum<BIT>(acc[i].y);
+    }
+}
+
+// Element offset, in the output, of a lane after cell_finish: its kept lane
+// bits and the register cell its reduce-scatter bits select.
+template <int CB, int RB>
+__device__ __forceinline__ uint32_t cell_out_lane(const CellLane<CB> &cl, int n_ops, int L, int ls,
+                                                  int lane) {
+  uint32_t o = L < 6 ? (uint32_t)lane >> L : 0u;
+  const int q = min(RB, ls);
+#pragma unroll
+  for (int t = 0; t < RB; t++)
+    if (t < q) {
+      // lane bit t selects the upper half: register bit RB - 1 - t
+      const uint32_t s = __builtin_amdgcn_readlane(cl.step[RB - 1 - t], n_ops);
+      o += ((lane >> t) & 1) ? s : 0u;
+    }
+  return o;
 }
 
 // Sums the lane-summed bits 0..ls-1 of the 2^RB register accumulators and
-// writes the results: a reduce-scatter over the first q = min(RB, ls) bits
-// (afterwards lane bit t selects half of the cells), butterflies for the rest.
-template <class T, int RB>
-__device__ __forceinline__ void cell_finish(const GI &G, T *acc, const uint8_t *__restrict__ ubit,
-                                            uint32_t Iu, int ls, int lane, T *out) {
+// writes the results at out + out_lane: a reduce-scatter over the first
+// q = min(RB, ls) bits (afterwards lane bit t selects half of the cells),
+// butterflies for the rest.
+template <class T, int CB, int RB>
+__device__ __forceinline__ void cell_finish(T *acc, const CellLane<CB> &cl, int n_ops, int ls,
+                                            int lane, char *out, uint32_t out_lane) {
   constexpr int NR = 1 << RB;
-  const int L = G.L, q = min(RB, ls);
-  if (RB >= 1 && ls > 0) reduce_scatter_step<T, (NR >> 1)>(acc, lane, 0);
-  if (RB >= 2 && ls > 1) reduce_scatter_step<T, (NR >> 2)>(acc, lane, 1);
-  if (RB >= 3 && ls > 2) reduce_scatter_step<T, (NR >> 3)>(acc, lane, 2);
-  if (RB >= 4 && ls > 3) reduce_scatter_step<T, (NR >> 4)>(acc, lane, 3);
+  const int q = min(RB, ls);
+  if (RB >= 1 && ls > 0) reduce_scatter_step<T, (NR >> 1), 0>(acc, lane);
+  if (RB >= 2 && ls > 1) reduce_scatter_step<T, (NR >> 2), 1>(acc, lane);
+  if (RB >= 3 && ls > 2) reduce_scatter_step<T, (NR >> 3), 2>(acc, lane);
+  if (RB >= 4 && ls > 3) reduce_scatter_step<T, (NR >> 4), 3>(acc, lane);
   const int nacc = NR >> q;
-  for (int t = q; t < ls; t++) {
-#pragma unroll
-    for (int i = 0; i < NR; i++)
-      if (i < nacc) acc[i] = cadd(acc[i], shfl_xor2(acc[i], 1 << t));
-  }
+  if (RB <= 0 && ls > 0) butterfly_step<T, NR, 0>(acc, nacc);
+  if (RB <= 1 && ls > 1) butterfly_step<T, (RB >= 1 ? NR / 2 : NR), 1>(acc, nacc);
+  if (RB <= 2 && ls > 2) butterfly_step<T, (RB >= 2 ? NR / 4 : 1), 2>(acc, nacc);
+  if (RB <= 3 && ls > 3) butterfly_step<T, 1, 3>(acc, nacc);
+  if (ls > 4) butterfly_step<T, 1, 4>(acc, nacc);
+  if (ls > 5) butterfly_step<T, 1, 5>(acc, nacc);
   // lanes whose summed bits q..ls-1 are zero hold the results; acc[i] is
-  // register cell i + sum_t (lane bit t) * (NR >> (t + 1))
+  // register cell i plus the cells out_lane counts
   if ((((uint32_t)lane >> q) & ((1u << (ls - q)) - 1u)) == 0) {
-    const uint32_t Ik = Iu | ((uint32_t)lane & ~((1u << ls) - 1u));
-    uint32_t jb = 0;
-    for (int t = 0; t < q; t++) jb += (((uint32_t)lane >> t) & 1u) * (uint32_t)(NR >> (t + 1));
-    const uint32_t nout = 1u << (G.w - L);
 #pragma unroll
     for (int i = 0; i < NR; i++) {
       if (i < nacc) {
-        const uint32_t j = jb + (uint32_t)i;
-        uint32_t I = Ik;
+        uint64_t o = 0;
 #pragma unroll
-        for (int b = 0; b < RB; b++) I |= ((j >> b) & 1u) << ubit_at(ubit, b);
-        const uint32_t o = I >> L;
-        if (o < nout) out[o] = acc[i];
+        for (int b = 0; b < RB; b++)
+          if ((i >> b) & 1) o += (uint64_t)(uint32_t)__builtin_amdgcn_readlane(cl.step[b], n_ops);
+        ((T *)(out + o * sizeof(T)))[out_lane] = acc[i];
       }
     }
   }
 }
 
-// acc[c] (c < N; first: set to) times operand k, whose index holds the cell
-// bits CM: only the distinct cells (c & ~CM == 0) are loaded, each value
-// serving every cell that differs from it in bits outside CM.
-template <class T, bool CVT, int NC, int N, int CM>
-__device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, int dt,
-                                           const uint32_t *lt) {
+// acc[c] (c < N; first: set to) times an operand whose index holds the cell
+// bits CM (scalar address p, lane offset lt, cell steps st): only the
+// distinct cells (c & ~CM == 0) are loaded, each value serving every cell
+// that differs from it in bits outside CM.  A cell's offset is uniform, so it
+// goes into the scalar address.  OTHER: stored in the other precision.
+template <class T, bool OTHER, int N, int CM>
+__device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, uint32_t lt,
+                                           const uint32_t *st) {
   T v[N];
 #pragma unroll
   for (int c = 0; c < N; c++)
-    if ((c & ~CM) == 0) v[c] = gload_dt<T, CVT>(p, lt[c * 64], dt);
+    if ((c & ~CM) == 0) {
+      uint64_t o = 0;
+#pragma unroll
+      for (int b = 0; b < 4; b++)
+        if ((c >> b) & 1) o += st[b];
+      v[c] = OTHER ? gload_dt<T, true>(p + o, lt, sizeof(T) == 16 ? 1 : 0) : gload<T>(p + o, lt);
+    }
   if (first) {
 #pragma unroll
     for (int c = 0; c < N; c++) acc[c] = v[c & CM];
@@ -610,24 +688,35 @@ __device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, in
   }
 }
 
-// acc[c] (c < N) times operand k (uniform): scalar base from lane k's
-// address, per-lane offsets of each cell from the LDS table.
-template <class T, bool CVT, int NC, int N>
-__device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLane &cl,
-                                        uint64_t addr, const uint32_t *s_tab, int lane) {
+// acc[c] (c < N) times operand k (uniform) at the addresses of lane k.
+template <class T, bool CVT, int CB, int N>
+__device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLane<CB> &cl,
+                                        uint64_t addr, uint32_t lt) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)addr, k);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(addr >> 32), k);
   const char *p = (const char *)(((uint64_t)hi << 32) | lo);
   const int dt = CVT ? (int)__builtin_amdgcn_readlane(cl.dt, k) : 0;
   const uint32_t cm = __builtin_amdgcn_readlane(cl.cm, k) & (uint32_t)(N - 1);
-  const uint32_t *lt = s_tab + k * NC * 64 + lane;
-#define QTN_CM(m) \
-  case m: cell_op_cm<T, CVT, NC, N, (m) & (N - 1)>(acc, first, p, dt, lt); break;
-  switch (cm) {
-    QTN_CM(0) QTN_CM(1) QTN_CM(2) QTN_CM(3) QTN_CM(4) QTN_CM(5) QTN_CM(6) QTN_CM(7)
-    QTN_CM(8) QTN_CM(9) QTN_CM(10) QTN_CM(11) QTN_CM(12) QTN_CM(13) QTN_CM(14)
-    default: cell_op_cm<T, CVT, NC, N, (15 & (N - 1))>(acc, first, p, dt, lt); break;
+  uint32_t st[4] = {};
+#pragma unroll
+  for (int b = 0; b < CB; b++)
+    if ((1 << b) < N) st[b] = __builtin_amdgcn_readlane(cl.step[b], k);
+#define QTN_CM(O, m) \
+  case m: cell_op_cm<T, O, N, (m) & (N - 1)>(acc, first, p, lt, st); break;
+#define QTN_CMS(O)                                                                                \
+  switch (cm) {                                                                                   \
+    QTN_CM(O, 0) QTN_CM(O, 1) QTN_CM(O, 2) QTN_CM(O, 3) QTN_CM(O, 4) QTN_CM(O, 5) QTN_CM(O, 6)    \
+    QTN_CM(O, 7) QTN_CM(O, 8) QTN_CM(O, 9) QTN_CM(O, 10) QTN_CM(O, 11) QTN_CM(O, 12)              \
+    QTN_CM(O, 13) QTN_CM(O, 14)                                                                   \
+    default: cell_op_cm<T, O, N, (15 & (N - 1))>(acc, first, p, lt, st); break;                   \
   }
+  // one branch per operand on its storage, so that its loads stay together
+  if (CVT && dt != (sizeof(T) == 16 ? 0 : 1)) {
+    QTN_CMS(CVT)
+  } else {
+    QTN_CMS(false)
+  }
+#undef QTN_CMS
 #undef QTN_CM
 }
 
@@ -639,34 +728,44 @@ __device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLan
 // operands, as bucket elimination orders them: the operands holding bit 6
 // in every cell, then bit 6 is summed, the operands holding bit 7 (but not
 // 6) in the cells left, bit 7 is summed, and the other operands multiply the
-// 2^RB register cells.  The lane-summed bits are reduced last.  Operand
-// addresses for the unit are formed by lane k for operand k.
+// 2^RB register cells.  The lane-summed bits are reduced last.  Addresses for
+// the unit are formed by lane k for operand k, and by lane n_ops for the
+// output.  A unit is a chain of one load round trip per operand, and what a
+// wave does between them is exposed: so the lane offset of the next operand
+// is read while this one's loads are under way, the cells' offsets are scalar
+// steps, and no descriptor is read from memory.
 template <class T, bool CVT, int CB, int SL>
-__device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl,
-                                          const uint8_t *__restrict__ ubit, char *__restrict__ data,
+__device__ __forceinline__ void cell_unit(const GI &G, const CellLane<CB> &cl, uint64_t set_base,
                                           const uint32_t *s_tab, const T *P, uint32_t u, int lane,
-                                          uint32_t set) {
+                                          int ls, uint32_t out_lane) {
   constexpr int NC = 1 << CB, RB = CB - SL, NR = 1 << RB;
   const int n_step = G.n_step, n_ops = G.n_ops, nfix = G.n_step0;
-  // lane k: unit part of operand k's index, then its address for this unit
-  const uint32_t *s_ur = s_tab + n_ops * NC * 64 + min(lane, n_ops - 1) * (kCellURuns / 2);
+  const uint32_t *s_lane = s_tab + lane;
+  // lane k: unit part of tensor k's index, then its address for this unit
+  const uint32_t *s_ur = s_tab + n_ops * 64 + min(lane, n_ops) * (kCellURuns / 2);
   uint32_t ub = 0;
-  for (int i = 0; i < G.n_unit; i += 2) {
-    const uint32_t w = s_ur[i >> 1];
+  for (int i = 0; i < G.n_unit; i += 4) {
+    const uint2 w2 = *(const uint2 *)(s_ur + (i >> 1));
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
-      const uint32_t rr = (w >> (16 * h)) & 0xFFFFu;  // an unused run is 0
+    for (int h = 0; h < 4; h++) {
+      const uint32_t rr = ((h < 2 ? w2.x : w2.y) >> (16 * (h & 1))) & 0xFFFFu;  // an unused run is 0
       const uint32_t src = rr & 31u, len = (rr >> 5) & 63u, dst = rr >> 11;
       ub |= ((u >> src) & (uint32_t)((1ull << len) - 1ull)) << dst;
     }
   }
-  const uint64_t addr = cl.base + (uint64_t)set * cl.sstride + (uint64_t)ub * cl.es;
+  const uint64_t addr = set_base + (uint64_t)ub * cl.es;
   T acc[NC];
   // operands holding bit 6 (every operand when no bit is serial) in all
   // cells; without serial bits, the first nfix (lane bits only) are the
   // product P[0] applied last
   int k = SL == 0 ? nfix : 0;
-  for (const int k0 = k; k < n_step; k++) cell_op<T, CVT, NC, NC>(acc, k == k0, k, cl, addr, s_tab, lane);
+  uint32_t lt = s_lane[min(k, n_ops - 1) * 64];
+  auto next = [&](int q) { return s_lane[min(q, n_ops - 1) * 64]; };
+  for (const int k0 = k; k < n_step; k++) {
+    const uint32_t l0 = lt;
+    lt = next(k + 1);
+    cell_op<T, CVT, CB, NC>(acc, k == k0, k, cl, addr, l0);
+  }
   if (SL == 0 && nfix > 0) {
     if (nfix == n_step) {
 #pragma unroll
@@ -684,8 +783,11 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl,
   if (SL == 2) {
     // operands holding bit 7 but not 6, then sum bit 7
     const int k1 = n_step + G.n_serial;
-    for (k = n_step; k < k1; k++)
-      cell_op<T, CVT, NC, (SL == 2 ? NC / 2 : 1)>(acc, false, k, cl, addr, s_tab, lane);
+    for (k = n_step; k < k1; k++) {
+      const uint32_t l0 = lt;
+      lt = next(k + 1);
+      cell_op<T, CVT, CB, (SL == 2 ? NC / 2 : 1)>(acc, false, k, cl, addr, l0);
+    }
 #pragma unroll
     for (int c = 0; c < NC / 4; c++) acc[c] = cadd(acc[c], acc[c + NC / 4]);
   }
@@ -693,15 +795,21 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl,
     // the operands without serial bits in the register cells: first the
     // unit-invariant product, then the others
     k = n_step + (SL == 2 ? G.n_serial : 0);
-    if (SL >= 1 && nfix > 0) {
+    if (nfix > 0) {
 #pragma unroll
       for (int c = 0; c < NR; c++) acc[c] = cmul(acc[c], P[c]);
       k += nfix;
+      lt = next(k);
     }
-    for (; k < n_ops; k++) cell_op<T, CVT, NC, NR>(acc, false, k, cl, addr, s_tab, lane);
+    for (; k < n_ops; k++) {
+      const uint32_t l0 = lt;
+      lt = next(k + 1);
+      cell_op<T, CVT, CB, NR>(acc, false, k, cl, addr, l0);
+    }
   }
-  const uint32_t Iu = unit_bits(u, ubit, G.n_ubits, RB);
-  cell_finish<T, RB>(G, acc, ubit, Iu, SL > 0 ? 6 : min(G.L, 6), lane, (T *)outp(data, G, set));
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)addr, n_ops);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(addr >> 32), n_ops);
+  cell_finish<T, CB, RB>(acc, cl, n_ops, ls, lane, (char *)(((uint64_t)hi << 32) | lo), out_lane);
 }
 
 // Setup and units [u0, u1) (one per wave, strided) of a cell-mapped group.
@@ -712,28 +820,30 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl,
 // when its set changes.
 template <class T, bool CVT, int CB, int SL>
 __device__ __forceinline__ void cell_units(const GI &G, const DevOp *__restrict__ gops,
-                                           const int32_t *__restrict__ ctab,
-                                           const uint8_t *__restrict__ ubit, char *__restrict__ data,
+                                           const int32_t *__restrict__ ctab, char *__restrict__ data,
                                            uint32_t *s_tab, uint32_t u0, uint32_t u1,
                                            uint32_t stride, uint32_t set_units, int lane) {
-  constexpr int NC = 1 << CB, NR = 1 << (CB - SL);
-  CellLane cl;
-  cell_setup<T, CVT, NC>(G, gops, ctab, data, s_tab, cl);
+  constexpr int NR = 1 << (CB - SL);
+  CellLane<CB> cl;
+  cell_setup<T, CVT, CB>(G, gops, ctab, data, s_tab, cl);
   __syncthreads();
   const int nfix = G.n_step0;
   const int kf = SL == 0 ? 0 : G.n_step + (SL == 2 ? G.n_serial : 0);
+  const int ls = SL > 0 ? 6 : min(G.L, 6);
+  const uint32_t out_lane = cell_out_lane<CB, CB - SL>(cl, G.n_ops, G.L, ls, lane);
   T P[SL > 0 ? NR : 1];
   uint32_t pset = 0xFFFFFFFFu;
+  uint64_t set_base = 0;
   // flat unit f: angle set f / set_units, unit f % set_units
   for (uint32_t f = u0; f < u1; f += stride) {
     const uint32_t set = f / set_units;
-    if (nfix > 0 && set != pset) {
-      const uint64_t a0 = cl.base + (uint64_t)set * cl.sstride;  // no unit part
+    if (set != pset) {
+      set_base = cl.base + (uint64_t)set * cl.sstride;  // no unit part
       for (int k = kf; k < kf + nfix; k++)
-        cell_op<T, CVT, NC, (SL > 0 ? NR : 1)>(P, k == kf, k, cl, a0, s_tab, lane);
+        cell_op<T, CVT, CB, (SL > 0 ? NR : 1)>(P, k == kf, k, cl, set_base, s_tab[k * 64 + lane]);
       pset = set;
     }
-    cell_unit<T, CVT, CB, SL>(G, cl, ubit, data, s_tab, P, f - set * set_units, lane, set);
+    cell_unit<T, CVT, CB, SL>(G, cl, set_base, s_tab, P, f - set * set_units, lane, ls, out_lane);
   }
 }
 
@@ -975,12 +1085,9 @@ struct ProgBase {
   char *lds;  // the workgroup's LDS
 };
 
-// The values of one operand (record words r0..r3, wave-uniform) at the
-// points I0 + 64 c, c < NC.
-template <class T, int NC>
-__device__ __forceinline__ void prog_load(const ProgBase &B, uint32_t r0, uint32_t r1, uint32_t r2,
-                                          uint32_t r3, uint32_t I0, T *v) {
-  // compress of the mask's bits, four moves
+// Index of an operand's element for union bits I0: compress of its mask's
+// bits in four moves (record words 1..3, wave-uniform).
+__device__ __forceinline__ uint32_t prog_index(uint32_t r1, uint32_t r2, uint32_t r3, uint32_t I0) {
   uint32_t x = I0 & r3, t;
   t = x & (r1 & 0xFFFFu);
   x = (x ^ t) | (t >> 1);
@@ -989,74 +1096,79 @@ __device__ __forceinline__ void prog_load(const ProgBase &B, uint32_t r0, uint32
   t = x & (r2 & 0xFFFFu);
   x = (x ^ t) | (t >> 4);
   t = x & (r2 >> 16);
-  x = (x ^ t) | (t >> 8);
-  // element steps of bits 6 and 7
-  const uint32_t lane_part = (uint32_t)__builtin_popcount(r3 & 63u), b6 = (r3 >> 6) & 1u;
-  const uint32_t s6 = b6 << lane_part, s7 = ((r3 >> 7) & 1u) << (lane_part + b6);
-  const uint32_t where = r0 >> 2;
-  auto spread = [&](auto load) {
-    v[0] = load(0u);
-    if (NC >= 2) v[1] = s6 ? load(s6) : v[0];
-    if (NC >= 4) {
-      if (s7) {
-        v[2] = load(s7);
-        v[3] = s6 ? load(s6 + s7) : v[2];
-      } else {
-        v[2] = v[0];
-        v[3] = v[1];
-      }
-    }
-  };
-  if ((r0 & 3u) == kLocLds) {
-    const char *p = B.lds + where + x * (uint32_t)sizeof(T);
-    spread([&](uint32_t d) { return *(const T *)(p + d * (uint32_t)sizeof(T)); });
+  return (x ^ t) | (t >> 8);
+}
+
+// acc[c] (c < NC; first: set to) times an operand at index x + (steps of the
+// cell bits in c): only the distinct cells are loaded (CM: cell bits held).
+template <int NC, int CM, class LD>
+__device__ __forceinline__ void prog_mul(double2 *acc, bool first, uint32_t s6, uint32_t s7, LD load) {
+  double2 v[NC];
+#pragma unroll
+  for (int c = 0; c < NC; c++)
+    if ((c & ~CM) == 0) v[c] = to_d(load(((c & 1) ? s6 : 0u) + ((c & 2) ? s7 : 0u)));
+  if (first) {
+#pragma unroll
+    for (int c = 0; c < NC; c++) acc[c] = v[c & CM];
   } else {
-    const char *p = B.arena + (uint64_t)where * 256u;
-    if ((r0 & 3u) == kLocArena) {
-      spread([&](uint32_t d) { return gload<T>(p, (x + d) * (uint32_t)sizeof(T)); });
-    } else if (sizeof(T) == 16) {
-      spread([&](uint32_t d) {
-        const float2 f = gload<float2>(p, (x + d) * 8u);
-        return make_c<T>(f.x, f.y);
-      });
-    } else {
-      spread([&](uint32_t d) {
-        const double2 f = gload<double2>(p, (x + d) * 16u);
-        return make_c<T>(f.x, f.y);
-      });
-    }
+#pragma unroll
+    for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], v[c & CM]);
   }
+}
+template <int NC, class LD>
+__device__ __forceinline__ void prog_mul_cm(double2 *acc, bool first, uint32_t s6, uint32_t s7, LD load) {
+  if (NC >= 4 && s6 && s7)
+    prog_mul<NC, (3 & (NC - 1))>(acc, first, s6, s7, load);
+  else if (NC >= 4 && s7)
+    prog_mul<NC, (2 & (NC - 1))>(acc, first, s6, s7, load);
+  else if (NC >= 2 && s6)
+    prog_mul<NC, (1 & (NC - 1))>(acc, first, s6, s7, load);
+  else
+    prog_mul<NC, 0>(acc, first, s6, s7, load);
 }
 
 // Units [u0, u0 + nu) of one group: every point multiplies all operands (a
 // level-l operand does not depend on the l bits summed before it, so the sum
 // is the same), then the summed bits are added over registers and lanes.
+// Complex64 groups compute in FP64 too, which issues at the same rate, and
+// round once, to store: the product of all operands at every point takes more
+// roundings than summing between them does.  A unit is 64 * NC points: bits 0..5 on lanes, the next log2(NC) in registers.
 template <class T, int NC>
 __device__ __forceinline__ void prog_units(const ProgBase &B, const uint4 *ops, uint32_t head,
-                                           uint32_t out, uint32_t u0, uint32_t nu, uint32_t set_lane) {
+                                           uint32_t out, uint32_t u0, uint32_t nu, uint32_t lane) {
+  constexpr int CB = NC == 4 ? 2 : (NC == 2 ? 1 : 0);
   const int w = head & 31, L = (head >> 5) & 15, n_ops = (head >> 9) & 127;
-  const uint32_t lane = set_lane;
   const uint4 rec = ops[min((int)lane, n_ops - 1)];
   for (uint32_t u = u0; u < u0 + nu; u++) {
-    const uint32_t I0 = lane | (u << 8);
-    T acc[NC], v[NC];
-    // two operands at a time: the second one's loads are under way while the
-    // first is multiplied in
-    for (int k = 0; k < n_ops; k += 2) {
-      T v2[NC];
-      const int k2 = min(k + 1, n_ops - 1);
-      prog_load<T, NC>(B, __builtin_amdgcn_readlane(rec.x, k), __builtin_amdgcn_readlane(rec.y, k),
-                       __builtin_amdgcn_readlane(rec.z, k), __builtin_amdgcn_readlane(rec.w, k), I0,
-                       v);
-      if (k + 1 < n_ops)
-        prog_load<T, NC>(B, __builtin_amdgcn_readlane(rec.x, k2),
-                         __builtin_amdgcn_readlane(rec.y, k2), __builtin_amdgcn_readlane(rec.z, k2),
-                         __builtin_amdgcn_readlane(rec.w, k2), I0, v2);
-#pragma unroll
-      for (int c = 0; c < NC; c++) acc[c] = k == 0 ? v[c] : cmul(acc[c], v[c]);
-      if (k + 1 < n_ops) {
-#pragma unroll
-        for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], v2[c]);
+    const uint32_t I0 = lane | (u << (6 + CB));
+    double2 acc[NC];
+    for (int k = 0; k < n_ops; k++) {
+      const uint32_t r0 = __builtin_amdgcn_readlane(rec.x, k), r1 = __builtin_amdgcn_readlane(rec.y, k);
+      const uint32_t r2 = __builtin_amdgcn_readlane(rec.z, k), r3 = __builtin_amdgcn_readlane(rec.w, k);
+      const uint32_t x = prog_index(r1, r2, r3, I0);
+      // element steps of the register bits
+      const uint32_t low = (uint32_t)__builtin_popcount(r3 & 63u), b6 = (r3 >> 6) & 1u;
+      const uint32_t s6 = b6 << low, s7 = ((r3 >> 7) & 1u) << (low + b6);
+      const uint32_t where = r0 >> 2;
+      if ((r0 & 3u) == kLocLds) {
+        const char *p = B.lds + where + x * (uint32_t)sizeof(T);
+        prog_mul_cm<NC>(acc, k == 0, s6, s7,
+                           [&](uint32_t d) { return *(const T *)(p + d * (uint32_t)sizeof(T)); });
+      } else {
+        const char *p = B.arena + (uint64_t)where * 256u;
+        if ((r0 & 3u) == kLocArena) {
+          prog_mul_cm<NC>(acc, k == 0, s6, s7, [&](uint32_t d) {
+            return gload<T>(p + (uint64_t)d * sizeof(T), x * (uint32_t)sizeof(T));
+          });
+        } else if (sizeof(T) == 16) {
+          prog_mul_cm<NC>(acc, k == 0, s6, s7, [&](uint32_t d) {
+            return gload<float2>(p + (uint64_t)d * 8u, x * 8u);
+          });
+        } else {
+          prog_mul_cm<NC>(acc, k == 0, s6, s7, [&](uint32_t d) {
+            return gload<double2>(p + (uint64_t)d * 16u, x * 16u);
+          });
+        }
       }
     }
     int nc = NC;  // cells left: bit 6, then bit 7 summed
@@ -1082,7 +1194,7 @@ __device__ __forceinline__ void prog_units(const ProgBase &B, const uint4 *ops, 
       const int cs = L >= 7 ? 7 : 6;
 #pragma unroll
       for (int c = 0; c < NC; c++)
-        if (c < nc) *(T *)(p + (uint64_t)((I0 | ((uint32_t)c << cs)) >> L) * sizeof(T)) = acc[c];
+        if (c < nc) *(T *)(p + (uint64_t)((I0 | ((uint32_t)c << cs)) >> L) * sizeof(T)) = make_c<T>(acc[c].x, acc[c].y);
     }
   }
 }
@@ -1133,10 +1245,10 @@ __device__ __forceinline__ void run_program_t(const uint32_t *__restrict__ prog,
         const uint32_t out = __builtin_amdgcn_readfirstlane(it.y);
         const uint32_t un = __builtin_amdgcn_readfirstlane(it.z);
         const uint4 *gops = ops + (head >> 16);
-        const uint32_t w = head & 31u;
-        if (w <= 6)
+        const uint32_t cb = it.w;
+        if (__builtin_amdgcn_readfirstlane(cb) == 0u)
           prog_units<T, 1>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
-        else if (w == 7)
+        else if (__builtin_amdgcn_readfirstlane(cb) == 1u)
           prog_units<T, 2>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
         else
           prog_units<T, 4>(B, gops, head, out, un & 0xFFFFu, un >> 16, lane);
@@ -1238,7 +1350,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_block_groups(char *__restrict__ d
 // Segments that are all programs of one precision: without the other
 // mappings' code the kernel needs few registers and nothing spills.
 template <class T>
-__global__ __launch_bounds__(kBlock) void k_programs(char *__restrict__ data,
+__global__ __launch_bounds__(kProgThreads) void k_programs(char *__restrict__ data,
                                                      const uint32_t *__restrict__ prog,
                                                      const int4 *__restrict__ ranges,
                                                      int range_base, int n_ranges) {
@@ -1259,9 +1371,9 @@ __global__ __launch_bounds__(kBlock) void k_programs(char *__restrict__ data,
 struct UnitWalk {
   uint32_t first, end, stride;
 };
-__device__ __forceinline__ UnitWalk wide_walk(uint32_t n_units, uint32_t nw, uint32_t w) {
-  const uint32_t nb = gridDim.x, b = blockIdx.x;
-  const bool xcd = nb % 8u == 0u;
+__device__ __forceinline__ UnitWalk wide_walk(uint32_t n_units, uint32_t nw, uint32_t w, uint32_t nb,
+                                              uint32_t b, bool aligned = true) {
+  const bool xcd = aligned && nb % 8u == 0u;
   const uint32_t nx = xcd ? 8u : 1u, x = xcd ? b % 8u : 0u, j = xcd ? b / 8u : b;
   const uint32_t per = (n_units + nx - 1) / nx;
   UnitWalk W;
@@ -1285,7 +1397,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
   const int lane = threadIdx.x & 63;
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0);
+  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0, gridDim.x, blockIdx.x);
   stream_setup(G, gops, s_lane);
   __syncthreads();
   // flat unit f: angle set f / n_units, unit f % n_units
@@ -1296,11 +1408,14 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
   }
 }
 
-// With 3 cell bits and 2 serial bits the kernel fits 5 waves per SIMD without
-// spilling when asked to (92 registers; 4 waves otherwise): 7% faster on the
-// 8-summed-bit groups.  The other forms would spill, for no measured gain.
+// Waves per SIMD asked for: with 3 cell bits and 2 serial bits the kernel
+// fits 5 without spilling (94 registers), 7% faster on the 8-summed-bit groups
+// than the 4 it takes otherwise; the other 3-cell-bit forms fit 4.
+constexpr int cell_waves(int cb, int sl, bool cvt) {
+  return cb == 3 ? (sl == 2 && !cvt ? 5 : 4) : 1;
+}
 template <class T, bool CVT, int CB, int SL>
-__global__ __launch_bounds__(kBlock, (CB == 3 && SL == 2 ? 5 : 1)) void k_wide_cells(char *__restrict__ data,
+__global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT))) void k_wide_cells(char *__restrict__ data,
                                                        const DevGroup *__restrict__ groups,
                                                        const DevOp *__restrict__ ops,
                                                        const int32_t *__restrict__ ctab,
@@ -1311,9 +1426,9 @@ __global__ __launch_bounds__(kBlock, (CB == 3 && SL == 2 ? 5 : 1)) void k_wide_c
   const GI G = load_group(groups + gid);
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0);
-  cell_units<T, CVT, CB, SL>(G, ops + G.op_begin, ctab, uperm + 32 * gid, data, s_tab, W.first,
-                             W.end, W.stride, G.n_units, threadIdx.x & 63);
+  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0, gridDim.x, blockIdx.x);
+  cell_units<T, CVT, CB, SL>(G, ops + G.op_begin, ctab, data, s_tab, W.first, W.end, W.stride,
+                             G.n_units, threadIdx.x & 63);
 }
 
 template <class T, bool CVT>
@@ -1328,11 +1443,89 @@ __global__ __launch_bounds__(kBlock) void k_wide_generic(char *__restrict__ data
   const int lane = threadIdx.x & 63;
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0);
+  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0, gridDim.x, blockIdx.x);
   for (uint32_t f = W.first; f < W.end; f += W.stride) {
     const uint32_t set = f / G.n_units;
     generic_unit<T, CVT>(G, gops, uperm + 32 * gid, data, f - set * G.n_units, lane, set);
   }
+}
+
+// One step of every light cone in one launch.  A light cone's wide groups and
+// segments form a chain, and launched one by one most of them leave the chip
+// idle: a group of 2^17 points is 64 workgroups for a few microseconds, and a
+// 40-vertex quartic graph has 1,400 of them an evaluation.  Here the j-th
+// task of every cone runs in one launch: workgroups [tasks[t].y, +
+// tasks[t].z) take task t, a cell-mapped group (x >= 0, over all angle sets)
+// or a segment program (x < 0, program word w, one workgroup per set).
+// Compiled for 4 waves per SIMD, what the widest of the mappings needs.
+__device__ __forceinline__ int find_task(const int4 *__restrict__ tasks, int n, int b) {
+  // last t with tasks[t].y <= b: every 64th entry, then the 64 between
+  const int lane = threadIdx.x & 63;
+  int lo = 0;
+  for (int base = 0; base < n; base += 4096) {
+    const int i = base + lane * 64;
+    const int c = __popcll(__ballot(i < n && tasks[i < n ? i : 0].y <= b));
+    if (c == 0) break;
+    lo = base + (c - 1) * 64;
+    if (c < 64) break;
+  }
+  const int i = lo + lane;
+  return lo + __popcll(__ballot(i < n && tasks[i < n ? i : 0].y <= b)) - 1;
+}
+
+template <class T, bool CVT>
+__device__ __forceinline__ void step_cells(const GI &G, const DevOp *__restrict__ ops,
+                                           const int32_t *__restrict__ ctab, char *__restrict__ data,
+                                           uint32_t *s_tab, const UnitWalk &W) {
+  const DevOp *gops = ops + G.op_begin;
+  const int lane = threadIdx.x & 63;
+  if (G.sl == 0)
+    cell_units<T, CVT, kCellRuleCB, 0>(G, gops, ctab, data, s_tab, W.first, W.end, W.stride,
+                                       G.n_units, lane);
+  else if (G.sl == 1)
+    cell_units<T, CVT, kCellRuleCB, 1>(G, gops, ctab, data, s_tab, W.first, W.end, W.stride,
+                                       G.n_units, lane);
+  else
+    cell_units<T, CVT, kCellRuleCB, 2>(G, gops, ctab, data, s_tab, W.first, W.end, W.stride,
+                                       G.n_units, lane);
+}
+
+// P: arithmetic of the schedule (kPrecMixed: per group, operands converted)
+template <int P>
+__global__ __launch_bounds__(kStepMaxThreads, 4) void k_step(char *__restrict__ data,
+                                                    const DevGroup *__restrict__ groups,
+                                                    const DevOp *__restrict__ ops,
+                                                    const int32_t *__restrict__ ctab,
+                                                    const uint8_t *__restrict__ uperm,
+                                                    const uint32_t *__restrict__ prog,
+                                                    const int4 *__restrict__ tasks, int n_tasks,
+                                                    uint32_t n_sets) {
+  extern __shared__ __align__(16) uint32_t s_tab[];
+  const int t = __builtin_amdgcn_readfirstlane(find_task(tasks, n_tasks, (int)blockIdx.x));
+  const int4 tk = tasks[t];
+  const uint32_t b = blockIdx.x - (uint32_t)tk.y;
+  if (b >= (uint32_t)tk.z) return;  // between tasks, for alignment
+  if (tk.x < 0) {
+    if (P == kPrecC64)
+      run_program_t<float2>(prog + tk.w, data, (char *)s_tab, b);
+    else if (P == kPrecC128 || prog[tk.w + kPgPrec] == 0u)
+      run_program_t<double2>(prog + tk.w, data, (char *)s_tab, b);
+    else
+      run_program_t<float2>(prog + tk.w, data, (char *)s_tab, b);
+    return;
+  }
+  const GI G = load_group(groups + tk.x);
+  const uint32_t nw = blockDim.x >> 6;
+  const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0, (uint32_t)tk.z, b, tk.y % 8 == 0);
+  if (P == kPrecC128)
+    step_cells<double2, false>(G, ops, ctab, data, s_tab, W);
+  else if (P == kPrecC64)
+    step_cells<float2, false>(G, ops, ctab, data, s_tab, W);
+  else if (G.prec == 0)
+    step_cells<double2, true>(G, ops, ctab, data, s_tab, W);
+  else
+    step_cells<float2, true>(G, ops, ctab, data, s_tab, W);
 }
 
 // Waves per SIMD the matrix-form kernel is compiled for: three accumulator
@@ -1351,7 +1544,7 @@ __global__ __launch_bounds__(kBlock, (mm_waves<T, NCB>())) void k_wide_mfma(char
                                                       uint32_t n_sets) {
   __shared__ __align__(16) char s_tile[mm_lds_bytes<T, NCB>()];
   const GI G = load_group(groups + gid);
-  const UnitWalk W = wide_walk(G.n_units * n_sets, 1, 0);
+  const UnitWalk W = wide_walk(G.n_units * n_sets, 1, 0, gridDim.x, blockIdx.x);
   for (uint32_t f = W.first; f < W.end; f += W.stride) {
     const uint32_t set = f / G.n_units;
     mm_tile<T, CVT, NCB>(G, ops + G.op_begin, stab, uperm + 32 * gid, data, s_tile,
@@ -1629,15 +1822,29 @@ __global__ void k_fill(char *__restrict__ data, const double *__restrict__ angle
     fill_table<float2>((float2 *)(data + f.table64 + set * f.sstride64), gamma, beta, f.p);
 }
 
+// sum += x, with the rounding error added to comp (Neumaier).
+__device__ __forceinline__ void two_sum(double &sum, double &comp, double x) {
+  const double t = sum + x;
+  comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
+  sum = t;
+}
+
 // Block s reduces angle set s: its scalar slots start scalar_sstride bytes
-// after those of set s - 1, its results 2 n_cones + n_nets doubles after.
+// after those of set s - 1, its results 2 n_cones + n_nets doubles after.  The
+// results go straight to the caller's side (out_base: page-locked host
+// memory), which takes the place of a copy after the kernel; e_jk also to
+// device memory, where the energies read it.  With ctl, the persistent
+// executors' error word goes along.
 template <class T>
-__global__ void k_reduce(const char *__restrict__ scalar_base, int64_t scalar_sstride,
+__global__ __launch_bounds__(1024) void k_reduce(const char *__restrict__ scalar_base, int64_t scalar_sstride,
                          const int *__restrict__ csb, const int *__restrict__ ncb,
                          const int *__restrict__ cns, int n_cones, int n_nets,
-                         double *__restrict__ res_base) {
+                         double *__restrict__ res_base, double *__restrict__ out_base,
+                         const uint32_t *__restrict__ ctl, uint32_t *__restrict__ err) {
   const T *scalars = (const T *)(scalar_base + blockIdx.x * scalar_sstride);
   double *res = res_base + (int64_t)blockIdx.x * (2 * n_cones + n_nets);
+  double *out = out_base + (int64_t)blockIdx.x * (2 * n_cones + n_nets);
+  if (ctl && blockIdx.x == 0 && threadIdx.x == 0) *err = ctl[2];
   for (int c = threadIdx.x; c < n_cones; c += blockDim.x) {
     // the cone's slots split into cns[c] runs, one per slice (index
     // slicing); e_jk is the sum over slices of each run's product
@@ -1660,17 +1867,22 @@ __global__ void k_reduce(const char *__restrict__ scalar_base, int64_t scalar_ss
       }
     }
     res[c] = sre;
-    res[n_cones + c] = sim;
+    out[c] = sre;
+    out[n_cones + c] = sim;
   }
   __syncthreads();
-  for (int n = threadIdx.x; n < n_nets; n += blockDim.x) {
+  // a wave per network: compensated sums of a lane's cones, then of pairs of
+  // lanes, each sum's rounding error carried along
+  const int lane = threadIdx.x & 63;
+  for (int n = threadIdx.x >> 6; n < n_nets; n += blockDim.x >> 6) {
     double sum = 0.0, comp = 0.0;
-    for (int c = ncb[n]; c < ncb[n + 1]; c++) {
-      const double x = res[c], t = sum + x;
-      comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-      sum = t;
+    for (int c = ncb[n] + lane; c < ncb[n + 1]; c += 64) two_sum(sum, comp, res[c]);
+    for (int d = 1; d < 64; d <<= 1) {
+      const double s2 = __shfl_xor(sum, d), c2 = __shfl_xor(comp, d);
+      two_sum(sum, comp, s2);
+      comp += c2;
     }
-    res[2 * n_cones + n] = 0.5 * (double)(ncb[n + 1] - ncb[n]) - 0.5 * (sum + comp);
+    if (lane == 0) out[2 * n_cones + n] = 0.5 * (double)(ncb[n + 1] - ncb[n]) - 0.5 * (sum + comp);
   }
 }
 
@@ -1736,16 +1948,21 @@ hipError_t launch_fill(int prec, void *data, const double *angles, const FillDes
   return hipGetLastError();
 }
 
+// Programs in a launch up to which each takes 16 waves: two a compute unit.
+constexpr int kProgFew = 512;
+
 hipError_t launch_block_groups(int prec, void *data, const DevGroup *groups, const DevOp *ops,
                                const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
                                const int4 *ranges, int range_base, int n_blocks, int n_sets, hipStream_t s,
                                hipEvent_t t0, hipEvent_t t1) {
   if (n_blocks <= 0 || n_sets <= 0) return no_launch(t0, t1, s);
+  // few programs: 16 waves each, as the chip is otherwise idle; many: 4
+  const int threads = (int64_t)n_blocks * n_sets <= kProgFew ? kProgThreads : kBlock;
   if (prec == kPrecC128)
-    QTN_LAUNCH(t0, t1, k_programs<double2>, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
+    QTN_LAUNCH(t0, t1, k_programs<double2>, dim3(n_blocks * n_sets), dim3(threads), s, (char *)data,
                prog, ranges, range_base, n_blocks);
   else if (prec == kPrecC64)
-    QTN_LAUNCH(t0, t1, k_programs<float2>, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
+    QTN_LAUNCH(t0, t1, k_programs<float2>, dim3(n_blocks * n_sets), dim3(threads), s, (char *)data,
                prog, ranges, range_base, n_blocks);
   else
     QTN_LAUNCH(t0, t1, k_block_groups, dim3(n_blocks * n_sets), dim3(kBlock), s, (char *)data,
@@ -1763,7 +1980,7 @@ void launch_wide_t(const DevGroup &hg, uint32_t units, char *d, const DevGroup *
     QTN_LAUNCH_LDS(t0, t1, (k_wide_stream<T, CVT>), dim3(nb), dim3(kBlock), lds, s, d, groups, ops,
                    stab, uperm, group, n_sets);
   } else if (hg.variant == kVarCell) {
-    const size_t lds = cell_lds_words(hg.n_ops, hg.rls) * sizeof(uint32_t);
+    const size_t lds = cell_lds_words(hg.n_ops) * sizeof(uint32_t);
 #define QTN_CELL_LAUNCH(CB, SL)                                                                  \
   do {                                                                                           \
     const int nb = wide_grid(k_wide_cells<T, CVT, CB, SL>, lds, units);                         \
@@ -1796,9 +2013,9 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
   if ((hg.variant == kVarStream || hg.variant == kVarCell) &&
       (hg.n_ops < 1 || hg.n_ops > kStreamMaxOps))
     return hipErrorInvalidValue;
-  if (hg.variant == kVarCell && (hg.rls < kCellMinCB || hg.rls > kCellMaxCB || hg.n_ops > 64 ||
-                                 hg.sl > kCellMaxSerial || hg.sl > hg.rls ||
-                                 cell_lds_words(hg.n_ops, hg.rls) > kCellMaxLdsWords))
+  if (hg.variant == kVarCell && (hg.rls < kCellMinCB || hg.rls > kCellMaxCB ||
+                                 hg.n_ops > kCellMaxOps || hg.sl > kCellMaxSerial ||
+                                 hg.sl > hg.rls))
     return hipErrorInvalidValue;
   const uint32_t ns = (uint32_t)n_sets, units = n_units * ns;
   char *d = (char *)data;
@@ -1833,6 +2050,40 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
     launch_wide_t<float2, false>(hg, units, d, groups, ops, stab, uperm, group, ns, s, t0, t1);
   else
     launch_wide_t<float2, true>(hg, units, d, groups, ops, stab, uperm, group, ns, s, t0, t1);
+  return hipGetLastError();
+}
+
+bool step_group(const DevGroup &hg) {
+  return hg.variant == kVarCell && hg.rls == kCellRuleCB && hg.n_ops >= 1 &&
+         hg.n_ops <= kCellMaxOps && hg.sl <= kCellMaxSerial;
+}
+
+int step_blocks(const DevGroup &hg, int n_sets, double units_per_wave, int threads) {
+  const double units = (double)hg.n_units * n_sets;
+  const double nb = std::ceil(units / (threads / 64) / std::max(1.0, units_per_wave));
+  const int b = (int)std::min(nb, (double)(kStepWaves / (threads / 64)));
+  return b >= 64 ? b & ~7 : std::max(1, b);
+}
+
+size_t step_lds(const DevGroup &hg) { return cell_lds_words(hg.n_ops) * sizeof(uint32_t); }
+
+hipError_t launch_step(int prec, void *data, const DevGroup *groups, const DevOp *ops,
+                       const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                       const int4 *tasks, int n_tasks, int n_blocks, int threads, size_t lds,
+                       int n_sets, hipStream_t s) {
+  if (threads < 64 || threads > kStepMaxThreads || threads % 64) return hipErrorInvalidValue;
+  if (n_tasks <= 0 || n_blocks <= 0) return hipSuccess;
+  char *d = (char *)data;
+  const dim3 grid(n_blocks), block(threads);
+  if (prec == kPrecC128)
+    hipLaunchKernelGGL(k_step<kPrecC128>, grid, block, lds, s, d, groups, ops, stab, uperm, prog,
+                       tasks, n_tasks, (uint32_t)n_sets);
+  else if (prec == kPrecC64)
+    hipLaunchKernelGGL(k_step<kPrecC64>, grid, block, lds, s, d, groups, ops, stab, uperm, prog,
+                       tasks, n_tasks, (uint32_t)n_sets);
+  else
+    hipLaunchKernelGGL(k_step<kPrecMixed>, grid, block, lds, s, d, groups, ops, stab, uperm, prog,
+                       tasks, n_tasks, (uint32_t)n_sets);
   return hipGetLastError();
 }
 
@@ -1879,14 +2130,16 @@ int persistent_blocks(int prec, int n_cu) {
 
 hipError_t launch_reduce(int prec, const void *data, int64_t scalar_off, int64_t scalar_sstride,
                          const int *csb, const int *ncb, const int *cns, int n_cones, int n_nets,
-                         int n_sets, double *res, hipStream_t s) {
+                         int n_sets, double *res, double *out, const uint32_t *ctl, uint32_t *err,
+                         hipStream_t s) {
   const char *sc = (const char *)data + scalar_off;
+  const dim3 grid(n_sets), block(n_cones > 256 || n_nets > 4 ? 1024 : 256);
   if (prec == kPrecC64)
-    hipLaunchKernelGGL(k_reduce<float2>, dim3(n_sets), dim3(256), 0, s, sc, scalar_sstride, csb,
-                       ncb, cns, n_cones, n_nets, res);
+    hipLaunchKernelGGL(k_reduce<float2>, grid, block, 0, s, sc, scalar_sstride, csb, ncb, cns,
+                       n_cones, n_nets, res, out, ctl, err);
   else
-    hipLaunchKernelGGL(k_reduce<double2>, dim3(n_sets), dim3(256), 0, s, sc, scalar_sstride, csb,
-                       ncb, cns, n_cones, n_nets, res);
+    hipLaunchKernelGGL(k_reduce<double2>, grid, block, 0, s, sc, scalar_sstride, csb, ncb, cns,
+                       n_cones, n_nets, res, out, ctl, err);
   return hipGetLastError();
 }
 

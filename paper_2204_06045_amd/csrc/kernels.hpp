@@ -24,7 +24,8 @@ struct FillDesc {
   int32_t p, pad;
 };
 
-// n_sets angle sets of n_angles doubles each, set after set.
+// n_sets angle sets of n_angles doubles each, set after set (page-locked host
+// memory: a few doubles a block, read over the link).
 hipError_t launch_fill(int prec, void *data, const double *angles,
                        const FillDesc *fills, int n_nets, int n_angles, int n_sets,
                        hipStream_t s);
@@ -47,6 +48,22 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
                              const DevOp *ops, const int32_t *stab, const uint8_t *uperm,
                              int group, int n_sets, hipStream_t s, hipEvent_t t0 = nullptr,
                              hipEvent_t t1 = nullptr);
+
+// One step of every light cone in one launch (k_step).  tasks[t]: (group, first
+// workgroup, workgroups, -) for a cell-mapped group that step_group() takes,
+// or (-1, first workgroup, n_sets, program word) for a segment program;
+// workgroups from the last task's end to the next one's first stay idle.
+// lds: the most bytes any task needs (step_lds, kProgLdsBytes).
+constexpr int kStepMaxThreads = 1024;  // widest workgroup
+constexpr int kStepWaves = 4096;       // most waves of one group: 4 on each SIMD
+bool step_group(const DevGroup &hg);
+// Workgroups of a group whose waves take about units_per_wave units each.
+int step_blocks(const DevGroup &hg, int n_sets, double units_per_wave, int threads);
+size_t step_lds(const DevGroup &hg);
+hipError_t launch_step(int prec, void *data, const DevGroup *groups, const DevOp *ops,
+                       const int32_t *stab, const uint8_t *uperm, const uint32_t *prog,
+                       const int4 *tasks, int n_tasks, int n_blocks, int threads, size_t lds,
+                       int n_sets, hipStream_t s);
 
 // Clears the control words, then runs every light cone's task list in
 // lockstep inside one persistent launch of n_blocks resident blocks.
@@ -87,11 +104,14 @@ int persistent_blocks(int prec, int n_cu);
 // slicing (cone_slices[c] > 1) the slots split into that many equal runs, one
 // per slice, and e_jk is the sum of the runs' products; per network:
 // E = |E|/2 - 1/2 sum Re e_jk with Neumaier compensation.
-// res: per angle set [n_cones] Re, [n_cones] Im, [n_nets] energies.
+// out: per angle set [n_cones] Re, [n_cones] Im, [n_nets] energies (page-locked
+// host memory); res: device memory of the same size; ctl, err: the persistent
+// executors' control words (or null), whose error word goes to *err.
 hipError_t launch_reduce(int prec, const void *data, int64_t scalar_off,
                          int64_t scalar_sstride, const int *cone_scalar_begin,
                          const int *net_cone_begin, const int *cone_slices, int n_cones,
-                         int n_nets, int n_sets, double *res, hipStream_t s);
+                         int n_nets, int n_sets, double *res, double *out,
+                         const uint32_t *ctl, uint32_t *err, hipStream_t s);
 
 
 // Bytes of the device scratch array that the allocation-free bucket entry

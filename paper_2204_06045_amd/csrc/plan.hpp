@@ -127,6 +127,8 @@ struct Group {
   int8_t pick_place = -1;    // 0 inside a workgroup segment, 1 own launch
   int8_t pick_variant = -1;  // 1 generic mapping, 2 streaming mapping
   int8_t pick_rls = -1;      // streaming: lane-summed bits
+  // the cost model's time of the group where it runs (milliseconds; -1: none)
+  float pred_ms = -1.0f;
 };
 
 

@@ -79,6 +79,29 @@ def test_segment_programs(qtn, orc, gpu, n, d, p, cfg, prec):
         _check(zz, zi, en, ref, ref_en, prec, str((cfg, more)))
 
 
+@pytest.mark.parametrize("cfg,mixed", [
+    (dict(), 18),
+    (dict(small_width=10), 14),            # more and narrower own-launch groups
+    (dict(small_width=8, max_levels=7), 12),  # a few of them of other mappings
+])
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_step_launches_equal_group_launches(qtn, gpu, cfg, mixed, prec):
+    # a step runs the same units with the same arithmetic as one launch per
+    # group (executor 1): equal bit for bit, for one angle set and for several
+    inst = qs.instance(20, 3, 3, 0, 3)
+    gs = np.array([a[0] for a in inst["angles"]])
+    bs = np.array([a[1] for a in inst["angles"]])
+    got = {}
+    for executor in (0, 1):
+        print(f"executor={executor} {cfg} prec={prec}", flush=True)
+        net = qtn.Network(20, inst["edges"], gs[0], bs[0], executor=executor, mixed_width=mixed, **cfg)
+        net.plan(prec)
+        got[executor] = net.contract()[0], *net.contract_angles(gs, bs)
+        net.close()
+    for a, b in zip(got[0], got[1]):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("n,p", [(12, 2), (16, 3), (16, 4), (20, 3)])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_small_graphs_all_configs(qtn, orc, gpu, n, p, prec):
