@@ -682,12 +682,36 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
     dg.n_ubits = (uint8_t)sc.size();
     s.uperm.insert(s.uperm.end(), up, up + 32);
   }
-  // A cell group's table of a tensor holding the union bits of mask: its
-  // unit-bit runs, the steps of the cell bits (kept bits, then serial bits:
-  // serial cell bit rb + t is union bit 6 + sl - 1 - t, bit 6 the highest
-  // cell bit, summed first) and the mask of those it holds.
+  // union bit of cell bit j: kept bits, then serial bits (serial cell bit
+  // rb + t is union bit 6 + sl - 1 - t, bit 6 the highest, summed first)
+  auto cell_bit = [&](int j) {
+    const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32;
+    return j < rb ? (int)rp[j] : 6 + dg.sl - 1 - (j - rb);
+  };
+  if (cell) {
+    // Operand order.  Every point multiplies all operands, but an operand
+    // without cell bits is one value per lane: without serial bits those form
+    // a product of their own, which meets the cells once.  Of the others, the
+    // one with the most cell bits comes first (its values become the cells,
+    // none copied) and the one with the fewest last (it takes that product).
+    auto held = [&](int k) {
+      int n = 0;
+      for (int j = 0; j < cb; j++) n += (G.ops[k].mask >> cell_bit(j)) & 1u;
+      return n;
+    };
+    auto most_first = [&](int x, int y) { return held(x) > held(y); };
+    if (dg.sl == 0) {
+      const auto first = order.begin() + dg.n_step0;
+      const auto full = std::stable_partition(first, order.end(), [&](int k) { return held(k) == 0; });
+      dg.n_serial = (uint8_t)(full - first);
+      std::stable_sort(full, order.end(), most_first);
+    } else {
+      std::stable_sort(order.begin(), order.begin() + dg.n_step, most_first);
+    }
+  }
+  // A cell group's table of a tensor holding the union bits of mask.
   auto cell_table = [&](uint32_t mask) -> int {
-    const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32, *up = rp + rb;
+    const uint8_t *up = s.uperm.data() + s.uperm.size() - 32 + rb;
     uint16_t ur[kCellURuns];
     std::memset(ur, 0, sizeof ur);
     auto place = [&](int q) { return __builtin_popcount(mask & ((1u << q) - 1u)); };
@@ -711,10 +735,8 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
       s.stab.push_back((int32_t)((uint32_t)ur[2 * w] | ((uint32_t)ur[2 * w + 1] << 16)));
     uint32_t cm = 0;
     for (int j = 0; j < cb; j++) {
-      const int q = j < rb ? rp[j] : 6 + dg.sl - 1 - (j - rb);
-      const bool held = (mask >> q) & 1u;
-      s.stab.push_back(held ? (int32_t)(1u << place(q)) : 0);
-      cm |= (held ? 1u : 0u) << j;
+      const int q = cell_bit(j);
+      if ((mask >> q) & 1u) cm |= (uint32_t)place(q) << (5 * j) | 1u << (20 + j);
     }
     s.stab.push_back((int32_t)cm);
     return QTN_OK;

@@ -70,20 +70,28 @@ enum Variant : uint8_t { kVarGeneric = 0, kVarStream = 1, kVarMfma = 2, kVarCell
 // uperm).  Ops [0, n_step) hold bit 6 (all ops when sl = 0), the next
 // n_serial hold bit 7 but not 6 (sl = 2), the rest no serial bit; the first
 // n_step0 ops of the last of these levels hold no unit bit (sl = 0: hold lane
-// bits only); n_unit = the most unit-bit runs of any operand or of the
-// output.  Each op's stab entry starts its table: kCellURuns / 2 words of
-// unit-bit runs (src | len << 5 | dst << 11, two per word, src counting unit
-// bits; unused runs 0) giving the unit part of its index, then CB element
-// steps of the cell bits (0: not held), then the mask of the cell bits held.
-// The output's, at gtab, is of the same form (dst and steps in the output).
+// bits only).  With sl = 0, n_serial counts the ops after those that hold no
+// cell bit.  Of the ops in all cells, the first holds the most cell bits and
+// the last the fewest.  n_unit = the most unit-bit runs of any operand or of
+// the output.  Tables: the output's at gtab, operand k's at gtab + (k + 1)
+// cell_table_words() (also its stab): kCellURuns / 2 words of unit-bit runs
+// (src | len << 5 | dst << 11, two per word, src counting unit bits; unused
+// runs 0) giving the unit part of the tensor's index, then the cell word: bits
+// 5 j to 5 j + 4 log2 of the element step of cell bit j, from bit 20 the mask
+// of the cell bits held.
 constexpr int kCellMinCB = 2, kCellMaxCB = 4, kCellRuleCB = 3;
 constexpr int kCellURuns = 16;
 constexpr int kCellMaxSerial = 2;
 constexpr int kCellMaxOps = 63;  // one lane per operand and one for the output
-constexpr int cell_table_words(int cb) { return kCellURuns / 2 + cb + 1; }
+constexpr int cell_table_words() { return kCellURuns / 2 + 1; }
+// Union bit (of the low six) on lane bit b, L summed bits: with 3 to 5 of them
+// the bits from 2 up are reversed, so that summed ones lie on lane bits 5 and
+// 4, which two registers of a wave can exchange in one instruction; bits 0
+// and 1 stay, which keeps the elements of four neighbouring lanes together.
+constexpr int cell_lane_bit(int b, int L) { return L >= 3 && L <= 5 && b >= 2 ? 7 - b : b; }
 // LDS words of a cell group's tables: the operands' lane offsets, and the
-// unit-bit runs of the operands and the output.
-constexpr int cell_lds_words(int n_ops) { return n_ops * 64 + (n_ops + 1) * (kCellURuns / 2); }
+// unit-bit runs of the operands and the output (a rotation and a mask each).
+constexpr int cell_lds_words(int n_ops) { return n_ops * 64 + (n_ops + 1) * 2 * kCellURuns; }
 
 // Matrix form (kVarMfma): ops are [side A..., side B...] with n_unit = |side
 // A|, n_step = |side B|.  A work unit is one kMmTM x 16 rls (m x n) output

@@ -507,42 +507,54 @@ __device__ __forceinline__ void stream_unit(const GI &G, const DevOp *__restrict
 
 // Per-lane constants of the cell mapping: lane k < n_ops holds operand k's,
 // lane n_ops the output's.
-template <int CB> struct CellLane {
-  uint64_t base;     // address in angle set 0
-  uint64_t sstride;  // bytes between angle sets
-  uint32_t es, dt;   // element bytes, storage type (read with CVT only)
-  uint32_t cm;       // cell bits the operand's index holds
-  uint32_t step[CB]; // operands: bytes from a cell bit's 0 to its 1; output: elements
+struct CellLane {
+  uint32_t es, dt;  // element bytes, storage type (read with CVT only)
+  uint32_t cells;   // the tensor's cell word
 };
+// The lane's tensor's address in angle set `set` (read again from the
+// descriptors when the set changes: held, it would cost four registers).
+__device__ __forceinline__ uint64_t cell_base(const GI &G, const DevOp *__restrict__ gops,
+                                              const char *data, int lane, uint32_t set) {
+  const bool out = lane >= G.n_ops;
+  const DevOp &o = gops[out ? 0 : lane];
+  return (uint64_t)data + (uint64_t)(out ? G.out_off : o.off) +
+         (uint64_t)set * (uint64_t)(out ? G.out_sstride : o.sstride);
+}
+
+// Union bits 0..5 of a lane.
+__device__ __forceinline__ uint32_t cell_lane(uint32_t lane, int L) {
+  if (L < 3 || L > 5) return lane;
+  return (lane & 3u) | (__builtin_bitreverse32(lane >> 2) >> 26 & 0x3Cu);
+}
 
 // Block-wide setup.  LDS: every operand's byte offset of every lane
-// ([k][lane]), then the unit-bit runs of the operands and the output
-// ([k][kCellURuns / 2]).  Registers: the lane's own constants.
-template <class T, bool CVT, int CB>
+// ([k][lane]), then the unit-bit runs of the operands and the output, each as
+// the rotation that brings the unit number's bits to their place and the mask
+// that keeps them ([k][kCellURuns][2]).  Registers: the lane's own constants.
+template <class T, bool CVT>
 __device__ __forceinline__ void cell_setup(const GI &G, const DevOp *__restrict__ gops,
-                                           const int32_t *__restrict__ ctab, char *data,
-                                           uint32_t *s_tab, CellLane<CB> &cl) {
+                                           const int32_t *__restrict__ ctab, uint32_t *s_tab,
+                                           CellLane &cl) {
   const int n_ops = G.n_ops, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int k = wave; k < n_ops; k += blockDim.x >> 6) {
     // operand k is the same for the whole wave
     const DevOp &o = gops[__builtin_amdgcn_readfirstlane(k)];
-    s_tab[k * 64 + lane] = pext_runs((uint32_t)lane, o) * esize<T, CVT>(op_dt(o));
+    s_tab[k * 64 + lane] = pext_runs(cell_lane(lane, G.L), o) * esize<T, CVT>(op_dt(o));
   }
-  uint32_t *s_ur = s_tab + n_ops * 64;
-  for (int e = threadIdx.x; e < (n_ops + 1) * (kCellURuns / 2); e += blockDim.x) {
-    const int k = e / (kCellURuns / 2), i = e % (kCellURuns / 2);
-    s_ur[e] = (uint32_t)ctab[(k < n_ops ? gops[k].stab : G.gtab) + i];
+  uint2 *s_ur = (uint2 *)(s_tab + n_ops * 64);
+  const int32_t *tab = ctab + G.gtab;  // the output's table, then the operands'
+  for (int e = threadIdx.x; e < (n_ops + 1) * kCellURuns; e += blockDim.x) {
+    const int k = e / kCellURuns, i = e % kCellURuns;
+    const uint32_t w = (uint32_t)tab[(k < n_ops ? k + 1 : 0) * cell_table_words() + (i >> 1)];
+    const uint32_t rr = (w >> (16 * (i & 1))) & 0xFFFFu;  // an unused run is 0: mask 0
+    const uint32_t src = rr & 31u, len = (rr >> 5) & 63u, dst = rr >> 11;
+    s_ur[e] = make_uint2((src - dst) & 31u, (uint32_t)((1ull << len) - 1ull) << dst);
   }
   const bool out = lane >= n_ops;
   const DevOp &o = gops[out ? 0 : lane];
   cl.dt = CVT && !out ? (uint32_t)o.dt : 0u;
   cl.es = out ? (uint32_t)sizeof(T) : esize<T, CVT>(cl.dt);
-  cl.base = (uint64_t)(data + (out ? G.out_off : o.off));
-  cl.sstride = (uint64_t)(out ? G.out_sstride : o.sstride);
-  const int32_t *t = ctab + (out ? G.gtab : o.stab) + kCellURuns / 2;
-#pragma unroll
-  for (int j = 0; j < CB; j++) cl.step[j] = (uint32_t)t[j] * (out ? 1u : cl.es);
-  cl.cm = (uint32_t)t[CB];
+  cl.cells = (uint32_t)tab[(out ? 0 : lane + 1) * cell_table_words() + kCellURuns / 2];
 }
 
 // v of the lane whose index differs in bit t (any values in the others).
@@ -586,89 +598,125 @@ template <int T> __device__ __forceinline__ double xor_sum(double v) {
   return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
 
-// One reduce-scatter step over lane bit T: of the 2 * HALF accumulators the
-// lane keeps the half selected by its bit T, adding the partner lane's copy.
+// One reduce-scatter step over lane bit BIT: of the 2 * HALF accumulators the
+// lane keeps the half selected by its bit, adding the partner lane's copy.
+// Over bits 5 and 4 the two halves of a pair change places in one instruction
+// a word; over the others each lane selects what it keeps and what it sends.
+template <int BIT>
+__device__ __forceinline__ float swap_sum(float lo, float hi) {
+  const auto r = BIT == 5 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false)
+                          : __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int BIT>
+__device__ __forceinline__ double swap_sum(double lo, double hi) {
+  const uint32_t ll = (uint32_t)__double2loint(lo), lh = (uint32_t)__double2hiint(lo);
+  const uint32_t hl = (uint32_t)__double2loint(hi), hh = (uint32_t)__double2hiint(hi);
+  const auto a = BIT == 5 ? __builtin_amdgcn_permlane32_swap(ll, hl, false, false)
+                          : __builtin_amdgcn_permlane16_swap(ll, hl, false, false);
+  const auto b = BIT == 5 ? __builtin_amdgcn_permlane32_swap(lh, hh, false, false)
+                          : __builtin_amdgcn_permlane16_swap(lh, hh, false, false);
+  return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+}
 template <class T, int HALF, int BIT>
 __device__ __forceinline__ void reduce_scatter_step(T *acc, int lane) {
-  const bool hi = ((lane >> BIT) & 1) != 0;
+  const bool up = ((lane >> (BIT & 31)) & 1) != 0;
 #pragma unroll
   for (int i = 0; i < HALF; i++) {
-    const T keep = hi ? acc[i + HALF] : acc[i];
-    const T send = hi ? acc[i] : acc[i + HALF];
-    acc[i] = cadd(keep, xor_lane<BIT>(send));
+    if (BIT >= 4) {
+      acc[i].x = swap_sum<BIT>(acc[i].x, acc[i + HALF].x);
+      acc[i].y = swap_sum<BIT>(acc[i].y, acc[i + HALF].y);
+    } else {
+      const T keep = up ? acc[i + HALF] : acc[i];
+      const T send = up ? acc[i] : acc[i + HALF];
+      acc[i] = cadd(keep, xor_lane<(BIT < 4 ? BIT : 0)>(send));
+    }
   }
 }
 template <class T, int N, int BIT>
-__device__ __forceinline__ void butterfly_step(T *acc, int nacc) {
+__device__ __forceinline__ void butterfly_step(T *acc) {
 #pragma unroll
-  for (int i = 0; i < N; i++)
-    if (i < nacc) {
-      acc[i].x = xor_sum<BIT>(acc[i].x);
-      acc[i].y = xor_sum<BIT>(acc[i].y);
-    }
+  for (int i = 0; i < N; i++) {
+    acc[i].x = xor_sum<BIT>(acc[i].x);
+    acc[i].y = xor_sum<BIT>(acc[i].y);
+  }
+}
+
+// Lane bit summed in step t of a group's lane reduction: with three summed
+// bits and more 5, 4, 3, 2 (as many as there are over two), then 0 and 1.
+__host__ __device__ constexpr int sum_bit(int t, int ls) {
+  return ls < 3 ? t : (t < ls - 2 ? 5 - t : t - (ls - 2));
+}
+// Steps T..LS-1 of the lane reduction of M cells: reduce-scatters while there
+// are two cells and more, then butterflies.
+template <class T, int M, int LS, int STEP>
+__device__ __forceinline__ void lane_steps(T *acc, int lane) {
+  if constexpr (STEP < LS) {
+    if constexpr (M > 1)
+      reduce_scatter_step<T, (M >> 1), sum_bit(STEP, LS)>(acc, lane);
+    else
+      butterfly_step<T, 1, sum_bit(STEP, LS)>(acc);
+    lane_steps<T, (M > 1 ? M / 2 : 1), LS, STEP + 1>(acc, lane);
+  }
 }
 
 // Element offset, in the output, of a lane after cell_finish: its kept lane
 // bits and the register cell its reduce-scatter bits select.
-template <int CB, int RB>
-__device__ __forceinline__ uint32_t cell_out_lane(const CellLane<CB> &cl, int n_ops, int L, int ls,
-                                                  int lane) {
-  uint32_t o = L < 6 ? (uint32_t)lane >> L : 0u;
-  const int q = min(RB, ls);
+template <int RB>
+__device__ __forceinline__ uint32_t cell_out_lane(uint32_t out_cells, int L, int ls, int lane) {
+  uint32_t o = L < 6 ? cell_lane(lane, L) >> L : 0u;
 #pragma unroll
   for (int t = 0; t < RB; t++)
-    if (t < q) {
-      // lane bit t selects the upper half: register bit RB - 1 - t
-      const uint32_t s = __builtin_amdgcn_readlane(cl.step[RB - 1 - t], n_ops);
-      o += ((lane >> t) & 1) ? s : 0u;
-    }
+    if (t < ls)  // the step's lane bit selects the upper half: register bit RB - 1 - t
+      o += ((lane >> sum_bit(t, ls)) & 1) ? 1u << ((out_cells >> (5 * (RB - 1 - t))) & 31u) : 0u;
   return o;
 }
 
-// Sums the lane-summed bits 0..ls-1 of the 2^RB register accumulators and
-// writes the results at out + out_lane: a reduce-scatter over the first
-// q = min(RB, ls) bits (afterwards lane bit t selects half of the cells),
-// butterflies for the rest.
-template <class T, int CB, int RB>
-__device__ __forceinline__ void cell_finish(T *acc, const CellLane<CB> &cl, int n_ops, int ls,
-                                            int lane, char *out, uint32_t out_lane) {
-  constexpr int NR = 1 << RB;
-  const int q = min(RB, ls);
-  if (RB >= 1 && ls > 0) reduce_scatter_step<T, (NR >> 1), 0>(acc, lane);
-  if (RB >= 2 && ls > 1) reduce_scatter_step<T, (NR >> 2), 1>(acc, lane);
-  if (RB >= 3 && ls > 2) reduce_scatter_step<T, (NR >> 3), 2>(acc, lane);
-  if (RB >= 4 && ls > 3) reduce_scatter_step<T, (NR >> 4), 3>(acc, lane);
-  const int nacc = NR >> q;
-  if (RB <= 0 && ls > 0) butterfly_step<T, NR, 0>(acc, nacc);
-  if (RB <= 1 && ls > 1) butterfly_step<T, (RB >= 1 ? NR / 2 : NR), 1>(acc, nacc);
-  if (RB <= 2 && ls > 2) butterfly_step<T, (RB >= 2 ? NR / 4 : 1), 2>(acc, nacc);
-  if (RB <= 3 && ls > 3) butterfly_step<T, 1, 3>(acc, nacc);
-  if (ls > 4) butterfly_step<T, 1, 4>(acc, nacc);
-  if (ls > 5) butterfly_step<T, 1, 5>(acc, nacc);
-  // lanes whose summed bits q..ls-1 are zero hold the results; acc[i] is
-  // register cell i plus the cells out_lane counts
-  if ((((uint32_t)lane >> q) & ((1u << (ls - q)) - 1u)) == 0) {
+// Sums the LS lane-summed bits of the 2^RB register accumulators and writes
+// the results at out + out_lane: reduce-scatters over the first q =
+// min(RB, LS) of them (afterwards step t's lane bit selects half of the
+// cells), butterflies for the rest.
+template <class T, int RB, int LS>
+__device__ __forceinline__ void cell_finish_ls(T *acc, uint32_t out_cells, int lane, char *out,
+                                               uint32_t out_lane) {
+  constexpr int NR = 1 << RB, Q = RB < LS ? RB : LS;
+  lane_steps<T, NR, LS, 0>(acc, lane);
+  // lanes whose summed bits past the reduce-scatters are zero hold the
+  // results; acc[i] is register cell i plus the cells out_lane counts
+  uint32_t rest = 0;
 #pragma unroll
-    for (int i = 0; i < NR; i++) {
-      if (i < nacc) {
-        uint64_t o = 0;
+  for (int t = Q; t < LS; t++) rest |= 1u << sum_bit(t, LS);
+  if (((uint32_t)lane & rest) == 0) {
 #pragma unroll
-        for (int b = 0; b < RB; b++)
-          if ((i >> b) & 1) o += (uint64_t)(uint32_t)__builtin_amdgcn_readlane(cl.step[b], n_ops);
-        ((T *)(out + o * sizeof(T)))[out_lane] = acc[i];
-      }
+    for (int i = 0; i < (NR >> Q); i++) {
+      uint64_t o = 0;
+#pragma unroll
+      for (int b = 0; b < RB; b++)
+        if ((i >> b) & 1) o += 1ull << ((out_cells >> (5 * b)) & 31u);
+      ((T *)(out + o * sizeof(T)))[out_lane] = acc[i];
     }
   }
+}
+template <class T, int RB, bool SERIAL>
+__device__ __forceinline__ void cell_finish(T *acc, uint32_t out_cells, int ls, int lane, char *out,
+                                            uint32_t out_lane) {
+  if (SERIAL || ls == 6) cell_finish_ls<T, RB, 6>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 1) cell_finish_ls<T, RB, 1>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 2) cell_finish_ls<T, RB, 2>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 3) cell_finish_ls<T, RB, 3>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 4) cell_finish_ls<T, RB, 4>(acc, out_cells, lane, out, out_lane);
+  else cell_finish_ls<T, RB, 5>(acc, out_cells, lane, out, out_lane);
 }
 
 // acc[c] (c < N; first: set to) times an operand whose index holds the cell
 // bits CM (scalar address p, lane offset lt, cell steps st): only the
 // distinct cells (c & ~CM == 0) are loaded, each value serving every cell
 // that differs from it in bits outside CM.  A cell's offset is uniform, so it
-// goes into the scalar address.  OTHER: stored in the other precision.
+// goes into the scalar address.  OTHER: stored in the other precision.  With
+// scale, the values are multiplied by w before they meet the cells.
 template <class T, bool OTHER, int N, int CM>
 __device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, uint32_t lt,
-                                           const uint32_t *st) {
+                                           const uint32_t *st, bool scale, T w) {
   T v[N];
 #pragma unroll
   for (int c = 0; c < N; c++)
@@ -679,6 +727,11 @@ __device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, ui
         if ((c >> b) & 1) o += st[b];
       v[c] = OTHER ? gload_dt<T, true>(p + o, lt, sizeof(T) == 16 ? 1 : 0) : gload<T>(p + o, lt);
     }
+  if (scale) {
+#pragma unroll
+    for (int c = 0; c < N; c++)
+      if ((c & ~CM) == 0) v[c] = cmul(v[c], w);
+  }
   if (first) {
 #pragma unroll
     for (int c = 0; c < N; c++) acc[c] = v[c & CM];
@@ -689,26 +742,27 @@ __device__ __forceinline__ void cell_op_cm(T *acc, bool first, const char *p, ui
 }
 
 // acc[c] (c < N) times operand k (uniform) at the addresses of lane k.
-template <class T, bool CVT, int CB, int N>
-__device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLane<CB> &cl,
-                                        uint64_t addr, uint32_t lt) {
+template <class T, bool CVT, int N>
+__device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLane &cl, uint64_t addr,
+                                        uint32_t lt, bool scale, T w) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)addr, k);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(addr >> 32), k);
   const char *p = (const char *)(((uint64_t)hi << 32) | lo);
   const int dt = CVT ? (int)__builtin_amdgcn_readlane(cl.dt, k) : 0;
-  const uint32_t cm = __builtin_amdgcn_readlane(cl.cm, k) & (uint32_t)(N - 1);
+  const uint32_t cells = N > 1 ? __builtin_amdgcn_readlane(cl.cells, k) : 0u;
+  const uint32_t cm = (cells >> 20) & (uint32_t)(N - 1), es = esize<T, CVT>(dt);
   uint32_t st[4] = {};
 #pragma unroll
-  for (int b = 0; b < CB; b++)
-    if ((1 << b) < N) st[b] = __builtin_amdgcn_readlane(cl.step[b], k);
+  for (int b = 0; b < 4; b++)
+    if ((1 << b) < N) st[b] = es << ((cells >> (5 * b)) & 31u);  // read where cm has the bit
 #define QTN_CM(O, m) \
-  case m: cell_op_cm<T, O, N, (m) & (N - 1)>(acc, first, p, lt, st); break;
+  case m: cell_op_cm<T, O, N, (m) & (N - 1)>(acc, first, p, lt, st, scale, w); break;
 #define QTN_CMS(O)                                                                                \
   switch (cm) {                                                                                   \
     QTN_CM(O, 0) QTN_CM(O, 1) QTN_CM(O, 2) QTN_CM(O, 3) QTN_CM(O, 4) QTN_CM(O, 5) QTN_CM(O, 6)    \
     QTN_CM(O, 7) QTN_CM(O, 8) QTN_CM(O, 9) QTN_CM(O, 10) QTN_CM(O, 11) QTN_CM(O, 12)              \
     QTN_CM(O, 13) QTN_CM(O, 14)                                                                   \
-    default: cell_op_cm<T, O, N, (15 & (N - 1))>(acc, first, p, lt, st); break;                   \
+    default: cell_op_cm<T, O, N, (15 & (N - 1))>(acc, first, p, lt, st, scale, w); break;         \
   }
   // one branch per operand on its storage, so that its loads stay together
   if (CVT && dt != (sizeof(T) == 16 ? 0 : 1)) {
@@ -730,68 +784,76 @@ __device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLan
 // 6) in the cells left, bit 7 is summed, and the other operands multiply the
 // 2^RB register cells.  The lane-summed bits are reduced last.  Addresses for
 // the unit are formed by lane k for operand k, and by lane n_ops for the
-// output.  A unit is a chain of one load round trip per operand, and what a
-// wave does between them is exposed: so the lane offset of the next operand
-// is read while this one's loads are under way, the cells' offsets are scalar
-// steps, and no descriptor is read from memory.
+// output.
+//
+// Bound: vector instruction issue and, behind it, one load round trip per
+// operand (a group of 24 bits, 4 summed, 7 operands, complex128: 250
+// instructions a unit keep the SIMDs 55% busy; of the 514 it took before, the
+// complex products needed 130, and they kept them 67% busy).  So what can be
+// scalar is: cell offsets are shifts of one word per operand, no descriptor is
+// read from memory, and the next operand's lane offset is read while this
+// one's loads are under way.
 template <class T, bool CVT, int CB, int SL>
-__device__ __forceinline__ void cell_unit(const GI &G, const CellLane<CB> &cl, uint64_t set_base,
+__device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint64_t set_base,
                                           const uint32_t *s_tab, const T *P, uint32_t u, int lane,
-                                          int ls, uint32_t out_lane) {
+                                          int ls, uint32_t out_cells, uint32_t out_lane) {
   constexpr int NC = 1 << CB, RB = CB - SL, NR = 1 << RB;
   const int n_step = G.n_step, n_ops = G.n_ops, nfix = G.n_step0;
   const uint32_t *s_lane = s_tab + lane;
   // lane k: unit part of tensor k's index, then its address for this unit
-  const uint32_t *s_ur = s_tab + n_ops * 64 + min(lane, n_ops) * (kCellURuns / 2);
+  const uint4 *s_ur = (const uint4 *)(s_tab + n_ops * 64 + min(lane, n_ops) * (2 * kCellURuns));
   uint32_t ub = 0;
-  for (int i = 0; i < G.n_unit; i += 4) {
-    const uint2 w2 = *(const uint2 *)(s_ur + (i >> 1));
-#pragma unroll
-    for (int h = 0; h < 4; h++) {
-      const uint32_t rr = ((h < 2 ? w2.x : w2.y) >> (16 * (h & 1))) & 0xFFFFu;  // an unused run is 0
-      const uint32_t src = rr & 31u, len = (rr >> 5) & 63u, dst = rr >> 11;
-      ub |= ((u >> src) & (uint32_t)((1ull << len) - 1ull)) << dst;
-    }
+  for (int i = 0; i < G.n_unit; i += 2) {
+    const uint4 r = s_ur[i >> 1];
+    ub |= __builtin_amdgcn_alignbit(u, u, r.x) & r.y;
+    ub |= __builtin_amdgcn_alignbit(u, u, r.z) & r.w;
   }
   const uint64_t addr = set_base + (uint64_t)ub * cl.es;
   T acc[NC];
-  // operands holding bit 6 (every operand when no bit is serial) in all
-  // cells; without serial bits, the first nfix (lane bits only) are the
-  // product P[0] applied last
-  int k = SL == 0 ? nfix : 0;
-  uint32_t lt = s_lane[min(k, n_ops - 1) * 64];
+  uint32_t lt = s_lane[0];
   auto next = [&](int q) { return s_lane[min(q, n_ops - 1) * 64]; };
-  for (const int k0 = k; k < n_step; k++) {
-    const uint32_t l0 = lt;
-    lt = next(k + 1);
-    cell_op<T, CVT, CB, NC>(acc, k == k0, k, cl, addr, l0);
-  }
-  if (SL == 0 && nfix > 0) {
-    if (nfix == n_step) {
-#pragma unroll
-      for (int c = 0; c < NC; c++) acc[c] = P[0];
-    } else {
-#pragma unroll
-      for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], P[0]);
+  int k = 0;
+  if (SL == 0) {
+    // the product w of the operands without cell bits: the first nfix (lane
+    // bits only) once per angle set, the next n_serial per unit
+    const int n0 = nfix + G.n_serial;
+    T w = P[0];
+    lt = next(nfix);
+    for (k = nfix; k < n0; k++) {
+      const uint32_t l0 = lt;
+      lt = next(k + 1);
+      cell_op<T, CVT, 1>(&w, k == 0, k, cl, addr, l0, false, w);
     }
-  }
-  if (SL >= 1) {
+    for (; k < n_ops; k++) {
+      const uint32_t l0 = lt;
+      lt = next(k + 1);
+      cell_op<T, CVT, NC>(acc, k == n0, k, cl, addr, l0, k == n_ops - 1 && n0 > 0, w);
+    }
+    if (n0 == n_ops) {
+#pragma unroll
+      for (int c = 0; c < NC; c++) acc[c] = w;
+    }
+  } else {
+    const T one = make_c<T>(1.0, 0.0);  // not used: nothing is scaled
+    for (k = 0; k < n_step; k++) {
+      const uint32_t l0 = lt;
+      lt = next(k + 1);
+      cell_op<T, CVT, NC>(acc, k == 0, k, cl, addr, l0, false, one);
+    }
     // sum bit 6 (the highest cell bit)
 #pragma unroll
     for (int c = 0; c < NC / 2; c++) acc[c] = cadd(acc[c], acc[c + NC / 2]);
-  }
-  if (SL == 2) {
-    // operands holding bit 7 but not 6, then sum bit 7
-    const int k1 = n_step + G.n_serial;
-    for (k = n_step; k < k1; k++) {
-      const uint32_t l0 = lt;
-      lt = next(k + 1);
-      cell_op<T, CVT, CB, (SL == 2 ? NC / 2 : 1)>(acc, false, k, cl, addr, l0);
-    }
+    if (SL == 2) {
+      // operands holding bit 7 but not 6, then sum bit 7
+      const int k1 = n_step + G.n_serial;
+      for (k = n_step; k < k1; k++) {
+        const uint32_t l0 = lt;
+        lt = next(k + 1);
+        cell_op<T, CVT, (SL == 2 ? NC / 2 : 1)>(acc, false, k, cl, addr, l0, false, one);
+      }
 #pragma unroll
-    for (int c = 0; c < NC / 4; c++) acc[c] = cadd(acc[c], acc[c + NC / 4]);
-  }
-  if (SL >= 1) {
+      for (int c = 0; c < NC / 4; c++) acc[c] = cadd(acc[c], acc[c + NC / 4]);
+    }
     // the operands without serial bits in the register cells: first the
     // unit-invariant product, then the others
     k = n_step + (SL == 2 ? G.n_serial : 0);
@@ -804,12 +866,12 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane<CB> &cl, u
     for (; k < n_ops; k++) {
       const uint32_t l0 = lt;
       lt = next(k + 1);
-      cell_op<T, CVT, CB, NR>(acc, false, k, cl, addr, l0);
+      cell_op<T, CVT, NR>(acc, false, k, cl, addr, l0, false, one);
     }
   }
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)addr, n_ops);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(addr >> 32), n_ops);
-  cell_finish<T, CB, RB>(acc, cl, n_ops, ls, lane, (char *)(((uint64_t)hi << 32) | lo), out_lane);
+  cell_finish<T, RB, (SL > 0)>(acc, out_cells, ls, lane, (char *)(((uint64_t)hi << 32) | lo), out_lane);
 }
 
 // Setup and units [u0, u1) (one per wave, strided) of a cell-mapped group.
@@ -824,26 +886,31 @@ __device__ __forceinline__ void cell_units(const GI &G, const DevOp *__restrict_
                                            uint32_t *s_tab, uint32_t u0, uint32_t u1,
                                            uint32_t stride, uint32_t set_units, int lane) {
   constexpr int NR = 1 << (CB - SL);
-  CellLane<CB> cl;
-  cell_setup<T, CVT, CB>(G, gops, ctab, data, s_tab, cl);
+  CellLane cl;
+  cell_setup<T, CVT>(G, gops, ctab, s_tab, cl);
   __syncthreads();
   const int nfix = G.n_step0;
   const int kf = SL == 0 ? 0 : G.n_step + (SL == 2 ? G.n_serial : 0);
   const int ls = SL > 0 ? 6 : min(G.L, 6);
-  const uint32_t out_lane = cell_out_lane<CB, CB - SL>(cl, G.n_ops, G.L, ls, lane);
+  const uint32_t out_cells = __builtin_amdgcn_readlane(cl.cells, G.n_ops);
+  const uint32_t out_lane = cell_out_lane<CB - SL>(out_cells, G.L, ls, lane);
   T P[SL > 0 ? NR : 1];
+  P[0] = make_c<T>(1.0, 0.0);
   uint32_t pset = 0xFFFFFFFFu;
   uint64_t set_base = 0;
-  // flat unit f: angle set f / set_units, unit f % set_units
+  // flat unit f: angle set f / set_units, unit f % set_units; set_units is a
+  // power of two
+  const int lg = 31 - __builtin_clz(set_units);
   for (uint32_t f = u0; f < u1; f += stride) {
-    const uint32_t set = f / set_units;
+    const uint32_t set = f >> lg;
     if (set != pset) {
-      set_base = cl.base + (uint64_t)set * cl.sstride;  // no unit part
+      set_base = cell_base(G, gops, data, lane, set);  // no unit part
       for (int k = kf; k < kf + nfix; k++)
-        cell_op<T, CVT, CB, (SL > 0 ? NR : 1)>(P, k == kf, k, cl, set_base, s_tab[k * 64 + lane]);
+        cell_op<T, CVT, (SL > 0 ? NR : 1)>(P, k == kf, k, cl, set_base, s_tab[k * 64 + lane], false, P[0]);
       pset = set;
     }
-    cell_unit<T, CVT, CB, SL>(G, cl, set_base, s_tab, P, f - set * set_units, lane, ls, out_lane);
+    cell_unit<T, CVT, CB, SL>(G, cl, set_base, s_tab, P, f & (set_units - 1u), lane, ls, out_cells,
+                              out_lane);
   }
 }
 
@@ -1408,14 +1475,15 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
   }
 }
 
-// Waves per SIMD asked for: with 3 cell bits and 2 serial bits the kernel
-// fits 5 without spilling (94 registers), 7% faster on the 8-summed-bit groups
-// than the 4 it takes otherwise; the other 3-cell-bit forms fit 4.
-constexpr int cell_waves(int cb, int sl, bool cvt) {
-  return cb == 3 ? (sl == 2 && !cvt ? 5 : 4) : 1;
+// Waves per SIMD asked for with 3 cell bits.  Complex128: 5 with 2 serial bits
+// (89 registers, nothing spilled), 4 otherwise (120; 5 would spill 25 of them:
+// 32 sets of the 30-vertex depth-4 scan 153 ms against 99).  Complex64: 8 (2
+// of 67 registers spilled: the same scan 62.2 ms against 64.0 with 7).
+constexpr int cell_waves(int cb, int sl, bool cvt, bool f32) {
+  return cb != 3 ? 1 : (cvt ? 4 : (f32 ? 8 : (sl == 2 ? 5 : 4)));
 }
 template <class T, bool CVT, int CB, int SL>
-__global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT))) void k_wide_cells(char *__restrict__ data,
+__global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT, sizeof(T) == 8))) void k_wide_cells(char *__restrict__ data,
                                                        const DevGroup *__restrict__ groups,
                                                        const DevOp *__restrict__ ops,
                                                        const int32_t *__restrict__ ctab,
