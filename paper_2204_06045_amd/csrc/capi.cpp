@@ -293,10 +293,13 @@ struct qtn_network {
   std::vector<qtn_tune_rec> tune_log;
   size_t tune_workspace = 0;
   // angle-set batches: a schedule with one data copy per set, rebuilt when
-  // the set count or the plan changes
-  std::unique_ptr<Exec> angle_exec;
-  int angle_sets = 0;
-  uint64_t angle_version = 0;
+  // the set count or the plan changes; [1]: with the plan's order of
+  // operations (derivatives in complex64)
+  struct AngleExec {
+    std::unique_ptr<Exec> exec;
+    int sets = 0;
+    uint64_t version = 0;
+  } angle_exec[2];
 };
 
 namespace {
@@ -384,6 +387,7 @@ struct GroupEnv {
   int var_req = 0, rls_req = 2;           // mapping requested (0: the width rule)
   bool is_small = false;                  // runs inside a workgroup segment
   bool persistent = false;                // the schedule runs in a persistent executor
+  bool in_order = false;                  // complex64 groups keep the plan's operand order
 };
 
 // Device descriptor of one group: chooses its mapping, appends its operands
@@ -688,7 +692,8 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
     const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32;
     return j < rb ? (int)rp[j] : 6 + dg.sl - 1 - (j - rb);
   };
-  if (cell) {
+  dg.in_order = env.in_order && G.prec == 1;
+  if (cell && !dg.in_order) {
     // Operand order.  Every point multiplies all operands, but an operand
     // without cell bits is one value per lane: without serial bits those form
     // a product of their own, which meets the cells once.  Of the others, the
@@ -1116,10 +1121,11 @@ void plan_steps(Schedule &s) {
 // persistent: the schedule runs in a persistent executor (every group inside
 // a workgroup, so no group takes the cell mapping).  size_only: s.total is
 // wanted alone; the programs of single groups are left out and an upper bound
-// of their words is counted.
+// of their words is counted.  in_order: no segment programs, and complex64
+// groups multiply and sum in the plan's order.
 int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *force = nullptr,
                    int singleton_width = 0, int n_sets = 1, bool persistent = false,
-                   bool size_only = false) {
+                   bool size_only = false, bool in_order = false) {
   Schedule &s = *S;
   s = Schedule();
   s.serial = ++g_sched_serial;
@@ -1177,7 +1183,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       // network's hybrid width runs by per-group launches
       const bool heavy = persistent && net->executor == 5 && pl.max_width > net->hybrid_width;
       // segments run as programs unless the network asks for one mapping
-      const bool programs = net->variant == 0 || net->variant == 4;
+      const bool programs = !in_order && (net->variant == 0 || net->variant == 4);
       const int tab_prec = s.prec == kPrecC64 ? 1 : 0;
       const ProgBases pb = {table[tab_prec], table_sstride[tab_prec], arena, arena_sstride,
                             s.scalar_off, s.scalar_sstride, (int)gate_table_elems(net->p)};
@@ -1234,6 +1240,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
         }
         env.is_small = is_small;
         env.persistent = persistent && !heavy;
+        env.in_order = in_order;
         DevGroup dg;
         double gb = 0, gf = 0;
         s.stab_at.push_back(s.stab.size());
@@ -2187,25 +2194,32 @@ int qtn_contract(qtn_network *net, void *d_workspace, size_t bytes, void *hip_st
 
 constexpr int kMaxAngleSets = 1024;
 
-static Exec *angle_exec(qtn_network *net, int n_sets, int *rc) {
-  if (net->angle_exec && net->angle_sets == n_sets && net->angle_version == net->version)
-    return net->angle_exec.get();
+static Exec *angle_exec(qtn_network *net, int n_sets, bool in_order, int *rc) {
+  qtn_network::AngleExec &slot = net->angle_exec[in_order];
+  if (slot.exec && slot.sets == n_sets && slot.version == net->version) return slot.exec.get();
   auto ex = std::make_unique<Exec>();
   qtn_network *one[1] = {net};
   // the same kernel mappings as the network's own schedule (so that every
   // set equals its single-set evaluation), though launched per group
-  *rc = build_schedule(one, 1, &ex->sched, nullptr, 0, n_sets, net->exec->persistent);
+  *rc = build_schedule(one, 1, &ex->sched, nullptr, 0, n_sets, net->exec->persistent, false, in_order);
   if (*rc) return nullptr;
   // per-group launches (the persistent executors run one set)
   ex->lead_per_cone = net->executor == 3;
-  ex->steps = net->executor == 0;
+  // (a step's cell kernels have no form in the plan's order)
+  ex->steps = net->executor == 0 && !in_order;
   ex->spin_limit = net->spin_limit;
-  if (net->angle_exec) ex->rt.take(net->angle_exec->rt);
-  net->angle_exec = std::move(ex);
-  net->angle_sets = n_sets;
-  net->angle_version = net->version;
-  return net->angle_exec.get();
+  if (slot.exec) ex->rt.take(slot.exec->rt);
+  slot.exec = std::move(ex);
+  slot.sets = n_sets;
+  slot.version = net->version;
+  return slot.exec.get();
 }
+
+// A central difference divides the rounding of its two energies by 2 step:
+// at 1e-4, the 1e-7 of complex64 arithmetic becomes 5e-4 of a derivative.  So
+// where a network computes in complex64 every difference is taken with one
+// order of operations, the plan's, whatever the mapping would choose for speed.
+static bool gradient_in_order(const qtn_network *net) { return net->precision != kPrecC128; }
 
 int qtn_angles_workspace(qtn_network *net, int32_t n_sets, size_t *bytes_out) {
   try {
@@ -2214,18 +2228,22 @@ int qtn_angles_workspace(qtn_network *net, int32_t n_sets, size_t *bytes_out) {
     if (n_sets < 1 || n_sets > kMaxAngleSets)
       return set_err(QTN_EINVAL, "n_sets must be in 1.." + std::to_string(kMaxAngleSets));
     int rc = QTN_OK;
-    Exec *ex = angle_exec(net, n_sets, &rc);
+    Exec *ex = angle_exec(net, n_sets, false, &rc);
     if (!ex) return rc;
     *bytes_out = ex->sched.total;
+    if (n_sets == 4 * net->p + 1 && gradient_in_order(net)) {  // a gradient's sets
+      if (!(ex = angle_exec(net, n_sets, true, &rc))) return rc;
+      *bytes_out = std::max<size_t>(*bytes_out, ex->sched.total);
+    }
     return QTN_OK;
   } catch (...) {
     return exception_status();
   }
 }
 
-int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes, void *hip_stream,
-                        int32_t n_sets, const double *gamma, const double *beta, double *zz_out,
-                        double *energy_out, qtn_timing *timing) {
+static int contract_angles(qtn_network *net, void *d_workspace, size_t bytes, void *hip_stream,
+                           int32_t n_sets, bool in_order, const double *gamma, const double *beta,
+                           double *zz_out, double *energy_out, qtn_timing *timing) {
   try {
     if (!net || !gamma || !beta) return set_err(QTN_EINVAL, "NULL argument");
     if (!net->planned) return set_err(QTN_ESTATE, "qtn_plan has not been called");
@@ -2241,7 +2259,7 @@ int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes, void 
                 ang.begin() + (size_t)k * 2 * p + p);
     }
     int rc = QTN_OK;
-    Exec *ex = angle_exec(net, n_sets, &rc);
+    Exec *ex = angle_exec(net, n_sets, in_order, &rc);
     if (!ex) return rc;
     Timer tm;
     tm.on = timing != nullptr;
@@ -2260,6 +2278,13 @@ int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes, void 
   } catch (...) {
     return exception_status();
   }
+}
+
+int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes, void *hip_stream,
+                        int32_t n_sets, const double *gamma, const double *beta, double *zz_out,
+                        double *energy_out, qtn_timing *timing) {
+  return contract_angles(net, d_workspace, bytes, hip_stream, n_sets, false, gamma, beta, zz_out,
+                         energy_out, timing);
 }
 
 int qtn_contract_timed(qtn_network *net, void *d_workspace, size_t bytes, void *hip_stream,
@@ -2729,8 +2754,8 @@ int qtn_energy_gradient(qtn_network *net, void *d_workspace, size_t bytes, void 
       b[(size_t)(1 + 2 * p + 2 * l) * p + l] += step;
       b[(size_t)(2 + 2 * p + 2 * l) * p + l] -= step;
     }
-    const int rc = qtn_contract_angles(net, d_workspace, bytes, hip_stream, n, g.data(), b.data(),
-                                       nullptr, e.data(), nullptr);
+    const int rc = contract_angles(net, d_workspace, bytes, hip_stream, n, gradient_in_order(net),
+                                   g.data(), b.data(), nullptr, e.data(), nullptr);
     if (rc) return rc;
     *energy_out = e[0];
     for (int l = 0; l < p; l++) {

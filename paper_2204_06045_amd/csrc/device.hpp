@@ -45,7 +45,8 @@ struct DevGroup {       // 64 bytes
   uint8_t w, L, n_ops, variant;   // variant: kVar*
   uint8_t rls, sl, lk, n_unit;    // streaming: lane-summed bits, serial bits,
                                   // lane-kept bits, kClsUnit op count
-  uint8_t n_step, n_serial, n_step0, pad;  // n_step0: step-class ops with bit 0
+  uint8_t n_step, n_serial, n_step0;  // n_step0: step-class ops with bit 0
+  uint8_t in_order;     // cells: operands and lane bits in ascending order
   uint8_t level_end[8]; // generic: ops of levels <= l end at level_end[l];
                         // streaming: level_end[0] = uniform-class count; the
                         // n_serial - level_end[0] serial-class ops follow
@@ -72,7 +73,9 @@ enum Variant : uint8_t { kVarGeneric = 0, kVarStream = 1, kVarMfma = 2, kVarCell
 // n_step0 ops of the last of these levels hold no unit bit (sl = 0: hold lane
 // bits only).  With sl = 0, n_serial counts the ops after those that hold no
 // cell bit.  Of the ops in all cells, the first holds the most cell bits and
-// the last the fewest.  n_unit = the most unit-bit runs of any operand or of
+// the last the fewest.  in_order (complex64 arithmetic): the ops of a level
+// keep the plan's order (n_serial = 0 with sl = 0) and the lane-summed bits
+// are added in ascending order.  n_unit = the most unit-bit runs of any operand or of
 // the output.  Tables: the output's at gtab, operand k's at gtab + (k + 1)
 // cell_table_words() (also its stab): kCellURuns / 2 words of unit-bit runs
 // (src | len << 5 | dst << 11, two per word, src counting unit bits; unused

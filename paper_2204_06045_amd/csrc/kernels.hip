@@ -521,9 +521,11 @@ __device__ __forceinline__ uint64_t cell_base(const GI &G, const DevOp *__restri
          (uint64_t)set * (uint64_t)(out ? G.out_sstride : o.sstride);
 }
 
+// ORD below: the order of operations is the plan's (DevGroup::in_order).
+
 // Union bits 0..5 of a lane.
-__device__ __forceinline__ uint32_t cell_lane(uint32_t lane, int L) {
-  if (L < 3 || L > 5) return lane;
+template <bool ORD> __device__ __forceinline__ uint32_t cell_lane(uint32_t lane, int L) {
+  if (ORD || L < 3 || L > 5) return lane;
   return (lane & 3u) | (__builtin_bitreverse32(lane >> 2) >> 26 & 0x3Cu);
 }
 
@@ -531,7 +533,7 @@ __device__ __forceinline__ uint32_t cell_lane(uint32_t lane, int L) {
 // ([k][lane]), then the unit-bit runs of the operands and the output, each as
 // the rotation that brings the unit number's bits to their place and the mask
 // that keeps them ([k][kCellURuns][2]).  Registers: the lane's own constants.
-template <class T, bool CVT>
+template <class T, bool CVT, bool ORD>
 __device__ __forceinline__ void cell_setup(const GI &G, const DevOp *__restrict__ gops,
                                            const int32_t *__restrict__ ctab, uint32_t *s_tab,
                                            CellLane &cl) {
@@ -539,7 +541,7 @@ __device__ __forceinline__ void cell_setup(const GI &G, const DevOp *__restrict_
   for (int k = wave; k < n_ops; k += blockDim.x >> 6) {
     // operand k is the same for the whole wave
     const DevOp &o = gops[__builtin_amdgcn_readfirstlane(k)];
-    s_tab[k * 64 + lane] = pext_runs(cell_lane(lane, G.L), o) * esize<T, CVT>(op_dt(o));
+    s_tab[k * 64 + lane] = pext_runs(cell_lane<ORD>(lane, G.L), o) * esize<T, CVT>(op_dt(o));
   }
   uint2 *s_ur = (uint2 *)(s_tab + n_ops * 64);
   const int32_t *tab = ctab + G.gtab;  // the output's table, then the operands'
@@ -643,32 +645,33 @@ __device__ __forceinline__ void butterfly_step(T *acc) {
 }
 
 // Lane bit summed in step t of a group's lane reduction: with three summed
-// bits and more 5, 4, 3, 2 (as many as there are over two), then 0 and 1.
-__host__ __device__ constexpr int sum_bit(int t, int ls) {
-  return ls < 3 ? t : (t < ls - 2 ? 5 - t : t - (ls - 2));
+// bits and more 5, 4, 3, 2 (as many as there are over two), then 0 and 1; in
+// order, bit t.
+__host__ __device__ constexpr int sum_bit(int t, int ls, bool ord) {
+  return ls < 3 || ord ? t : (t < ls - 2 ? 5 - t : t - (ls - 2));
 }
 // Steps T..LS-1 of the lane reduction of M cells: reduce-scatters while there
 // are two cells and more, then butterflies.
-template <class T, int M, int LS, int STEP>
+template <class T, int M, int LS, bool ORD, int STEP>
 __device__ __forceinline__ void lane_steps(T *acc, int lane) {
   if constexpr (STEP < LS) {
     if constexpr (M > 1)
-      reduce_scatter_step<T, (M >> 1), sum_bit(STEP, LS)>(acc, lane);
+      reduce_scatter_step<T, (M >> 1), sum_bit(STEP, LS, ORD)>(acc, lane);
     else
-      butterfly_step<T, 1, sum_bit(STEP, LS)>(acc);
-    lane_steps<T, (M > 1 ? M / 2 : 1), LS, STEP + 1>(acc, lane);
+      butterfly_step<T, 1, sum_bit(STEP, LS, ORD)>(acc);
+    lane_steps<T, (M > 1 ? M / 2 : 1), LS, ORD, STEP + 1>(acc, lane);
   }
 }
 
 // Element offset, in the output, of a lane after cell_finish: its kept lane
 // bits and the register cell its reduce-scatter bits select.
-template <int RB>
+template <int RB, bool ORD>
 __device__ __forceinline__ uint32_t cell_out_lane(uint32_t out_cells, int L, int ls, int lane) {
-  uint32_t o = L < 6 ? cell_lane(lane, L) >> L : 0u;
+  uint32_t o = L < 6 ? cell_lane<ORD>(lane, L) >> L : 0u;
 #pragma unroll
   for (int t = 0; t < RB; t++)
     if (t < ls)  // the step's lane bit selects the upper half: register bit RB - 1 - t
-      o += ((lane >> sum_bit(t, ls)) & 1) ? 1u << ((out_cells >> (5 * (RB - 1 - t))) & 31u) : 0u;
+      o += ((lane >> sum_bit(t, ls, ORD)) & 1) ? 1u << ((out_cells >> (5 * (RB - 1 - t))) & 31u) : 0u;
   return o;
 }
 
@@ -676,16 +679,16 @@ __device__ __forceinline__ uint32_t cell_out_lane(uint32_t out_cells, int L, int
 // the results at out + out_lane: reduce-scatters over the first q =
 // min(RB, LS) of them (afterwards step t's lane bit selects half of the
 // cells), butterflies for the rest.
-template <class T, int RB, int LS>
+template <class T, int RB, int LS, bool ORD>
 __device__ __forceinline__ void cell_finish_ls(T *acc, uint32_t out_cells, int lane, char *out,
                                                uint32_t out_lane) {
   constexpr int NR = 1 << RB, Q = RB < LS ? RB : LS;
-  lane_steps<T, NR, LS, 0>(acc, lane);
+  lane_steps<T, NR, LS, ORD, 0>(acc, lane);
   // lanes whose summed bits past the reduce-scatters are zero hold the
   // results; acc[i] is register cell i plus the cells out_lane counts
   uint32_t rest = 0;
 #pragma unroll
-  for (int t = Q; t < LS; t++) rest |= 1u << sum_bit(t, LS);
+  for (int t = Q; t < LS; t++) rest |= 1u << sum_bit(t, LS, ORD);
   if (((uint32_t)lane & rest) == 0) {
 #pragma unroll
     for (int i = 0; i < (NR >> Q); i++) {
@@ -697,15 +700,15 @@ __device__ __forceinline__ void cell_finish_ls(T *acc, uint32_t out_cells, int l
     }
   }
 }
-template <class T, int RB, bool SERIAL>
+template <class T, int RB, bool SERIAL, bool ORD>
 __device__ __forceinline__ void cell_finish(T *acc, uint32_t out_cells, int ls, int lane, char *out,
                                             uint32_t out_lane) {
-  if (SERIAL || ls == 6) cell_finish_ls<T, RB, 6>(acc, out_cells, lane, out, out_lane);
-  else if (ls == 1) cell_finish_ls<T, RB, 1>(acc, out_cells, lane, out, out_lane);
-  else if (ls == 2) cell_finish_ls<T, RB, 2>(acc, out_cells, lane, out, out_lane);
-  else if (ls == 3) cell_finish_ls<T, RB, 3>(acc, out_cells, lane, out, out_lane);
-  else if (ls == 4) cell_finish_ls<T, RB, 4>(acc, out_cells, lane, out, out_lane);
-  else cell_finish_ls<T, RB, 5>(acc, out_cells, lane, out, out_lane);
+  if (SERIAL || ls == 6) cell_finish_ls<T, RB, 6, ORD>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 1) cell_finish_ls<T, RB, 1, ORD>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 2) cell_finish_ls<T, RB, 2, ORD>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 3) cell_finish_ls<T, RB, 3, ORD>(acc, out_cells, lane, out, out_lane);
+  else if (ls == 4) cell_finish_ls<T, RB, 4, ORD>(acc, out_cells, lane, out, out_lane);
+  else cell_finish_ls<T, RB, 5, ORD>(acc, out_cells, lane, out, out_lane);
 }
 
 // acc[c] (c < N; first: set to) times an operand whose index holds the cell
@@ -793,7 +796,7 @@ __device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLan
 // scalar is: cell offsets are shifts of one word per operand, no descriptor is
 // read from memory, and the next operand's lane offset is read while this
 // one's loads are under way.
-template <class T, bool CVT, int CB, int SL>
+template <class T, bool CVT, int CB, int SL, bool ORD>
 __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint64_t set_base,
                                           const uint32_t *s_tab, const T *P, uint32_t u, int lane,
                                           int ls, uint32_t out_cells, uint32_t out_lane) {
@@ -827,7 +830,11 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint6
     for (; k < n_ops; k++) {
       const uint32_t l0 = lt;
       lt = next(k + 1);
-      cell_op<T, CVT, NC>(acc, k == n0, k, cl, addr, l0, k == n_ops - 1 && n0 > 0, w);
+      cell_op<T, CVT, NC>(acc, k == n0, k, cl, addr, l0, k == n_ops - 1 && n0 > 0 && !ORD, w);
+    }
+    if (ORD && n0 > 0 && n0 < n_ops) {
+#pragma unroll
+      for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], w);
     }
     if (n0 == n_ops) {
 #pragma unroll
@@ -871,7 +878,7 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint6
   }
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)addr, n_ops);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(addr >> 32), n_ops);
-  cell_finish<T, RB, (SL > 0)>(acc, out_cells, ls, lane, (char *)(((uint64_t)hi << 32) | lo), out_lane);
+  cell_finish<T, RB, (SL > 0), ORD>(acc, out_cells, ls, lane, (char *)(((uint64_t)hi << 32) | lo), out_lane);
 }
 
 // Setup and units [u0, u1) (one per wave, strided) of a cell-mapped group.
@@ -880,20 +887,20 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint6
 // register cell and the angle set; without serial bits, P[0] is the product
 // of the first n_step0 operands, which hold lane bits only.  A wave forms P
 // when its set changes.
-template <class T, bool CVT, int CB, int SL>
+template <class T, bool CVT, int CB, int SL, bool ORD = false>
 __device__ __forceinline__ void cell_units(const GI &G, const DevOp *__restrict__ gops,
                                            const int32_t *__restrict__ ctab, char *__restrict__ data,
                                            uint32_t *s_tab, uint32_t u0, uint32_t u1,
                                            uint32_t stride, uint32_t set_units, int lane) {
   constexpr int NR = 1 << (CB - SL);
   CellLane cl;
-  cell_setup<T, CVT>(G, gops, ctab, s_tab, cl);
+  cell_setup<T, CVT, ORD>(G, gops, ctab, s_tab, cl);
   __syncthreads();
   const int nfix = G.n_step0;
   const int kf = SL == 0 ? 0 : G.n_step + (SL == 2 ? G.n_serial : 0);
   const int ls = SL > 0 ? 6 : min(G.L, 6);
   const uint32_t out_cells = __builtin_amdgcn_readlane(cl.cells, G.n_ops);
-  const uint32_t out_lane = cell_out_lane<CB - SL>(out_cells, G.L, ls, lane);
+  const uint32_t out_lane = cell_out_lane<CB - SL, ORD>(out_cells, G.L, ls, lane);
   T P[SL > 0 ? NR : 1];
   P[0] = make_c<T>(1.0, 0.0);
   uint32_t pset = 0xFFFFFFFFu;
@@ -909,7 +916,7 @@ __device__ __forceinline__ void cell_units(const GI &G, const DevOp *__restrict_
         cell_op<T, CVT, (SL > 0 ? NR : 1)>(P, k == kf, k, cl, set_base, s_tab[k * 64 + lane], false, P[0]);
       pset = set;
     }
-    cell_unit<T, CVT, CB, SL>(G, cl, set_base, s_tab, P, f & (set_units - 1u), lane, ls, out_cells,
+    cell_unit<T, CVT, CB, SL, ORD>(G, cl, set_base, s_tab, P, f & (set_units - 1u), lane, ls, out_cells,
                               out_lane);
   }
 }
@@ -1482,7 +1489,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
 constexpr int cell_waves(int cb, int sl, bool cvt, bool f32) {
   return cb != 3 ? 1 : (cvt ? 4 : (f32 ? 8 : (sl == 2 ? 5 : 4)));
 }
-template <class T, bool CVT, int CB, int SL>
+template <class T, bool CVT, int CB, int SL, bool ORD>
 __global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT, sizeof(T) == 8))) void k_wide_cells(char *__restrict__ data,
                                                        const DevGroup *__restrict__ groups,
                                                        const DevOp *__restrict__ ops,
@@ -1495,8 +1502,8 @@ __global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT, sizeof(T) == 8))) 
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const UnitWalk W = wide_walk(G.n_units * n_sets, nw, w0, gridDim.x, blockIdx.x);
-  cell_units<T, CVT, CB, SL>(G, ops + G.op_begin, ctab, data, s_tab, W.first, W.end, W.stride,
-                             G.n_units, threadIdx.x & 63);
+  cell_units<T, CVT, CB, SL, ORD>(G, ops + G.op_begin, ctab, data, s_tab, W.first, W.end, W.stride,
+                                  G.n_units, threadIdx.x & 63);
 }
 
 template <class T, bool CVT>
@@ -2049,11 +2056,17 @@ void launch_wide_t(const DevGroup &hg, uint32_t units, char *d, const DevGroup *
                    stab, uperm, group, n_sets);
   } else if (hg.variant == kVarCell) {
     const size_t lds = cell_lds_words(hg.n_ops) * sizeof(uint32_t);
-#define QTN_CELL_LAUNCH(CB, SL)                                                                  \
+#define QTN_CELL_KERNEL(CB, SL, ORD)                                                             \
   do {                                                                                           \
-    const int nb = wide_grid(k_wide_cells<T, CVT, CB, SL>, lds, units);                         \
-    QTN_LAUNCH_LDS(t0, t1, (k_wide_cells<T, CVT, CB, SL>), dim3(nb), dim3(kBlock), lds, s, d,   \
+    const int nb = wide_grid(k_wide_cells<T, CVT, CB, SL, ORD>, lds, units);                    \
+    QTN_LAUNCH_LDS(t0, t1, (k_wide_cells<T, CVT, CB, SL, ORD>), dim3(nb), dim3(kBlock), lds, s, d, \
                    groups, ops, stab, uperm, group, n_sets);                                      \
+  } while (0)
+#define QTN_CELL_LAUNCH(CB, SL)                                  \
+  do {                                                           \
+    constexpr bool kF32 = sizeof(T) == 8;                        \
+    if (kF32 && hg.in_order) QTN_CELL_KERNEL(CB, SL, kF32);      \
+    else QTN_CELL_KERNEL(CB, SL, false);                         \
   } while (0)
     if (hg.rls == 2 && hg.sl == 0) QTN_CELL_LAUNCH(2, 0);
     else if (hg.rls == 2 && hg.sl == 1) QTN_CELL_LAUNCH(2, 1);
@@ -2065,6 +2078,7 @@ void launch_wide_t(const DevGroup &hg, uint32_t units, char *d, const DevGroup *
     else if (hg.sl == 1) QTN_CELL_LAUNCH(4, 1);
     else QTN_CELL_LAUNCH(4, 2);
 #undef QTN_CELL_LAUNCH
+#undef QTN_CELL_KERNEL
   } else {
     const int nb = wide_grid(k_wide_generic<T, CVT>, 0, units);
     QTN_LAUNCH(t0, t1, (k_wide_generic<T, CVT>), dim3(nb), dim3(kBlock), s, d, groups, ops, stab,

@@ -102,6 +102,38 @@ def test_step_launches_equal_group_launches(qtn, gpu, cfg, mixed, prec):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("cfg", [
+    dict(small_width=8), dict(small_width=8, max_levels=2),
+    dict(small_width=8, max_levels=4), dict(small_width=8, max_levels=5),
+    dict(small_width=8, max_levels=7), dict(small_width=8, variant=4, lane_sum_bits=2),
+    dict(small_width=8, variant=4, lane_sum_bits=4), dict(small_width=12, executor=2),
+])
+@pytest.mark.parametrize("prec,mixed", [(1, 18), (2, 10)])
+def test_derivatives_in_plan_order(qtn, gpu, cfg, prec, mixed):
+    # the differences of a gradient in complex64 run in the plan's order of
+    # operations.  Bounds: float32 energies to 1e-6 |E| (about ten roundings of
+    # 6e-8 that add up), which a central difference with step h divides by 2h
+    # (here twice that, for the difference of two)
+    inst = qs.instance(16, 3, 3, 0, 2)
+    g, b = inst["angles"][0]
+    h = 1e-2
+    ref = qtn.Network(16, inst["edges"], g, b)
+    ref.plan(0)
+    want = ref.energy_gradient(g, b, h)
+    net = qtn.Network(16, inst["edges"], g, b, mixed_width=mixed, **cfg)
+    net.plan(prec)
+    ws = qtn.workspace(net.angles_workspace(4 * 3 + 1))
+    e, dg, db = net.energy_gradient(g, b, h, ws)
+    print(cfg, prec, e, want[0], flush=True)
+    tol = 1e-6 * max(1.0, abs(want[0]))
+    assert abs(e - want[0]) <= tol
+    assert abs(e - net.contract_angles([g], [b])[1][0]) <= 2 * tol
+    for x, y in ((dg, want[1]), (db, want[2])):
+        assert np.max(np.abs(x - y)) <= tol / h
+    net.close()
+    ref.close()
+
+
 @pytest.mark.parametrize("n,p", [(12, 2), (16, 3), (16, 4), (20, 3)])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_small_graphs_all_configs(qtn, orc, gpu, n, p, prec):
