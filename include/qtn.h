@@ -567,6 +567,9 @@ int qtn_bucket_get_info(const qtn_bucket *b, qtn_bucket_info *out);
  *   d_workspace  device memory of at least workspace_bytes, 256-byte
  *                aligned; the descriptors are copied into it on the stream,
  *                so it must stay untouched until the kernel has run
+ * After some calls the library keeps the descriptors in device memory of its
+ * own (workspace_bytes, until qtn_bucket_free), which later calls on that
+ * device use instead of the copy; calls under stream capture do not allocate.
  * Errors: QTN_EINVAL, QTN_ENOMEM (buffer or workspace too small),
  *         QTN_EDEVICE.
  */

@@ -266,3 +266,62 @@ def test_operand_over_4gib(qtn, orc, gpu):
     b.close()
     del data, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("ops,out,variant", [
+    ([[0, 1, 2], [0, 3]], [2, 3], 0),                                    # one wave
+    ([list(range(12)), [0, 1, 12, 13]], list(range(2, 14)), 0),          # cells
+    ([[0, 1, 2, 3] + list(range(4, 10)), [0, 1, 2, 3] + list(range(10, 15))],
+     list(range(4, 15)), 3),                                             # matrix form
+])
+def test_repeated_calls_keep_descriptors(qtn, gpu, ops, out, variant):
+    """Many calls of one bucket, plain, on a second stream, captured and from
+    threads, equal the first one bit for bit, before and after the library
+    keeps the descriptors in memory of its own (from then on a call leaves its
+    workspace alone)."""
+    import threading
+    b = qtn.Bucket(ops, out, variant=variant)
+    data, _ = _device_data(qtn, b, np.random.default_rng(5), 0)
+    res = data[b.out_offset:b.out_offset + (16 << len(out))]
+    b.contract(data)
+    torch.cuda.synchronize()
+    first = res.clone()
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert torch.equal(res, first), what
+        res.zero_()
+        torch.cuda.synchronize()
+
+    check("first")
+    side = torch.cuda.Stream()
+
+    def captured(what):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            b.contract(data, stream=torch.cuda.current_stream())
+        for k in range(3):
+            g.replay()
+            check(f"{what} replay {k}")
+
+    captured("before")
+    for k in range(40):  # the copy is made while these are queued
+        b.contract(data, stream=side if k % 3 == 2 else None)
+        if k % 3:
+            torch.cuda.synchronize()
+    check("queued")
+    ws = b.workspace()
+    ws.fill_(0xEE)
+    for stream in (None, side):
+        b.contract(data, stream=stream)
+        check("kept")
+    captured("after")
+    assert bool((ws == 0xEE).all())
+    threads = [threading.Thread(target=lambda: [b.contract(data, stream=side) for _ in range(20)])
+               for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    check("threads")
+    b.close()
