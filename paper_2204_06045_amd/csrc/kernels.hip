@@ -977,7 +977,17 @@ static_assert(mm_lds_bytes<float2, 4>() <= kStreamMaxOps * 64 * 4,
 // k's table (at its stab) holds kMmTM row (side A) or kMmTN column (side B)
 // offsets, then 2^L summed-index offsets.  Unit bits (uperm): m bits, then n
 // bits, then batch bits.
-template <class T, bool CVT, int NCB>
+//
+// Bound: a round trip per chunk (table entries, then elements) with the matrix
+// cores idle, unless the wave has products of its own to set beside it.  So
+// the first operand's addresses are formed once per tile, and with PIPE (own
+// launches; the workgroup kernels have no registers for it) a chunk's elements
+// are loaded while the matrix cores work on the chunk before it.  A 2048 x
+// 4096 x 256 product: complex128 319 -> 249 us (52 TFLOP/s of 3M products; a
+// library FP64 product reaches 68 on this card), complex64 190 -> 147 us; 512 x
+// 512 x 256: 69 -> 42 us and 59 -> 31 us.  Reading the LDS factors one step
+// ahead as well did not pay (268 us).
+template <class T, bool CVT, int NCB, bool PIPE>
 __device__ void mm_tile(const GI &G, const DevOp *__restrict__ gops, const int32_t *__restrict__ stab,
                         const uint8_t *__restrict__ bits, char *__restrict__ data, char *lds,
                         uint32_t tile, uint32_t set) {
@@ -990,7 +1000,10 @@ __device__ void mm_tile(const GI &G, const DevOp *__restrict__ gops, const int32
   const uint32_t M = 1u << nM, N = 1u << nN, K = 1u << L;
   const uint32_t mt = (M + kMmTM - 1) / kMmTM, nt = (N + TN - 1) / TN;
   const uint32_t bt = tile / (mt * nt), rem = tile % (mt * nt);
-  const uint32_t mi = rem / nt, ni = rem % nt;
+  // tiles in bands of 8 rows, column by column: the 96 or so that an XCD works
+  // on at a time share their rows and columns in its L2
+  const uint32_t gm = mt < 8 ? mt : 8, band = rem / (gm * nt), in_band = rem % (gm * nt);
+  const uint32_t mi = band * gm + in_band % gm, ni = in_band / gm;
   const uint32_t m0 = mi * kMmTM, n0 = ni * TN;
   // union bits of the tile: batch bits, and the m (n) bits above the
   // in-tile ones (a tile spans the lowest 6 m bits and TNB n bits)
@@ -1015,17 +1028,42 @@ __device__ void mm_tile(const GI &G, const DevOp *__restrict__ gops, const int32
   const int kl = tid & (KC - 1), rl = tid >> kb;
   const int pa = kMmTM / RP, pb = (TN + RP - 1) / RP;
   const int klt = (uint32_t)kl < K ? kl : 0;  // table index of kl (2^L < KC: padding)
-  for (uint32_t k0 = 0; k0 < K; k0 += (uint32_t)KC) {
-    const uint32_t k = k0 + (uint32_t)kl;
-    // side A: rows rl + RP j
-    T va[AP];
-    bool oka[AP];
+  // side A: rows rl + RP j; side B: columns rl + RP j.  Elements past the
+  // ranges (only where 2^L < KC, M < 64 or N < TN) are read at offset 0 and
+  // stored as zeros.
+  T va[AP], vb[NCB];
+  uint32_t oka = 0, okb = 0;
 #pragma unroll
-    for (int j = 0; j < AP; j++) {
-      oka[j] = j < pa && m0 + (uint32_t)(rl + RP * j) < M && k < K;
-      va[j] = make_c<T>(1.0, 0.0);
-    }
-    for (int q = 0; q < na; q++) {
+  for (int j = 0; j < AP; j++)
+    oka |= (uint32_t)(j < pa && m0 + (uint32_t)(rl + RP * j) < M && (uint32_t)kl < K) << j;
+  const int c0 = rl < TN ? rl : 0;
+#pragma unroll
+  for (int j = 0; j < NCB; j++) {
+    const int col = rl + RP * j;
+    okb |= (uint32_t)(j < pb && col < TN && n0 + (uint32_t)col < N && (uint32_t)kl < K) << j;
+  }
+  // the thread's part of the first operand's offset on each side
+  const int32_t *tA = stab + gops[0].stab, *tB = stab + gops[na].stab;
+  const uint32_t eA = base[0] + (uint32_t)tA[rl] + (uint32_t)tA[kMmTM + klt];
+  const uint32_t eB = base[na] + (uint32_t)tB[c0] + (uint32_t)tB[kMmTN + klt];
+  const char *pA = opnd(data, gops[0], set), *pB = opnd(data, gops[na], set);
+  const int dA = op_dt(gops[0]), dB = op_dt(gops[na]);
+  // of its rows and columns (uniform), and of a row or column that exists
+  uint32_t jA[AP], jB[NCB];
+#pragma unroll
+  for (int j = 0; j < AP; j++) jA[j] = (uint32_t)tA[j < pa ? RP * j : 0];
+#pragma unroll
+  for (int j = 0; j < NCB; j++) jB[j] = (uint32_t)tB[j < pb ? RP * j : 0];
+  auto at = [](uint32_t ok, int j, uint32_t off) { return off & (0u - ((ok >> j) & 1u)); };
+  auto load = [&](uint32_t k0) {
+    const uint32_t uA = eA + (uint32_t)tA[kMmTM + k0], uB = eB + (uint32_t)tB[kMmTN + k0];
+#pragma unroll
+    for (int j = 0; j < AP; j++)
+      va[j] = ld_elem<T, CVT>(pA, at(oka, j, uA + jA[j]), dA);
+#pragma unroll
+    for (int j = 0; j < NCB; j++)
+      vb[j] = ld_elem<T, CVT>(pB, at(okb, j, uB + jB[j]), dB);
+    for (int q = 1; q < na; q++) {
       const DevOp &o = gops[q];
       const int32_t *t = stab + o.stab;
       const char *p = opnd(data, o, set);
@@ -1034,38 +1072,37 @@ __device__ void mm_tile(const GI &G, const DevOp *__restrict__ gops, const int32
                           (uint32_t)t[kMmTM + k0];
 #pragma unroll
       for (int j = 0; j < AP; j++)
-        if (oka[j]) va[j] = cmul(va[j], ld_elem<T, CVT>(p, e0 + (uint32_t)t[RP * j], dt));
+        va[j] = cmul(va[j], ld_elem<T, CVT>(p, at(oka, j, e0 + (uint32_t)t[j < pa ? RP * j : 0]), dt));
     }
-#pragma unroll
-    for (int j = 0; j < AP; j++)
-      if (j < pa) sA[(rl + RP * j) * (kMmKC + 1) + kl] = oka[j] ? va[j] : make_c<T>(0.0, 0.0);
-    // side B: columns rl + RP j
-    T vb[NCB];
-    bool okb[NCB];
-#pragma unroll
-    for (int j = 0; j < NCB; j++) {
-      const int col = rl + RP * j;
-      okb[j] = j < pb && col < TN && n0 + (uint32_t)col < N && k < K;
-      vb[j] = make_c<T>(1.0, 0.0);
-    }
-    for (int q = na; q < na + nb; q++) {
+    for (int q = na + 1; q < na + nb; q++) {
       const DevOp &o = gops[q];
       const int32_t *t = stab + o.stab;
       const char *p = opnd(data, o, set);
       const int dt = op_dt(o);
-      const int c0 = rl < TN ? rl : 0;
       const uint32_t e0 = base[q] + (uint32_t)t[c0] + (uint32_t)t[kMmTN + klt] +
                           (uint32_t)t[kMmTN + k0];
 #pragma unroll
       for (int j = 0; j < NCB; j++)
-        if (okb[j]) vb[j] = cmul(vb[j], ld_elem<T, CVT>(p, e0 + (uint32_t)t[RP * j], dt));
+        vb[j] = cmul(vb[j], ld_elem<T, CVT>(p, at(okb, j, e0 + (uint32_t)t[j < pb ? RP * j : 0]), dt));
     }
+  };
+  auto kept = [](uint32_t ok, int j, T v) {
+    if (!((ok >> j) & 1u)) v.x = v.y = (R)0;
+    return v;
+  };
+  if (PIPE) load(0);
+  for (uint32_t k0 = 0; k0 < K; k0 += (uint32_t)KC) {
+    if (!PIPE) load(k0);
+#pragma unroll
+    for (int j = 0; j < AP; j++)
+      if (j < pa) sA[(rl + RP * j) * (kMmKC + 1) + kl] = kept(oka, j, va[j]);
 #pragma unroll
     for (int j = 0; j < NCB; j++) {
       const int col = rl + RP * j;
-      if (j < pb && col < TN) sB[kl * (TN + 1) + col] = okb[j] ? vb[j] : make_c<T>(0.0, 0.0);
+      if (j < pb && col < TN) sB[kl * (TN + 1) + col] = kept(okb, j, vb[j]);
     }
     __syncthreads();
+    if (PIPE && k0 + (uint32_t)KC < K) load(k0 + (uint32_t)KC);
     for (int kk = 0; kk < KC; kk += 4) {
       const T a = sA[(wave * 16 + (lane & 15)) * (kMmKC + 1) + kk + (lane >> 4)];
       const R ar = (R)a.x, ai = (R)a.y, as = ar + ai;
@@ -1379,10 +1416,10 @@ __device__ __forceinline__ void run_group(const GI &G, int g, const DevOp *__res
     // keeps the accumulators, and so these kernels' registers, few)
     if (G.cvt)
       for (uint32_t u = u0; u < u1; u++)
-        mm_tile<float2, true, 1>(G, gops, stab, ub, data, (char *)s_lane, u, set);
+        mm_tile<float2, true, 1, false>(G, gops, stab, ub, data, (char *)s_lane, u, set);
     else
       for (uint32_t u = u0; u < u1; u++)
-        mm_tile<float2, false, 1>(G, gops, stab, ub, data, (char *)s_lane, u, set);
+        mm_tile<float2, false, 1, false>(G, gops, stab, ub, data, (char *)s_lane, u, set);
   } else if (G.variant == kVarStream) {
     stream_setup(G, gops, s_lane);
     __syncthreads();
@@ -1605,7 +1642,9 @@ __global__ __launch_bounds__(kStepMaxThreads, 4) void k_step(char *__restrict__ 
 
 // Waves per SIMD the matrix-form kernel is compiled for: three accumulator
 // sets of NCB blocks (3M) fill many registers, and left alone the compiler
-// spends more on staging than this occupancy allows.
+// spends more on staging than this occupancy allows.  Complex128, 4 blocks: 3
+// waves (5 registers spilled, outside the loop) take 249 us for the product
+// above, 2 waves 266.
 template <class T, int NCB> constexpr int mm_waves() {
   return sizeof(T) == 8 ? (NCB == 4 ? 4 : 5) : (NCB == 4 ? 3 : 4);
 }
@@ -1622,7 +1661,7 @@ __global__ __launch_bounds__(kBlock, (mm_waves<T, NCB>())) void k_wide_mfma(char
   const UnitWalk W = wide_walk(G.n_units * n_sets, 1, 0, gridDim.x, blockIdx.x);
   for (uint32_t f = W.first; f < W.end; f += W.stride) {
     const uint32_t set = f / G.n_units;
-    mm_tile<T, CVT, NCB>(G, ops + G.op_begin, stab, uperm + 32 * gid, data, s_tile,
+    mm_tile<T, CVT, NCB, true>(G, ops + G.op_begin, stab, uperm + 32 * gid, data, s_tile,
                          f - set * G.n_units, set);
   }
 }
