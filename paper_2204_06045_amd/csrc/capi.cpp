@@ -453,6 +453,7 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
   std::vector<int> order(G.ops.size());
   std::vector<int> cls(G.ops.size(), 0);
   for (size_t k = 0; k < G.ops.size(); k++) order[k] = (int)k;
+  dg.in_order = cell && env.in_order && G.prec == 1;
   if (mfma) {
     dg.variant = kVarMfma;
     // [side A..., side B...]
@@ -612,13 +613,22 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
         const int lv = G.L <= 6 ? 0 : ((m >> 6) & 1u) ? 0 : (G.L > 7 && ((m >> 7) & 1u)) ? 1 : 2;
         for (int t = lv; t < dg.sl; t++) held[k] += (m >> (6 + t)) & 1u;
       }
+      // (in order, without serial bits: and the fewest products, each load
+      // counted as two; an operand is multiplied once per lane while no
+      // operand up to it holds a cell bit, once per cell from there on)
+      const bool count_products = dg.in_order && dg.sl == 0;
       for (int j = 0; j < rb; j++) {
         size_t bi = 0;
         double best_cost = -1;
         for (size_t q = 0; q < sc.size(); q++) {
           double cost = 0;
-          for (size_t k = 0; k < G.ops.size(); k++)
-            cost += std::ldexp(1.0, (int)held[k] + (int)((G.ops[k].mask >> sc[q].second) & 1u));
+          bool split = false;
+          for (size_t k = 0; k < G.ops.size(); k++) {
+            const int h = (int)held[k] + (int)((G.ops[k].mask >> sc[q].second) & 1u);
+            split |= h > 0;
+            cost += std::ldexp(1.0, h);
+            if (count_products) cost += split && (G.ops[k].mask & ~63u) ? 0.5 * (1 << rb) : 0.5;
+          }
           if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             bi = q;
@@ -692,8 +702,7 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
     const uint8_t *rp = s.uperm.data() + s.uperm.size() - 32;
     return j < rb ? (int)rp[j] : 6 + dg.sl - 1 - (j - rb);
   };
-  dg.in_order = env.in_order && G.prec == 1;
-  if (cell && !dg.in_order) {
+  if (cell) {
     // Operand order.  Every point multiplies all operands, but an operand
     // without cell bits is one value per lane: without serial bits those form
     // a product of their own, which meets the cells once.  Of the others, the
@@ -705,7 +714,14 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
       return n;
     };
     auto most_first = [&](int x, int y) { return held(x) > held(y); };
-    if (dg.sl == 0) {
+    if (dg.in_order) {
+      // the plan's order: of the operands without cell bits, those that come
+      // before every other one are multiplied once per lane
+      if (dg.sl == 0) {
+        const auto first = order.begin() + dg.n_step0;
+        dg.n_serial = (uint8_t)(std::find_if(first, order.end(), [&](int k) { return held(k) > 0; }) - first);
+      }
+    } else if (dg.sl == 0) {
       const auto first = order.begin() + dg.n_step0;
       const auto full = std::stable_partition(first, order.end(), [&](int k) { return held(k) == 0; });
       dg.n_serial = (uint8_t)(full - first);
@@ -1065,8 +1081,10 @@ void plan_steps(Schedule &s) {
   // a task: 17 (20 vertices, depth 3) 286 us against 355; 469 (27 sets of a
   // 22-vertex one) 333 against 430; 3,900 (40 vertices, mixed precision) 8.7
   // ms against 10.3; 21,500 (17 sets of a depth-4 one) 8.7 ms against 8.5;
-  // 87,000 (32 sets of the 30-vertex one) 108 ms against 100.  A schedule
-  // that is mostly other mappings keeps its streams.
+  // 87,000 (32 sets of the 30-vertex one) 108 ms against 100.  (With the cell
+  // units as they are now the first four take 170 us, 288 us, 6.0 ms and, on
+  // streams, 8.7 ms.)  A schedule that is mostly other mappings keeps its
+  // streams.
   if (n_tasks == 0 || n_other * 8 > n_tasks || units > kStepMaxUnits * (double)n_tasks) return;
   s.steps.resize(n_steps);
   std::vector<std::vector<const Task *>> in_step(n_steps);
@@ -2310,8 +2328,13 @@ static Exec *batch_exec(qtn_network *const *nets, int32_t n, int *rc) {
   auto it = g_batch.find(key);
   if (it != g_batch.end()) return it->second.get();
   auto ex = std::make_unique<Exec>();
+  // complex64: in the plan's order.  At arbitrary angles a graph's <ZZ> can all
+  // be near zero (rms 5e-4 among 16 cubic graphs of depths 2 to 4), and the
+  // rounding of 1e-8 that another order brings is 6e-5 of them.  That order
+  // costs 24.0 ms for those 16 graphs, the fastest one 18.4
   *rc = build_schedule(nets, n, &ex->sched, nullptr, 0, 1,
-                       nets[0]->executor != 1 && nets[0]->executor != 3);
+                       nets[0]->executor != 1 && nets[0]->executor != 3, false,
+                       nets[0]->precision == kPrecC64);
   if (*rc) return nullptr;
   // batches default to the persistent executor
   ex->persistent = nets[0]->executor != 1 && nets[0]->executor != 3;

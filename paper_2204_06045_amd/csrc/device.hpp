@@ -74,9 +74,10 @@ enum Variant : uint8_t { kVarGeneric = 0, kVarStream = 1, kVarMfma = 2, kVarCell
 // bits only).  With sl = 0, n_serial counts the ops after those that hold no
 // cell bit.  Of the ops in all cells, the first holds the most cell bits and
 // the last the fewest.  in_order (complex64 arithmetic): the ops of a level
-// keep the plan's order (n_serial = 0 with sl = 0) and the lane-summed bits
-// are added in ascending order.  n_unit = the most unit-bit runs of any operand or of
-// the output.  Tables: the output's at gtab, operand k's at gtab + (k + 1)
+// keep the plan's order (sl = 0: n_serial counts the ops without cell bits
+// that come before all with some, and the first n_step0 multiply last) and the
+// lane-summed bits are added in ascending order.  n_unit = the most unit-bit
+// runs of any operand or of the output.  Tables: the output's at gtab, operand k's at gtab + (k + 1)
 // cell_table_words() (also its stab): kCellURuns / 2 words of unit-bit runs
 // (src | len << 5 | dst << 11, two per word, src counting unit bits; unused
 // runs 0) giving the unit part of the tensor's index, then the cell word: bits

@@ -818,27 +818,29 @@ __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint6
   int k = 0;
   if (SL == 0) {
     // the product w of the operands without cell bits: the first nfix (lane
-    // bits only) once per angle set, the next n_serial per unit
+    // bits only) once per angle set, the next n_serial per unit (in order:
+    // those that precede every operand with cell bits, and P multiplies last)
     const int n0 = nfix + G.n_serial;
     T w = P[0];
     lt = next(nfix);
     for (k = nfix; k < n0; k++) {
       const uint32_t l0 = lt;
       lt = next(k + 1);
-      cell_op<T, CVT, 1>(&w, k == 0, k, cl, addr, l0, false, w);
+      cell_op<T, CVT, 1>(&w, ORD ? k == nfix : k == 0, k, cl, addr, l0, false, w);
+    }
+    if (ORD || n0 == n_ops) {  // in order and n0 > nfix: w stands in every cell
+#pragma unroll
+      for (int c = 0; c < NC; c++) acc[c] = w;
     }
     for (; k < n_ops; k++) {
       const uint32_t l0 = lt;
       lt = next(k + 1);
-      cell_op<T, CVT, NC>(acc, k == n0, k, cl, addr, l0, k == n_ops - 1 && n0 > 0 && !ORD, w);
+      cell_op<T, CVT, NC>(acc, ORD ? k == nfix : k == n0, k, cl, addr, l0,
+                          !ORD && k == n_ops - 1 && n0 > 0, w);
     }
-    if (ORD && n0 > 0 && n0 < n_ops) {
+    if (ORD && nfix > 0 && nfix < n_ops) {
 #pragma unroll
-      for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], w);
-    }
-    if (n0 == n_ops) {
-#pragma unroll
-      for (int c = 0; c < NC; c++) acc[c] = w;
+      for (int c = 0; c < NC; c++) acc[c] = cmul(acc[c], P[0]);
     }
   } else {
     const T one = make_c<T>(1.0, 0.0);  // not used: nothing is scaled
@@ -1522,12 +1524,14 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
 // Waves per SIMD asked for with 3 cell bits.  Complex128: 5 with 2 serial bits
 // (89 registers, nothing spilled), 4 otherwise (120; 5 would spill 25 of them:
 // 32 sets of the 30-vertex depth-4 scan 153 ms against 99).  Complex64: 8 (2
-// of 67 registers spilled: the same scan 62.2 ms against 64.0 with 7).
-constexpr int cell_waves(int cb, int sl, bool cvt, bool f32) {
-  return cb != 3 ? 1 : (cvt ? 4 : (f32 ? 8 : (sl == 2 ? 5 : 4)));
+// of 67 registers spilled: the same scan 62.2 ms against 64.0 with 7); in the
+// plan's order 6 (72 registers; 8 would spill 9 of them, 16 cubic graphs' own
+// launches 18.5 ms against 16.6).
+constexpr int cell_waves(int cb, int sl, bool cvt, bool f32, bool ord) {
+  return cb != 3 ? 1 : (cvt ? 4 : (f32 ? (ord && sl < 2 ? 6 : 8) : (sl == 2 ? 5 : 4)));
 }
 template <class T, bool CVT, int CB, int SL, bool ORD>
-__global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT, sizeof(T) == 8))) void k_wide_cells(char *__restrict__ data,
+__global__ __launch_bounds__(kBlock, (cell_waves(CB, SL, CVT, sizeof(T) == 8, ORD))) void k_wide_cells(char *__restrict__ data,
                                                        const DevGroup *__restrict__ groups,
                                                        const DevOp *__restrict__ ops,
                                                        const int32_t *__restrict__ ctab,
