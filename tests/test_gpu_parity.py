@@ -134,6 +134,26 @@ def test_derivatives_in_plan_order(qtn, gpu, cfg, prec, mixed):
     ref.close()
 
 
+@pytest.mark.parametrize("cfg", [dict(), dict(small_width=8), dict(small_width=8, max_levels=5)])
+def test_complex64_batches_in_plan_order(qtn, gpu, cfg):
+    # a complex64 batch of per-group launches and the sets of a gradient run
+    # the same groups in the same order of operations: equal energies
+    nets, alone = [], []
+    for n, p in ((14, 3), (16, 2)):
+        inst = qs.instance(n, 3, p, 0, 1)
+        g, b = inst["angles"][0]
+        net = qtn.Network(n, inst["edges"], g, b, executor=1, **cfg)
+        net.plan(1)
+        alone.append(net.energy_gradient(g, b, 1e-2)[0])
+        nets.append(net)
+    handles = [net.h for net in nets]
+    ws = qtn.workspace(qtn.qtn_batch_workspace(handles))
+    energy = qtn.qtn_contract_batch(handles, sum(net.m for net in nets), ws)[1]
+    assert np.array_equal(np.asarray(energy), np.asarray(alone))
+    for net in nets:
+        net.close()
+
+
 @pytest.mark.parametrize("n,p", [(12, 2), (16, 3), (16, 4), (20, 3)])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_small_graphs_all_configs(qtn, orc, gpu, n, p, prec):
