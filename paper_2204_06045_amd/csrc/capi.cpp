@@ -1842,6 +1842,12 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
                                    std::to_string(s.total));
   if ((uintptr_t)ws % 256) return set_err(QTN_EINVAL, "workspace must be 256-byte aligned");
   if (!set_angles && s.n_sets != 1) return set_err(QTN_EINVAL, "angle sets missing");
+  // a call waits for its results, which a capture does not allow: refused
+  // before anything of it joins the caller's graph
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) (void)hipGetLastError();
+  else if (capture != hipStreamCaptureStatusNone)
+    return set_err(QTN_EDEVICE, "the stream is being captured, and the call waits for its results");
   const int n_res = (2 * s.n_cones + s.n_nets) * s.n_sets;
   int rc = ensure_runtime(rt, n_streams, n_res + s.n_angles * s.n_sets);
   if (rc) return rc;
@@ -1869,7 +1875,7 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
   if (!rt.dev_desc || rt.dev_serial != s.serial) {
     QTN_HIP(hipMemcpyAsync(base + s.off_desc, s.desc_blob.data(), n_desc, hipMemcpyHostToDevice,
                            rt.main));
-    rt.dev_serial = s.serial;
+    rt.dev_serial = 0;  // known to be there once the stream has been waited for
   }
   double *angles = rt.pinned + n_res;
   if (set_angles) {
@@ -1902,6 +1908,7 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
     QTN_HIP(hipGraphLaunch(rt.exec, rt.main));
   }
   QTN_HIP(hipStreamSynchronize(rt.main));
+  rt.dev_serial = s.serial;
   if (X.persistent && rt.pinned_err[0] != 0)
     return set_err(QTN_EDEVICE, X.dataflow
                                     ? "persistent executor: a dependency wait exceeded its bound"
