@@ -629,8 +629,15 @@ __device__ __forceinline__ void reduce_scatter_step(T *acc, int lane) {
       acc[i].x = swap_sum<BIT>(acc[i].x, acc[i + HALF].x);
       acc[i].y = swap_sum<BIT>(acc[i].y, acc[i + HALF].y);
     } else {
-      const T keep = up ? acc[i + HALF] : acc[i];
-      const T send = up ? acc[i] : acc[i + HALF];
+      // selected word by word: choosing between the two array elements as a
+      // whole makes the compiler choose an address, which keeps the cells in
+      // scratch memory
+      const T lo = acc[i], hi = acc[i + HALF];
+      T keep, send;
+      keep.x = up ? hi.x : lo.x;
+      keep.y = up ? hi.y : lo.y;
+      send.x = up ? lo.x : hi.x;
+      send.y = up ? lo.y : hi.y;
       acc[i] = cadd(keep, xor_lane<(BIT < 4 ? BIT : 0)>(send));
     }
   }
@@ -1525,8 +1532,9 @@ __global__ __launch_bounds__(kBlock) void k_wide_stream(char *__restrict__ data,
 // (89 registers, nothing spilled), 4 otherwise (120; 5 would spill 25 of them:
 // 32 sets of the 30-vertex depth-4 scan 153 ms against 99).  Complex64: 8 (2
 // of 67 registers spilled: the same scan 62.2 ms against 64.0 with 7); in the
-// plan's order 6 (72 registers; 8 would spill 9 of them, 16 cubic graphs' own
-// launches 18.5 ms against 16.6).
+// plan's order 6 (68 registers; 8 would spill 2 of them: the gradient of a
+// 16-vertex depth-4 network 8.27 ms against 8.14, a batch of 16 cubic graphs
+// 19.7 against 19.8).
 constexpr int cell_waves(int cb, int sl, bool cvt, bool f32, bool ord) {
   return cb != 3 ? 1 : (cvt ? 4 : (f32 ? (ord && sl < 2 ? 6 : 8) : (sl == 2 ? 5 : 4)));
 }
