@@ -613,22 +613,13 @@ int describe_group(const Group &G, const ConePlan &pl, const GroupEnv &env, Sche
         const int lv = G.L <= 6 ? 0 : ((m >> 6) & 1u) ? 0 : (G.L > 7 && ((m >> 7) & 1u)) ? 1 : 2;
         for (int t = lv; t < dg.sl; t++) held[k] += (m >> (6 + t)) & 1u;
       }
-      // (in order, without serial bits: and the fewest products, each load
-      // counted as two; an operand is multiplied once per lane while no
-      // operand up to it holds a cell bit, once per cell from there on)
-      const bool count_products = dg.in_order && dg.sl == 0;
       for (int j = 0; j < rb; j++) {
         size_t bi = 0;
         double best_cost = -1;
         for (size_t q = 0; q < sc.size(); q++) {
           double cost = 0;
-          bool split = false;
-          for (size_t k = 0; k < G.ops.size(); k++) {
-            const int h = (int)held[k] + (int)((G.ops[k].mask >> sc[q].second) & 1u);
-            split |= h > 0;
-            cost += std::ldexp(1.0, h);
-            if (count_products) cost += split && (G.ops[k].mask & ~63u) ? 0.5 * (1 << rb) : 0.5;
-          }
+          for (size_t k = 0; k < G.ops.size(); k++)
+            cost += std::ldexp(1.0, (int)held[k] + (int)((G.ops[k].mask >> sc[q].second) & 1u));
           if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             bi = q;
