@@ -1399,7 +1399,8 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
     for (int i = (int)s.item_task.size() - 1; i >= 0; i--) s.task_first[s.item_task[i]] = i;
     s.n_init = s.n_steps > 0 ? s.step_begin[1] : 0;
   }
-  if (!force && !persistent && nets[0]->executor == 0) plan_steps(s);
+  // (the cell kernels of a step have no form in the plan's order)
+  if (!force && !persistent && !in_order && nets[0]->executor == 0) plan_steps(s);
   s.bytes[QTN_K_BLOCK] = s.init_bytes;
   s.flops[QTN_K_BLOCK] = s.init_flops;
   // a wide launch walks the units of every set in one flat 31-bit index
@@ -2221,8 +2222,7 @@ static Exec *angle_exec(qtn_network *net, int n_sets, bool in_order, int *rc) {
   if (*rc) return nullptr;
   // per-group launches (the persistent executors run one set)
   ex->lead_per_cone = net->executor == 3;
-  // (a step's cell kernels have no form in the plan's order)
-  ex->steps = net->executor == 0 && !in_order;
+  ex->steps = net->executor == 0;
   ex->spin_limit = net->spin_limit;
   if (slot.exec) ex->rt.take(slot.exec->rt);
   slot.exec = std::move(ex);

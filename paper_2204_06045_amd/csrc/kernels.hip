@@ -2188,7 +2188,7 @@ hipError_t launch_wide_group(const DevGroup &hg, void *data, const DevGroup *gro
 
 bool step_group(const DevGroup &hg) {
   return hg.variant == kVarCell && hg.rls == kCellRuleCB && hg.n_ops >= 1 &&
-         hg.n_ops <= kCellMaxOps && hg.sl <= kCellMaxSerial;
+         hg.n_ops <= kCellMaxOps && hg.sl <= kCellMaxSerial && !hg.in_order;
 }
 
 int step_blocks(const DevGroup &hg, int n_sets, double units_per_wave, int threads) {

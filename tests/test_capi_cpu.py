@@ -519,3 +519,18 @@ def test_order_search_by_plan_cost(qtn, cap):
     assert st[4]["max_width"] <= max(st[0]["max_width"], cap or 32)
     with pytest.raises(qtn.QtnError):
         qtn.Network(30, inst["edges"], g, b, order_weight=-1)
+
+
+@pytest.mark.parametrize("prec", [1, 2])
+def test_gradient_schedule_in_plan_order_has_no_steps(qtn, prec):
+    # step launches have no form in the plan's order, so that a gradient's
+    # schedule in complex64 is the same with them (executor 0) and without (1)
+    inst = qs.instance(20, 3, 3, 0)
+    g, b = inst["angles"][0]
+    need = []
+    for executor in (0, 1):
+        net = qtn.Network(20, inst["edges"], g, b, executor=executor, small_width=8, mixed_width=10)
+        net.plan(prec)
+        need.append(qtn.qtn_gradient_workspace(net.h))
+        net.close()
+    assert need[0] == need[1]
