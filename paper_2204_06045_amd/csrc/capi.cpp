@@ -89,8 +89,17 @@ struct Task {
   double ms = -1;  // the cost model's time (-1: none)
 };
 
+// Workspace of a schedule: byte offsets of its parts.
+struct Layout {
+  size_t off_res = 0, off_angles = 0, off_desc = 0, off_fills = 0, off_groups = 0, off_ops = 0,
+         off_stab = 0, off_uperm = 0, off_ranges = 0, off_prog = 0, off_csb = 0, off_ncb = 0,
+         off_cns = 0, off_step_tasks = 0, off_items = 0, off_steps = 0, off_item_task = 0,
+         off_task_next = 0, off_task_first = 0, off_task_need = 0, off_queue = 0, off_ctl = 0,
+         off_data = 0, total = 0;
+};
+
 // Device layout and launch list of one or more planned networks.
-struct Schedule {
+struct Schedule : Layout {
   int prec = 0;        // QTN_C128, QTN_C64 or QTN_MIXED
   int scalar_prec = 0;  // storage of the scalar slots
   std::vector<DevGroup> groups;
@@ -120,8 +129,7 @@ struct Schedule {
   int singles_range0 = 0;     // range index of singles[0]
   std::vector<std::vector<Task>> cone_tasks;  // after the leading small groups
   int n_cones = 0, n_nets = 0, n_angles = 0;
-  size_t off_res = 0, off_angles = 0, off_desc = 0, off_fills = 0, off_groups = 0,
-         off_ops = 0, off_stab = 0, off_uperm = 0, off_ranges = 0, off_prog = 0, off_csb = 0, off_ncb = 0, off_cns = 0, off_data = 0, total = 0;
+  size_t set_bytes = 0;  // data of one angle set
   int64_t scalar_off = 0, scalar_sstride = 0;
   int n_sets = 1;  // angle sets evaluated per launch (one copy of the data each)
   // step launches: the j-th task of every light cone (after the leading
@@ -134,7 +142,6 @@ struct Schedule {
   };
   std::vector<Step> steps;
   std::vector<int4> step_tasks;
-  size_t off_step_tasks = 0;
   std::vector<char> desc_blob;  // bytes [off_desc, off_data)
   uint64_t serial = 0;          // distinct for every schedule built
   int item_order = 0;           // lockstep steps: 0 costliest cone's items first, 1 reversed
@@ -146,8 +153,6 @@ struct Schedule {
   std::vector<int4> items;
   std::vector<int> step_begin, item_task, task_dep, task_need, task_next, task_first;
   int n_steps = 0, n_tasks = 0, n_init = 0;
-  size_t off_items = 0, off_steps = 0, off_item_task = 0, off_task_next = 0, off_task_first = 0,
-         off_task_need = 0, off_queue = 0, off_ctl = 0;
   int n_ctl = 0;
 };
 
@@ -829,6 +834,25 @@ struct ProgBases {
   int table_elems;
 };
 
+// Units of a small group in a segment program, and the items it is cut into.
+int prog_units(const DevGroup &G) { return 1 << std::max(0, G.w - 6 - prog_reg_bits(G.w, G.L)); }
+int prog_pieces(const DevGroup &G) { return std::min(prog_units(G), kProgPieces); }
+
+// End of the page that starts at group b of [b, g1); adds its operands to
+// n_ops and the most words it takes to words.
+int page_end(const Schedule &s, int b, int g1, int *n_ops, size_t *words) {
+  int e = b, w = kPageHeader + 8;
+  while (e < g1) {
+    const int more = 4 * s.groups[e].n_ops + 4 * prog_pieces(s.groups[e]) + 1;
+    if (e > b && w + more > kPageWords) break;
+    w += more;
+    *n_ops += s.groups[e].n_ops;
+    e++;
+  }
+  *words += (size_t)w;
+  return e;
+}
+
 // Compiles groups [g0, g1) of the schedule (one light cone's, in execution
 // order) into a segment program (prog); false where a group does not fit the
 // form (union wider than 16 bits, more than 64 operands, mixed arithmetic, a
@@ -858,24 +882,13 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
         return false;
     }
   }
-  auto prog_units = [](const DevGroup &G) {
-    return 1 << std::max(0, G.w - 6 - prog_reg_bits(G.w, G.L));
-  };
-  auto pieces_of = [&](const DevGroup &G) {
-    return std::min(prog_units(G), kProgPieces);
-  };
   size_t prev_at = 0;
   bool first = true;
   for (int b = g0; b < g1;) {
     // groups [b, e) make the page
-    int e = b, words = kPageHeader + 8, n_ops = 0;
-    while (e < g1) {
-      const int more = 4 * s.groups[e].n_ops + 4 * pieces_of(s.groups[e]) + 1;
-      if (e > b && words + more > kPageWords) break;
-      words += more;
-      n_ops += s.groups[e].n_ops;
-      e++;
-    }
+    int n_ops = 0;
+    size_t words = 0;
+    const int e = page_end(s, b, g1, &n_ops, &words);
     const int n = e - b;
     // who makes an operand: the last group of the page to write its address
     const int op0 = s.groups[b].op_begin;  // the page's operands are [op0, op0 + n_ops)
@@ -1016,7 +1029,7 @@ bool compile_segment(const Schedule &s, int g0, int g1, const ProgBases &pb,
     uint32_t item = 0;
     for (int i : by_level) {
       const DevGroup &G = s.groups[b + i];
-      const int np = pieces_of(G), per = prog_units(G) / np;
+      const int np = prog_pieces(G), per = prog_units(G) / np;
       uint32_t out;
       if (G.w == G.L) out = kLocScalar | (uint32_t)((G.out_off - pb.scalar) / es) << 2;
       else if (lds[i]) out = kLocLds | (uint32_t)(kProgPoolAt + where[i]) << 2;
@@ -1125,6 +1138,51 @@ void plan_steps(Schedule &s) {
     }
     st.n = (int)s.step_tasks.size() - st.first;
   }
+}
+
+// Workspace of a schedule with this many device descriptors, program words and
+// step tasks, for n_sets angle sets.
+Layout lay_out(const Schedule &s, size_t n_groups, size_t n_ops, size_t n_stab, size_t n_uperm,
+               size_t n_prog, size_t n_step_tasks, int n_sets) {
+  Layout l;
+  l.off_res = 0;
+  l.off_angles = align_up(8 * (size_t)(2 * s.n_cones + s.n_nets) * n_sets, 256);
+  l.off_desc = align_up(l.off_angles + 8 * (size_t)s.n_angles * n_sets, 256);
+  l.off_fills = l.off_desc;
+  l.off_groups = align_up(l.off_fills + sizeof(FillDesc) * s.fills.size(), 256);
+  l.off_ops = align_up(l.off_groups + sizeof(DevGroup) * n_groups, 256);
+  l.off_stab = align_up(l.off_ops + sizeof(DevOp) * n_ops, 256);
+  l.off_uperm = align_up(l.off_stab + sizeof(int32_t) * n_stab, 256);
+  l.off_ranges = align_up(l.off_uperm + n_uperm, 256);
+  l.off_prog = align_up(l.off_ranges + sizeof(int4) * s.ranges.size(), 256);
+  l.off_csb = align_up(l.off_prog + sizeof(uint32_t) * (n_prog), 256);
+  l.off_ncb = align_up(l.off_csb + sizeof(int) * s.csb.size(), 256);
+  l.off_cns = align_up(l.off_ncb + sizeof(int) * s.ncb.size(), 256);
+  l.off_step_tasks = align_up(l.off_cns + sizeof(int) * s.cns.size(), 256);
+  l.off_items = align_up(l.off_step_tasks + sizeof(int4) * n_step_tasks, 256);
+  l.off_steps = align_up(l.off_items + sizeof(int4) * s.items.size(), 256);
+  l.off_item_task = align_up(l.off_steps + sizeof(int) * s.step_begin.size(), 256);
+  l.off_task_next = align_up(l.off_item_task + sizeof(int) * s.item_task.size(), 256);
+  l.off_task_first = align_up(l.off_task_next + sizeof(int) * s.task_next.size(), 256);
+  l.off_task_need = align_up(l.off_task_first + sizeof(int) * s.task_first.size(), 256);
+  l.off_queue = align_up(l.off_task_need + sizeof(int) * s.task_need.size(), 256);
+  l.off_ctl = align_up(l.off_queue + sizeof(uint32_t) * s.items.size(), 256);
+  l.off_data = align_up(l.off_ctl + sizeof(uint32_t) * s.n_ctl, 256);
+  l.total = l.off_data + s.set_bytes * n_sets;
+  return l;
+}
+
+// Most bytes that a schedule built like s needs for n_sets angle sets, of its
+// two forms: in the plan's order every group has its descriptors on the
+// device; otherwise its small groups may be in programs, and tasks in steps.
+size_t form_bytes(const Schedule &s, bool in_order, int n_sets) {
+  size_t words = 0, tasks = 0;
+  if (!in_order) {
+    for (int r = 0, n_ops = 0; r < s.singles_range0; r++)
+      for (int g = s.ranges[r].x; g < s.ranges[r].y;) g = page_end(s, g, s.ranges[r].y, &n_ops, &words);
+    for (auto &tk : s.cone_tasks) tasks += tk.size();
+  }
+  return lay_out(s, s.groups.size(), s.ops.size(), s.stab.size(), s.uperm.size(), words, tasks, n_sets).total;
 }
 
 // persistent: the schedule runs in a persistent executor (every group inside
@@ -1466,31 +1524,9 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
       if (t.x >= 0) t.x = s.dev_group[t.x];
   }
 
-  // workspace layout (bytes)
-  s.off_res = 0;
-  s.off_angles = align_up(8 * (size_t)(2 * s.n_cones + s.n_nets) * s.n_sets, 256);
-  s.off_desc = align_up(s.off_angles + 8 * (size_t)s.n_angles * s.n_sets, 256);
-  s.off_fills = s.off_desc;
-  s.off_groups = align_up(s.off_fills + sizeof(FillDesc) * s.fills.size(), 256);
-  s.off_ops = align_up(s.off_groups + sizeof(DevGroup) * n_groups, 256);
-  s.off_stab = align_up(s.off_ops + sizeof(DevOp) * n_ops, 256);
-  s.off_uperm = align_up(s.off_stab + sizeof(int32_t) * n_stab, 256);
-  s.off_ranges = align_up(s.off_uperm + n_uperm, 256);
-  s.off_prog = align_up(s.off_ranges + sizeof(int4) * s.ranges.size(), 256);
-  s.off_csb = align_up(s.off_prog + sizeof(uint32_t) * (s.prog.size() + s.prog_more), 256);
-  s.off_ncb = align_up(s.off_csb + sizeof(int) * s.csb.size(), 256);
-  s.off_cns = align_up(s.off_ncb + sizeof(int) * s.ncb.size(), 256);
-  s.off_step_tasks = align_up(s.off_cns + sizeof(int) * s.cns.size(), 256);
-  s.off_items = align_up(s.off_step_tasks + sizeof(int4) * s.step_tasks.size(), 256);
-  s.off_steps = align_up(s.off_items + sizeof(int4) * s.items.size(), 256);
-  s.off_item_task = align_up(s.off_steps + sizeof(int) * s.step_begin.size(), 256);
-  s.off_task_next = align_up(s.off_item_task + sizeof(int) * s.item_task.size(), 256);
-  s.off_task_first = align_up(s.off_task_next + sizeof(int) * s.task_next.size(), 256);
-  s.off_task_need = align_up(s.off_task_first + sizeof(int) * s.task_first.size(), 256);
-  s.off_queue = align_up(s.off_task_need + sizeof(int) * s.task_need.size(), 256);
-  s.off_ctl = align_up(s.off_queue + sizeof(uint32_t) * s.items.size(), 256);
-  s.off_data = align_up(s.off_ctl + sizeof(uint32_t) * s.n_ctl, 256);
-  s.total = s.off_data + (size_t)data;
+  s.set_bytes = (size_t)data / n_sets;
+  (Layout &)s = lay_out(s, n_groups, n_ops, n_stab, n_uperm, s.prog.size() + s.prog_more,
+                        s.step_tasks.size(), n_sets);
   if (size_only) return QTN_OK;
   s.desc_blob.assign(s.off_data - s.off_desc, 0);
   auto put = [&](size_t off, const void *src, size_t bytes) {
@@ -2237,6 +2273,8 @@ static Exec *angle_exec(qtn_network *net, int n_sets, bool in_order, int *rc) {
 // order of operations, the plan's, whatever the mapping would choose for speed.
 static bool gradient_in_order(const qtn_network *net) { return net->precision != kPrecC128; }
 
+static int gradient_sets(const qtn_network *net) { return 4 * net->p + 1; }
+
 int qtn_angles_workspace(qtn_network *net, int32_t n_sets, size_t *bytes_out) {
   try {
     if (!net || !bytes_out) return set_err(QTN_EINVAL, "NULL argument");
@@ -2247,10 +2285,9 @@ int qtn_angles_workspace(qtn_network *net, int32_t n_sets, size_t *bytes_out) {
     Exec *ex = angle_exec(net, n_sets, false, &rc);
     if (!ex) return rc;
     *bytes_out = ex->sched.total;
-    if (n_sets == 4 * net->p + 1 && gradient_in_order(net)) {  // a gradient's sets
-      if (!(ex = angle_exec(net, n_sets, true, &rc))) return rc;
-      *bytes_out = std::max<size_t>(*bytes_out, ex->sched.total);
-    }
+    // as many sets as a gradient takes, or more, serve the gradient too
+    if (n_sets >= gradient_sets(net) && gradient_in_order(net))
+      *bytes_out = std::max(*bytes_out, form_bytes(ex->sched, true, gradient_sets(net)));
     return QTN_OK;
   } catch (...) {
     return exception_status();
@@ -2749,8 +2786,20 @@ int qtn_autotune(qtn_network *net, void *d_workspace, size_t bytes, void *hip_st
 }
 
 int qtn_gradient_workspace(qtn_network *net, size_t *workspace_bytes_out) {
-  if (!net) return set_err(QTN_EINVAL, "NULL argument");
-  return qtn_angles_workspace(net, 4 * net->p + 1, workspace_bytes_out);
+  if (!net || !workspace_bytes_out) return set_err(QTN_EINVAL, "NULL argument");
+  if (!net->planned || !gradient_in_order(net))
+    return qtn_angles_workspace(net, gradient_sets(net), workspace_bytes_out);
+  try {
+    // builds the gradient's schedule; serves as many sets of
+    // qtn_contract_angles too
+    int rc = QTN_OK;
+    Exec *ex = angle_exec(net, gradient_sets(net), true, &rc);
+    if (!ex) return rc;
+    *workspace_bytes_out = std::max(ex->sched.total, form_bytes(ex->sched, false, gradient_sets(net)));
+    return QTN_OK;
+  } catch (...) {
+    return exception_status();
+  }
 }
 
 int qtn_energy_gradient(qtn_network *net, void *d_workspace, size_t bytes, void *hip_stream,
@@ -2761,7 +2810,7 @@ int qtn_energy_gradient(qtn_network *net, void *d_workspace, size_t bytes, void 
       return set_err(QTN_EINVAL, "NULL argument");
     if (!(step > 0.0) || !std::isfinite(step))
       return set_err(QTN_EINVAL, "step must be positive and finite");
-    const int p = net->p, n = 4 * p + 1;
+    const int p = net->p, n = gradient_sets(net);
     // set 0: the angles; then gamma_l + h, gamma_l - h for every l, then the
     // same for beta_l
     std::vector<double> g((size_t)n * p), b((size_t)n * p), e(n);

@@ -526,11 +526,47 @@ def test_gradient_schedule_in_plan_order_has_no_steps(qtn, prec):
     # step launches have no form in the plan's order, so that a gradient's
     # schedule in complex64 is the same with them (executor 0) and without (1)
     inst = qs.instance(20, 3, 3, 0)
-    g, b = inst["angles"][0]
+    g, b = (np.array(a) for a in inst["angles"][0])
     need = []
     for executor in (0, 1):
         net = qtn.Network(20, inst["edges"], g, b, executor=executor, small_width=8, mixed_width=10)
         net.plan(prec)
-        need.append(qtn.qtn_gradient_workspace(net.h))
+        need.append(_gradient_bytes(qtn, net, g, b))
         net.close()
     assert need[0] == need[1]
+
+
+def _bytes_needed(qtn, net, call, *args):
+    """The bytes of a call, refused for its size before anything is queued."""
+    assert call(net.h, ctypes.c_void_p(256), 1, None, *args) == -3
+    return int(re.search(r"plan needs (\d+)", qtn.qtn_last_error())[1])
+
+
+def _gradient_bytes(qtn, net, g, b):
+    from paper_2204_06045_amd import _capi
+    pd = ctypes.POINTER(ctypes.c_double)
+    out = [np.zeros(net.p) for _ in range(3)]
+    g, b, *out = [x.ctypes.data_as(pd) for x in (g, b, *out)]
+    return _bytes_needed(qtn, net, _capi.lib().qtn_energy_gradient, g, b, 1e-4, *out)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("n,d,p", [(24, 4, 2), (16, 3, 3), (10, 3, 1)])
+def test_workspace_of_more_sets_serves_a_gradient(qtn, n, d, p, prec):
+    """A workspace of as many angle sets as a gradient takes, or more, serves
+    the gradient, and the gradient's serves as many sets."""
+    from paper_2204_06045_amd import _capi
+    inst = qs.instance(n, d, p, 0)
+    g, b = (np.array(a) for a in inst["angles"][0])
+    net = qtn.Network(n, inst["edges"], g, b, mixed_width=10)
+    net.plan(prec)
+    sets = 4 * p + 1
+    enough = [net.angles_workspace(sets + k) for k in range(4)]
+    gradient = qtn.qtn_gradient_workspace(net.h)
+    need = _gradient_bytes(qtn, net, g, b)
+    assert need <= gradient and need <= min(enough)
+    pd = ctypes.POINTER(ctypes.c_double)
+    zz, energy = np.zeros(sets * net.m), np.zeros(sets)
+    arrays = [x.ctypes.data_as(pd) for x in (np.tile(g, (sets, 1)), np.tile(b, (sets, 1)), zz, energy)]
+    assert gradient >= _bytes_needed(qtn, net, _capi.lib().qtn_contract_angles, sets, *arrays, None)
+    net.close()
