@@ -173,6 +173,7 @@ struct Runtime {
   char *dev_desc = nullptr;
   size_t dev_desc_cap = 0;
   uint64_t dev_serial = 0;    // schedule whose descriptors dev_desc holds
+  uint64_t no_dev_serial = 0; // schedule for which there was no memory
   char *desc_base = nullptr;  // offsets off_desc..off_data count from here
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
@@ -1880,7 +1881,7 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
   int rc = ensure_runtime(rt, n_streams, n_res + s.n_angles * s.n_sets);
   if (rc) return rc;
   const size_t n_desc = s.desc_blob.size();
-  if (rt.dev_desc_cap < n_desc) {
+  if (rt.dev_desc_cap < n_desc && rt.no_dev_serial != s.serial) {
     drop_graph(rt);
     if (rt.dev_desc) QTN_HIP(hipFree(rt.dev_desc));
     rt.dev_desc = nullptr;
@@ -1890,6 +1891,7 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
       rt.dev_desc_cap = n_desc;
     } else {
       rt.dev_desc = nullptr;
+      rt.no_dev_serial = s.serial;
       (void)hipGetLastError();
     }
   }

@@ -291,11 +291,27 @@ int refused_under_capture() {
   return 0;
 }
 
+// Without memory for the descriptors every call sends them into the workspace,
+// which is all that it pays: one failed allocation, one graph.
+int no_memory_for_descriptors() {
+  Net net(10, 2);
+  ihipStream_t s;
+  malloc_fails = true;
+  for (int k = 0; k < 3; k++) CHECK(net.contract(&s) == QTN_OK);
+  CHECK(n.mallocs == 1 && n.graphs == 1 && n.copies == 3);
+  malloc_fails = false;
+  CHECK(qtn_set_tune_picks(net.h, nullptr, 0) == QTN_OK);  // a new schedule tries again
+  for (int k = 0; k < 3; k++) CHECK(net.contract(&s) == QTN_OK);
+  CHECK(n.mallocs == 2 && n.graphs == 2 && n.copies == 4);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_under_capture") return refused_under_capture();
+  if (what == "no_memory_for_descriptors") return no_memory_for_descriptors();
   std::printf("no scenario '%s'\n", what.c_str());
   return 2;
 }

@@ -31,3 +31,7 @@ def test_refused_call_leaves_no_descriptors_behind(fake):
     # a schedule's descriptors go up once: a copy that a capture swallowed must
     # not count
     _run(fake, "refused_under_capture")
+
+
+def test_failed_descriptor_allocation_is_tried_once(fake):
+    _run(fake, "no_memory_for_descriptors")
