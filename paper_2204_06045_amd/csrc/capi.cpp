@@ -156,6 +156,38 @@ struct Schedule : Layout {
   int n_ctl = 0;
 };
 
+// Device memory that the library keeps for descriptors, all together.  A batch's
+// lives until one of its networks is planned anew or freed, so a program that
+// forms batch after batch of the same networks would otherwise fill the card;
+// past the bound, this part of the device's memory, a call sends its
+// descriptors into the workspace.  A batch of 64 graphs of 20 to 200 vertices,
+// depths 2 to 4, takes 236 MB: nine of them on a card of 288 GB.
+constexpr size_t kDescPart = 128;
+std::atomic<size_t> g_desc_bytes{0};
+
+// Null past the bound, and where the device has none left (*none).
+char *desc_alloc(size_t bytes, bool *none) {
+  char *p = nullptr;
+  size_t free_bytes = 0, all = 0;
+  *none = false;
+  const size_t held = g_desc_bytes.fetch_add(bytes) + bytes;
+  if (hipMemGetInfo(&free_bytes, &all) != hipSuccess ||
+      (held <= all / kDescPart && hipMalloc((void **)&p, bytes) != hipSuccess)) {
+    (void)hipGetLastError();
+    *none = true;
+    p = nullptr;
+  }
+  if (p) return p;
+  g_desc_bytes -= bytes;
+  return nullptr;
+}
+
+void desc_free(char *p, size_t bytes) {
+  if (!p) return;
+  (void)hipFree(p);
+  g_desc_bytes -= bytes;
+}
+
 // Streams, events, pinned staging and the captured graph of one schedule.
 struct Runtime {
   int device = -1;
@@ -194,7 +226,7 @@ struct Runtime {
     if (main) (void)hipStreamDestroy(main);
     if (pinned) (void)hipHostFree(pinned);
     if (pinned_err) (void)hipHostFree(pinned_err);
-    if (dev_desc) (void)hipFree(dev_desc);
+    desc_free(dev_desc, dev_desc_cap);
     pinned_err = nullptr;
     dev_desc = desc_base = nullptr;
     dev_desc_cap = 0;
@@ -1882,18 +1914,13 @@ int run_exec(Exec &X, const std::vector<const qtn_network *> &nets, void *ws, si
   if (rc) return rc;
   const size_t n_desc = s.desc_blob.size();
   if (rt.dev_desc_cap < n_desc && rt.no_dev_serial != s.serial) {
-    drop_graph(rt);
-    if (rt.dev_desc) QTN_HIP(hipFree(rt.dev_desc));
-    rt.dev_desc = nullptr;
-    rt.dev_desc_cap = 0;
+    if (rt.dev_desc) drop_graph(rt);
+    desc_free(rt.dev_desc, rt.dev_desc_cap);
+    bool none;
+    rt.dev_desc = desc_alloc(n_desc, &none);
+    rt.dev_desc_cap = rt.dev_desc ? n_desc : 0;
     rt.dev_serial = 0;
-    if (hipMalloc((void **)&rt.dev_desc, n_desc) == hipSuccess) {
-      rt.dev_desc_cap = n_desc;
-    } else {
-      rt.dev_desc = nullptr;
-      rt.no_dev_serial = s.serial;
-      (void)hipGetLastError();
-    }
+    if (none) rt.no_dev_serial = s.serial;
   }
   // the captured graph holds the old addresses
   char *base = rt.dev_desc ? rt.dev_desc - s.off_desc : (char *)ws;
@@ -2951,7 +2978,7 @@ class BucketDesc {
   ~BucketDesc() {
     RelaxedCapture relax;
     if (ev_) (void)hipEventDestroy(ev_);
-    if (dev_) (void)hipFree(dev_);  // waits for the kernels that read it
+    desc_free(dev_, bytes_);  // waits for the kernels that read it
   }
   // The device copy if a launch on st may read it, else null.
   char *get(hipStream_t st) {
@@ -2975,8 +3002,9 @@ class BucketDesc {
       return;
     }
     RelaxedCapture relax;
-    const bool ok = stream_device(st, &device_) && hipMalloc((void **)&dev_, blob.size()) == hipSuccess &&
-                    hipEventCreateWithFlags(&ev_, hipEventDisableTiming) == hipSuccess &&
+    bool none;
+    if (stream_device(st, &device_)) dev_ = desc_alloc(bytes_ = blob.size(), &none);
+    const bool ok = dev_ && hipEventCreateWithFlags(&ev_, hipEventDisableTiming) == hipSuccess &&
                     hipMemcpyAsync(dev_, blob.data(), blob.size(), hipMemcpyHostToDevice, st) == hipSuccess &&
                     hipEventRecord(ev_, st) == hipSuccess;
     if (!ok) (void)hipGetLastError();
@@ -3013,6 +3041,7 @@ class BucketDesc {
   std::atomic<int> state_{kNone};
   int calls_ = 0, device_ = -1;
   char *dev_ = nullptr;
+  size_t bytes_ = 0;
   hipEvent_t ev_ = nullptr;
 };
 

@@ -32,6 +32,7 @@ struct Counts {
   int mallocs = 0, copies = 0, captured_copies = 0, graphs = 0, launches = 0;
 };
 Counts n;
+constexpr size_t kDeviceBytes = 4ull << 30;
 size_t live_bytes = 0, most_bytes = 0;
 std::map<void *, size_t> *sizes;
 std::set<ihipStream_t *> *joined;  // streams in the caller's capture
@@ -117,6 +118,11 @@ hipError_t hipMalloc(void **p, size_t bytes) {
   (*sizes)[*p] = bytes;
   live_bytes += bytes;
   if (live_bytes > most_bytes) most_bytes = live_bytes;
+  return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t *free_bytes, size_t *all) {
+  *all = kDeviceBytes;
+  *free_bytes = kDeviceBytes - live_bytes;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
@@ -306,12 +312,39 @@ int no_memory_for_descriptors() {
   return 0;
 }
 
+// Batches keep their descriptors on the device until one of their networks
+// goes: many different ones stay under a bound together, every one still runs,
+// and what they took is given back.
+int descriptors_of_many_batches() {
+  constexpr size_t kBound = kDeviceBytes / 128;
+  Net net(30, 3);
+  ihipStream_t s;
+  for (int k = 0; n.copies == k && k < 64; k++) {  // a batch without memory of its own sends them twice
+    const std::vector<qtn_network *> nets(8 + k, net.h);
+    const int count = (int)nets.size();
+    std::vector<double> e(count);
+    size_t bytes = 0;
+    CHECK(qtn_batch_workspace(nets.data(), count, &bytes) == QTN_OK);
+    void *ws = std::aligned_alloc(256, bytes);
+    for (int r = 0; r < 2; r++)
+      CHECK(qtn_contract_batch(nets.data(), count, ws, bytes, &s, nullptr, e.data()) == QTN_OK);
+    std::free(ws);
+  }
+  CHECK(n.copies > n.mallocs);
+  CHECK(most_bytes <= kBound && most_bytes > kBound / 2);
+  qtn_network_free(net.h);
+  net.h = nullptr;
+  CHECK(live_bytes == 0);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_under_capture") return refused_under_capture();
   if (what == "no_memory_for_descriptors") return no_memory_for_descriptors();
+  if (what == "descriptors_of_many_batches") return descriptors_of_many_batches();
   std::printf("no scenario '%s'\n", what.c_str());
   return 2;
 }

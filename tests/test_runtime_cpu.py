@@ -35,3 +35,7 @@ def test_refused_call_leaves_no_descriptors_behind(fake):
 
 def test_failed_descriptor_allocation_is_tried_once(fake):
     _run(fake, "no_memory_for_descriptors")
+
+
+def test_descriptors_of_many_batches_are_bounded(fake):
+    _run(fake, "descriptors_of_many_batches")
