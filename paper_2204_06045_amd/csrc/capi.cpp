@@ -125,8 +125,10 @@ struct Schedule : Layout {
   // groups that run as segment programs (-1)
   std::vector<int> dev_group;
   std::vector<size_t> stab_at;  // first stab entry of each group
-  std::vector<int> singles;   // groups also given a one-group range (tuning)
-  int singles_range0 = 0;     // range index of singles[0]
+  // groups also given one-group ranges (tuning): from singles_range0 on, each
+  // one's program (if it has one), then each one by its mapping
+  std::vector<int> singles;
+  int singles_range0 = 0;
   std::vector<std::vector<Task>> cone_tasks;  // after the leading small groups
   int n_cones = 0, n_nets = 0, n_angles = 0;
   size_t set_bytes = 0;  // data of one angle set
@@ -1412,6 +1414,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
   s.singles_range0 = (int)s.ranges.size();
   for (size_t i = 0; i < s.singles.size(); i++)
     s.ranges.push_back(make_int4(s.singles[i], s.singles[i] + 1, single_prog[i], 0));
+  for (int g : s.singles) s.ranges.push_back(make_int4(g, g + 1, -1, 0));
   s.n_nets = n;
   // persistent work items: the j-th task of every cone forms step j (leading
   // segment first); inside a step the costlier cones come first.  The
@@ -2554,10 +2557,10 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
     const auto &cands = tune_candidates();
     const int nc = (int)cands.size();
     qtn_network *one[1] = {net};
-    // per plan group: measured ms per candidate, own launch and inside a block
-    // (the fastest of the passes)
+    // per plan group: measured ms per candidate, own launch and inside a block,
+    // and as a segment program (the fastest of the passes)
     struct Meas {
-      double wide[8], block[8];
+      double wide[8], block[8], prog;
     };
     std::map<std::pair<int, int>, Meas> meas;
     qtn_tune_report rep;
@@ -2585,33 +2588,36 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           give_back();
           return rc;
         }
-        // the same groups again, each alone in one workgroup
-        Timer tb;
-        tb.on = true;
+        // the same groups again, each alone in one workgroup: by the candidate's
+        // mapping, which runs where a schedule has no segment programs (in the
+        // plan's order), and once as a program
+        Timer tb, tp;
+        tb.on = tp.on = true;
         char *ws = (char *)d_workspace, *desc = ex.rt.desc_base;
         const Schedule &s = ex.sched;
-        for (size_t i = 0; i < s.singles.size(); i++) {
+        const int n_single = (int)s.singles.size();
+        auto alone = [&](Timer &t, int single, int range) -> int {
+          int rc = t.begin(QTN_K_BLOCK, ex.rt.main, s.singles[single], 1, 0, 0, true);
+          if (rc) return rc;
+          QTN_HIP(launch_block_groups(
+              prog_prec(s, range), ws + s.off_data, (const DevGroup *)(desc + s.off_groups),
+              (const DevOp *)(desc + s.off_ops), (const int32_t *)(desc + s.off_stab),
+              (const uint8_t *)(desc + s.off_uperm), (const uint32_t *)(desc + s.off_prog),
+              (const int4 *)(desc + s.off_ranges), range, 1, n_sets, ex.rt.main, t.t0(), t.t1()));
+          return t.end(ex.rt.main, true);
+        };
+        for (int i = 0; i < n_single && !rc; i++) {
           // the cell mapping, the complex128 matrix form and matrix-form
           // tiles wider than one column block only run in their own launch
           const DevGroup &dg = s.groups[s.singles[i]];
-          if (dg.variant == kVarCell || (dg.variant == kVarMfma && (dg.prec == 0 || dg.rls != 1)))
-            continue;
-          if ((rc = tb.begin(QTN_K_BLOCK, ex.rt.main, s.singles[i], 1, 0, 0, true))) {
-            give_back();
-            return rc;
-          }
-          hipError_t he = launch_block_groups(
-              prog_prec(s, s.singles_range0 + (int)i), ws + s.off_data,
-              (const DevGroup *)(desc + s.off_groups),
-              (const DevOp *)(desc + s.off_ops), (const int32_t *)(desc + s.off_stab),
-              (const uint8_t *)(desc + s.off_uperm), (const uint32_t *)(desc + s.off_prog),
-              (const int4 *)(desc + s.off_ranges),
-              s.singles_range0 + (int)i, 1, n_sets, ex.rt.main, tb.t0(), tb.t1());
-          if (he == hipSuccess) rc = tb.end(ex.rt.main, true);
-          if (he != hipSuccess || rc) {
-            give_back();
-            return he != hipSuccess ? set_err(QTN_EDEVICE, hipGetErrorString(he)) : rc;
-          }
+          const int prog = s.singles_range0 + i;
+          if (dg.variant != kVarCell && !(dg.variant == kVarMfma && (dg.prec == 0 || dg.rls != 1)))
+            rc = alone(tb, i, prog + n_single);
+          if (!rc && ci == 0 && s.ranges[prog].z >= 0) rc = alone(tp, i, prog);
+        }
+        if (rc) {
+          give_back();
+          return rc;
         }
         hipError_t he = hipStreamSynchronize(ex.rt.main);
         if (he != hipSuccess) {
@@ -2627,7 +2633,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
         };
         auto slot = [&](int g) -> Meas & {
           return meas.emplace(key_of(g), Meas{{-1, -1, -1, -1, -1, -1, -1, -1},
-                                              {-1, -1, -1, -1, -1, -1, -1, -1}})
+                                              {-1, -1, -1, -1, -1, -1, -1, -1}, -1})
               .first->second;
         };
         auto keep_min = [](double &dst, double v) { dst = dst < 0 ? v : std::min(dst, v); };
@@ -2642,6 +2648,11 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           float ms = 0;
           (void)hipEventElapsedTime(&ms, r.a, r.b);
           keep_min(slot(r.group).block[ci], ms);
+        }
+        for (auto &r : tp.recs) {
+          float ms = 0;
+          (void)hipEventElapsedTime(&ms, r.a, r.b);
+          keep_min(slot(r.group).prog, ms);
         }
       }
     for (auto &kv : meas)
@@ -2697,6 +2708,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           ms_stream = m.wide[ci];
         if (cands[ci].variant == 3) ms_mfma = m.wide[ci];
       }
+      if (m.prog >= 0) mb = m.prog;  // what a workgroup runs
       tr.ms[QTN_VAR_BLOCK] = mb;
       tr.ms[QTN_VAR_STREAM] = ms_stream;
       tr.ms[QTN_VAR_GENERIC] = m.wide[0];

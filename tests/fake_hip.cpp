@@ -338,6 +338,26 @@ int descriptors_of_many_batches() {
   return 0;
 }
 
+// The autotuner times a small group alone in a workgroup by each mapping that
+// it may pick, and once as a segment program (which no pick changes).
+int autotuned_small_groups() {
+  Net net(12, 2);
+  ihipStream_t s;
+  qtn_plan_stats st;
+  CHECK(qtn_get_plan_stats(net.h, &st) == QTN_OK && st.max_width <= 16);
+  launched = new std::map<std::string, int>;
+  CHECK(qtn_autotune(net.h, net.ws, net.bytes, &s, nullptr) == QTN_OK);
+  int programs = 0, mappings = 0;
+  for (auto &kv : *launched) {
+    if (kv.first.find("k_programs") != std::string::npos) programs += kv.second;
+    if (kv.first.find("k_block_groups") != std::string::npos) mappings += kv.second;
+  }
+  constexpr int kPasses = 2, kMappings = 4;  // generic, streaming with 1, 2 and 3 lane bits
+  CHECK(programs == kPasses * st.n_groups);
+  CHECK(mappings >= kPasses * kMappings * st.n_groups);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -345,6 +365,7 @@ int main(int argc, char **argv) {
   if (what == "refused_under_capture") return refused_under_capture();
   if (what == "no_memory_for_descriptors") return no_memory_for_descriptors();
   if (what == "descriptors_of_many_batches") return descriptors_of_many_batches();
+  if (what == "autotuned_small_groups") return autotuned_small_groups();
   std::printf("no scenario '%s'\n", what.c_str());
   return 2;
 }

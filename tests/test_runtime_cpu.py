@@ -39,3 +39,7 @@ def test_failed_descriptor_allocation_is_tried_once(fake):
 
 def test_descriptors_of_many_batches_are_bounded(fake):
     _run(fake, "descriptors_of_many_batches")
+
+
+def test_autotuner_times_the_mappings_it_picks(fake):
+    _run(fake, "autotuned_small_groups")
