@@ -414,6 +414,14 @@ const std::vector<Force> &tune_candidates() {
   return c;
 }
 
+// A tuned or learned pick of the cell mapping where no cell kernel runs (the
+// persistent executors): the generic mapping up to this union width, past it
+// the width rule.  Persistent batches with learned picks, milliseconds by the
+// rule alone, up to 16, 20 and 32 bits: 6 graphs of 10 to 40 vertices, depths to 3,
+// complex128 1.61, 1.41, 1.34, 1.32, complex64 1.66, 1.47, 1.44, 1.44; 4 graphs of
+// 10 to 24 vertices, depths to 4, 6.32, 6.29, 5.97, 6.55 and 6.41, 6.19, 5.84, 6.28.
+constexpr int kNoCellWidth = 20;
+
 // Where a group's operands and output live (bytes from the data base) and
 // the kernel configuration requested for it.
 struct GroupEnv {
@@ -1342,6 +1350,7 @@ int build_schedule(qtn_network *const *nets, int n, Schedule *S, const Force *fo
         }
         env.is_small = is_small;
         env.persistent = persistent && !heavy;
+        if (!force && env.persistent && G.pick_variant == 4 && G.w <= kNoCellWidth) env.var_req = 1;
         env.in_order = in_order;
         DevGroup dg;
         double gb = 0, gf = 0;

@@ -570,3 +570,23 @@ def test_workspace_of_more_sets_serves_a_gradient(qtn, n, d, p, prec):
     arrays = [x.ctypes.data_as(pd) for x in (np.tile(g, (sets, 1)), np.tile(b, (sets, 1)), zz, energy)]
     assert gradient >= _bytes_needed(qtn, net, _capi.lib().qtn_contract_angles, sets, *arrays, None)
     net.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_cell_pick_without_cells_is_generic(qtn, prec):
+    # persistent executors have no cell kernels: up to 20 bits a pick of cells
+    # runs the generic mapping there, and it is cells in launches of their own
+    inst = qs.instance(16, 3, 4, 0)
+    g, b = inst["angles"][0]
+    for executor in (0, 2):
+        net = qtn.Network(16, inst["edges"], g, b, executor=executor)
+        net.plan(prec)
+        before = net.stats()
+        assert before["max_width"] <= 20
+        net.set_tune_picks([(e, k, pl, 4, 3, sh) for e, k, pl, _, _, sh in net.tune_picks()])
+        after = net.stats()
+        if executor == 0:
+            assert after["n_cell"] == before["n_cell"] > 0
+        else:
+            assert before["n_stream"] > 0 and after["n_stream"] == after["n_cell"] == 0
+        net.close()
