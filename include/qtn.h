@@ -175,7 +175,10 @@ int qtn_set_angles(qtn_network *net, const double *gamma, const double *beta);
  *   zz_out       [n_edges] Re e_jk
  *   zz_imag_out  [n_edges] Im e_jk (zero up to rounding) or NULL
  *   energy_out   <C> = |E|/2 - 1/2 sum Re e_jk, accumulated in FP64
- * Blocks until the results are on the host.
+ * Blocks until the results are on the host, and so is refused (QTN_EDEVICE) on
+ * a stream under capture.  The library keeps a plan's descriptors in device
+ * memory of its own, at most 1/128 of the device's for all plans together; past
+ * that they are copied into the workspace by every call.
  * Errors: QTN_ESTATE (no plan), QTN_ENOMEM (workspace too small),
  *         QTN_EDEVICE.
  */
@@ -185,7 +188,10 @@ int qtn_contract(qtn_network *net, void *d_workspace, size_t bytes,
 
 /*
  * Contract several planned networks in one batch: all of their light cones
- * share one workspace and one launch sequence.
+ * share one workspace and one launch sequence.  In complex64 every group
+ * multiplies and sums in the plan's order, so that results stay the same from
+ * version to version; their rounding differs from qtn_contract, which takes
+ * the faster order.
  *   nets         [n] planned networks of one precision
  *   d_workspace  at least qtn_batch_workspace() bytes
  *   zz_out       concatenated [sum n_edges] Re e_jk, network by network
@@ -276,14 +282,18 @@ int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes,
  * the energy is maximised over the angles): central differences
  * dE/dgamma_l = (E(gamma_l + h) - E(gamma_l - h)) / 2h, the same for beta_l,
  * with the 4p + 1 angle sets (the given angles and each shifted one) evaluated
- * in one qtn_contract_angles pass on the network's plan.  The network's own
- * angles (qtn_set_angles) are not changed.
+ * in one pass over the network's plan, as qtn_contract_angles does.  The
+ * network's own angles (qtn_set_angles) are not changed.  In complex64 and mixed
+ * precision the complex64 groups of this pass multiply and sum in the plan's
+ * order, so that results stay the same from version to version; the rounding
+ * of energy_out differs from qtn_contract_angles, which takes the faster order.
  *   gamma, beta     [p] radians (host)
  *   step            h > 0; the truncation error is O(h^2), the rounding error
  *                   O(eps |E| / h) (about 1e-4 .. 1e-3 in complex128)
  *   energy_out      E at the given angles
  *   grad_*_out      [p] (host)
- * qtn_gradient_workspace stores the workspace bytes (that of 4p + 1 sets).
+ * qtn_gradient_workspace stores the workspace bytes; a workspace of 4p + 1 or
+ * more sets (qtn_angles_workspace) serves too, and this one serves 4p + 1 sets.
  * Errors: as qtn_contract_angles; QTN_EINVAL also for a bad step.
  */
 int qtn_gradient_workspace(qtn_network *net, size_t *workspace_bytes_out);
