@@ -347,7 +347,7 @@ typedef struct qtn_tune_report {
     double cand_ms[8];    /* summed own-launch group time per configuration
                              (the matrix form: over the groups that have
                              one; 0 when none has)                          */
-    double tuned_ms;      /* the same with each group's fastest choice      */
+    double tuned_ms;      /* the same with each group's choice              */
     int32_t picks[8];     /* groups that chose each configuration           */
 } qtn_tune_report;
 
@@ -358,8 +358,9 @@ typedef struct qtn_tune_report {
  * 3 or 4 cell bits, for the groups wide enough for it), each group in
  * its own launch on one stream and, for groups up to width 16, again alone
  * inside one workgroup, timing every launch with HIP events.  Each group then
- * keeps its fastest configuration for where it runs, and the plan's schedule
- * is rebuilt.  Needs the workspace qtn_plan reported.  The timings
+ * keeps its fastest configuration for where it runs (short groups among step
+ * launches the cell mapping, which is the only one there), and the plan's
+ * schedule is rebuilt.  Needs the workspace qtn_plan reported.  The timings
  * are kept for qtn_tune_log.  Results of qtn_contract are unchanged up to
  * rounding order.
  */

@@ -2528,6 +2528,16 @@ int qtn_autotune_batch(qtn_network *const *nets, int32_t n, void *d_workspace, s
   }
 }
 
+// A group leaves the step launches' mapping when it takes more than this many
+// milliseconds in a launch of its own; a shorter one is mostly launch there, and
+// among other mappings the schedule loses its steps.  Choices by launches alone
+// against cells for all short groups, autotuned: 20 vertices, depth 3, 209 us
+// against 126; 16 vertices, depth 4, 1.60 ms against 0.92; quartic, 24 vertices,
+// depth 3, complex64, 2.22 against 0.77.  By the cost model: 232 us against 112,
+// 2.23 ms against 1.04; 40 vertices, quartic, 6.14 against 4.50.  The line itself
+// matters little: from 0.02 to no limit these stay within 3%.
+constexpr double kLeaveStepMs = 0.05;
+
 // Workspace of autotuning over n_sets copies of the network's angles: the
 // largest candidate schedule.
 static int tune_workspace_bytes(qtn_network *net, int n_sets, size_t *bytes) {
@@ -2680,6 +2690,12 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
     // the tuning log.
     constexpr double kSwitchGain = 0.97;
     net->tune_log.clear();
+    struct Chosen {
+      Group *group;
+      const Meas *meas;
+      int alone, in_step;  // candidate for launches of its own, and among step launches
+    };
+    std::vector<Chosen> chosen;
     for (auto &kv : meas) {
       ConePlan &pl = net->plans[kv.first.first];
       Group &G = pl.groups[kv.first.second];
@@ -2702,16 +2718,7 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           if (t[ci] >= 0) best = ci;
       for (int ci = 0; ci < nc; ci++)
         if (t[ci] >= 0 && (best < 0 || t[ci] < kSwitchGain * t[best])) best = ci;
-      if (best >= 0) {
-        G.pick_variant = (int8_t)cands[best].variant;
-        G.pick_rls = (int8_t)cands[best].rls;
-        G.pred_ms = -1;
-        if (!G.small) {
-          rep.tuned_ms += t[best];
-          rep.picks[best]++;
-          rep.n_groups++;
-        }
-      }
+      if (best >= 0) chosen.push_back({&G, &m, best, rule_cell >= 0 && m.wide[rule_cell] < kLeaveStepMs ? rule_cell : best});
       qtn_tune_rec tr;
       std::memset(&tr, 0, sizeof tr);
       group_features(G, pl, net->precision, tr.features);
@@ -2730,9 +2737,34 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
       tr.ms[QTN_VAR_MFMA] = ms_mfma;
       net->tune_log.push_back(tr);
     }
-    // the tuned schedule replaces the current one, on the same streams
+    // the tuned schedule replaces the current one, on the same streams.  Step
+    // launches run the cell mapping, and a group timed in a launch of its own is
+    // mostly launch: so the short groups keep that mapping where they leave the
+    // schedule (at this many angle sets) its steps.
     auto tuned = std::make_unique<Exec>();
-    int rc = build_schedule(one, 1, &tuned->sched, nullptr, 0, 1, net->exec->persistent);
+    int rc = QTN_OK;
+    for (bool in_step : {net->exec->steps, false}) {
+      rep.tuned_ms = 0;
+      rep.n_groups = 0;
+      std::fill(rep.picks, rep.picks + nc, 0);
+      for (const Chosen &c : chosen) {
+        const int k = in_step ? c.in_step : c.alone;
+        c.group->pick_variant = (int8_t)cands[k].variant;
+        c.group->pick_rls = (int8_t)cands[k].rls;
+        c.group->pred_ms = -1;
+        if (c.group->small) continue;
+        rep.tuned_ms += c.meas->wide[k];
+        rep.picks[k]++;
+        rep.n_groups++;
+      }
+      if (in_step && n_sets > 1) {
+        Schedule many;
+        if ((rc = build_schedule(one, 1, &many, nullptr, 0, n_sets))) break;
+        if (many.steps.empty()) continue;
+      }
+      if ((rc = build_schedule(one, 1, &tuned->sched, nullptr, 0, 1, net->exec->persistent))) break;
+      if (!in_step || n_sets > 1 || !tuned->sched.steps.empty()) break;
+    }
     if (rc) {
       give_back();
       return rc;
@@ -3520,10 +3552,6 @@ int qtn_costmodel_adam_step(qtn_costmodel *cm, const float *grad, float lr, void
     return exception_status();
   }
 }
-
-// A group leaves the step launches' mapping when it takes more than this many
-// milliseconds.
-constexpr double kLeaveStepMs = 0.05;
 
 int qtn_apply_costmodel(qtn_network *net, const qtn_costmodel *cm, void *d_ws, size_t bytes,
                         void *hip_stream, int32_t *counts_out) {

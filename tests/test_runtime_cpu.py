@@ -43,3 +43,7 @@ def test_descriptors_of_many_batches_are_bounded(fake):
 
 def test_autotuner_times_the_mappings_it_picks(fake):
     _run(fake, "autotuned_small_groups")
+
+
+def test_autotuner_keeps_step_launches(fake):
+    _run(fake, "autotuned_steps")
