@@ -189,9 +189,9 @@ int qtn_contract(qtn_network *net, void *d_workspace, size_t bytes,
 /*
  * Contract several planned networks in one batch: all of their light cones
  * share one workspace and one launch sequence.  In complex64 every group
- * multiplies and sums in the plan's order, so that results stay the same from
- * version to version; their rounding differs from qtn_contract, which takes
- * the faster order.
+ * multiplies and sums in one fixed order (the plan's), so that results stay the
+ * same from version to version; their rounding differs from qtn_contract, which
+ * takes the fastest order.
  *   nets         [n] planned networks of one precision
  *   d_workspace  at least qtn_batch_workspace() bytes
  *   zz_out       concatenated [sum n_edges] Re e_jk, network by network
@@ -284,9 +284,10 @@ int qtn_contract_angles(qtn_network *net, void *d_workspace, size_t bytes,
  * with the 4p + 1 angle sets (the given angles and each shifted one) evaluated
  * in one pass over the network's plan, as qtn_contract_angles does.  The
  * network's own angles (qtn_set_angles) are not changed.  In complex64 and mixed
- * precision the complex64 groups of this pass multiply and sum in the plan's
- * order, so that results stay the same from version to version; the rounding
- * of energy_out differs from qtn_contract_angles, which takes the faster order.
+ * precision the complex64 groups of this pass multiply and sum in one fixed
+ * order (the plan's), so that results stay the same from version to version; the
+ * rounding of energy_out differs from qtn_contract_angles, which takes the
+ * fastest order.
  *   gamma, beta     [p] radians (host)
  *   step            h > 0; the truncation error is O(h^2), the rounding error
  *                   O(eps |E| / h) (about 1e-4 .. 1e-3 in complex128)
@@ -581,6 +582,8 @@ int qtn_bucket_get_info(const qtn_bucket *b, qtn_bucket_info *out);
  * After some calls the library keeps the descriptors in device memory of its
  * own (workspace_bytes, until qtn_bucket_free), which later calls on that
  * device use instead of the copy; calls under stream capture do not allocate.
+ * A graph that captured a call reads the bucket's descriptors at every replay:
+ * the bucket must outlive it.
  * Errors: QTN_EINVAL, QTN_ENOMEM (buffer or workspace too small),
  *         QTN_EDEVICE.
  */

@@ -1104,7 +1104,7 @@ int prog_prec(const Schedule &s, int range) {
 // Step launches of the light cones' task chains, where the rule takes them.
 constexpr double kAloneMs = 3.5e-3;      // a launch of one tiny group
 constexpr double kStepUnits = 4;         // units a wave takes once those are busy: 40 vertices,
-                                         // mixed, 9.6 ms with 1, 8.7 with 4, 8.8 with 16
+                                         // mixed, 6.21 ms with 1, 5.94 with 4, 6.18 with 16
 constexpr double kStepMaxUnits = 16384;  // most units a task
 void plan_steps(Schedule &s) {
   double units = 0;
@@ -1124,13 +1124,14 @@ void plan_steps(Schedule &s) {
   }
   // Above the line the groups fill the chip by themselves, and the four
   // streams overlap the ends of launches of unlike light cones, which a step
-  // makes wait for each other.  Step launches against four streams, by units
-  // a task: 17 (20 vertices, depth 3) 286 us against 355; 469 (27 sets of a
-  // 22-vertex one) 333 against 430; 3,900 (40 vertices, mixed precision) 8.7
-  // ms against 10.3; 21,500 (17 sets of a depth-4 one) 8.7 ms against 8.5;
-  // 87,000 (32 sets of the 30-vertex one) 108 ms against 100.  (With the cell
-  // units as they are now the first four take 170 us, 288 us, 6.0 ms and, on
-  // streams, 8.7 ms.)  A schedule that is mostly other mappings keeps its
+  // makes wait for each other.  Four streams against step launches, by units
+  // a task: 17 (20 vertices, depth 3) 281 us against 159; 469 (27 sets of a
+  // 22-vertex one) 342 against 269; 1,479 (quartic, 24 vertices, depth 3) 2.46
+  // ms against 1.38; 3,912 (40 vertices, mixed precision) 6.80 against 5.94;
+  // 10,984 (4 sets of the 30-vertex depth-4 one) 13.64 against 13.58; 15,268 (9
+  // sets of a 16-vertex one) 6.58 against 6.36; 21,968 (8 sets of the 30-vertex
+  // one) 25.7 against 26.0; 87,871 (32 sets) 99.3 against 99.9, in complex64
+  // 62.0 against 71.8.  A schedule that is mostly other mappings keeps its
   // streams.
   if (n_tasks == 0 || n_other * 8 > n_tasks || units > kStepMaxUnits * (double)n_tasks) return;
   s.steps.resize(n_steps);
@@ -1148,11 +1149,13 @@ void plan_steps(Schedule &s) {
       if (t->kind == QTN_K_WIDE) step_units += (double)s.groups[t->index].n_units * s.n_sets;
     const double per_wave = std::min(kStepUnits, step_units / kStepWaves);
     // A segment is one workgroup's chain and wants many waves; groups that
-    // fill the chip want small workgroups, which start and end singly.  40
-    // vertices, mixed: 7.9 ms with 256 threads, 8.2 with 512, 8.6 with 1,024;
-    // 20 vertices, depth 3: 206, 169 and 165 us.  The cost model's times say
-    // where a segment outlasts the groups all the same (quartic graphs of
-    // 171 to 284 vertices at depth 3: 420-600, 341-471 and 337-446 us).
+    // fill the chip want small workgroups, which start and end singly.  256,
+    // 512 and 1,024 threads: 40 vertices, mixed, 5.95, 6.11 and 6.26 ms; 9 sets
+    // of a 16-vertex depth-4 network 6.35, 6.73 and 6.77; 20 vertices, depth 3,
+    // 195, 157 and 148 us.  The cost model's times say where a segment outlasts
+    // the groups all the same (quartic graphs of 171, 228 and 284 vertices at
+    // depth 3, complex64: 612, 499 and 491 us, 500, 393 and 357, 516, 413 and
+    // 375; by those times 470, 354 and 376).
     double seg_ms = 0, wide_ms = 0;
     for (const Task *t : in_step[j])
       (t->kind == QTN_K_BLOCK ? seg_ms : wide_ms) = std::max(t->kind == QTN_K_BLOCK ? seg_ms : wide_ms, t->ms);

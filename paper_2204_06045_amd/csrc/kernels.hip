@@ -796,13 +796,15 @@ __device__ __forceinline__ void cell_op(T *acc, bool first, int k, const CellLan
 // the unit are formed by lane k for operand k, and by lane n_ops for the
 // output.
 //
-// Bound: vector instruction issue and, behind it, one load round trip per
-// operand (a group of 24 bits, 4 summed, 7 operands, complex128: 250
-// instructions a unit keep the SIMDs 55% busy; of the 514 it took before, the
-// complex products needed 130, and they kept them 67% busy).  So what can be
-// scalar is: cell offsets are shifts of one word per operand, no descriptor is
-// read from memory, and the next operand's lane offset is read while this
-// one's loads are under way.
+// Bound: the path that returns loaded data to the registers, busy on 69% of the
+// cycles without serial bits and on 89% with two (32 sets of the 30-vertex
+// depth-4 network, complex128, stored kernel choices), and behind it one load
+// round trip per operand.  Vector instructions kept the SIMDs 67% busy while a
+// unit took 514 of them, of which the complex products needed 130 (a group of 24
+// bits, 4 summed, 7 operands); it takes 250 now, and on that workload they keep
+// them 30% and 54% busy.  So what can be scalar is: cell offsets are shifts of
+// one word per operand, no descriptor is read from memory, and the next operand's
+// lane offset is read while this one's loads are under way.
 template <class T, bool CVT, int CB, int SL, bool ORD>
 __device__ __forceinline__ void cell_unit(const GI &G, const CellLane &cl, uint64_t set_base,
                                           const uint32_t *s_tab, const T *P, uint32_t u, int lane,
