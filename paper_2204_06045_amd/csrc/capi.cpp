@@ -167,14 +167,23 @@ struct Schedule : Layout {
 constexpr size_t kDescPart = 128;
 std::atomic<size_t> g_desc_bytes{0};
 
+// Memory of the current device, asked for once per device (0: unknown).
+size_t device_bytes() {
+  constexpr int kMaxDevices = 64;
+  static std::atomic<size_t> known[kMaxDevices];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+  size_t all = known[dev];
+  if (!all && hipDeviceTotalMem(&all, dev) == hipSuccess) known[dev] = all;
+  return all;
+}
+
 // Null past the bound, and where the device has none left (*none).
 char *desc_alloc(size_t bytes, bool *none) {
   char *p = nullptr;
-  size_t free_bytes = 0, all = 0;
   *none = false;
-  const size_t held = g_desc_bytes.fetch_add(bytes) + bytes;
-  if (hipMemGetInfo(&free_bytes, &all) != hipSuccess ||
-      (held <= all / kDescPart && hipMalloc((void **)&p, bytes) != hipSuccess)) {
+  const size_t held = g_desc_bytes.fetch_add(bytes) + bytes, all = device_bytes();
+  if (!all || (held <= all / kDescPart && hipMalloc((void **)&p, bytes) != hipSuccess)) {
     (void)hipGetLastError();
     *none = true;
     p = nullptr;

@@ -128,9 +128,8 @@ hipError_t hipMalloc(void **p, size_t bytes) {
   if (live_bytes > most_bytes) most_bytes = live_bytes;
   return hipSuccess;
 }
-hipError_t hipMemGetInfo(size_t *free_bytes, size_t *all) {
+hipError_t hipDeviceTotalMem(size_t *all, hipDevice_t) {
   *all = kDeviceBytes;
-  *free_bytes = kDeviceBytes - live_bytes;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
