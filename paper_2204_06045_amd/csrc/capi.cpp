@@ -2730,7 +2730,8 @@ static int autotune_sets(qtn_network *net, void *d_workspace, size_t bytes, void
           if (t[ci] >= 0) best = ci;
       for (int ci = 0; ci < nc; ci++)
         if (t[ci] >= 0 && (best < 0 || t[ci] < kSwitchGain * t[best])) best = ci;
-      if (best >= 0) chosen.push_back({&G, &m, best, rule_cell >= 0 && m.wide[rule_cell] < kLeaveStepMs ? rule_cell : best});
+      const bool is_short = rule_cell >= 0 && m.wide[rule_cell] < kLeaveStepMs;
+      if (best >= 0) chosen.push_back({&G, &m, best, is_short ? rule_cell : best});
       qtn_tune_rec tr;
       std::memset(&tr, 0, sizeof tr);
       group_features(G, pl, net->precision, tr.features);
